@@ -399,8 +399,7 @@ int airg_export_level(airg_handle h, int level, airg_level_arrays* o) {
       DBuf<int32_t> inv(L.n, s);
       invert_perm(L.pos.get(), L.n, inv.get(), s);
       CSR A;
-      permute_rows(L.A, inv.get(), inv.get(), L.n, A, s);
-      sort_rows(A, s);
+      permute_rows(L.A, inv.get(), inv.get(), L.n, A, s, true);
       copy_csr_out(o->a_rowptr, o->a_col, o->a_val, &A, s, "level matrix");
       AIRG_HIP(hipStreamSynchronize(s));
     } else {

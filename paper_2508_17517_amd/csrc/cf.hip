@@ -5,6 +5,7 @@
 #include <cmath>
 
 #include "kernels.hpp"
+#include "rows.hpp"
 
 namespace airg {
 
@@ -90,27 +91,31 @@ void launch_check_map(const int32_t* m, int64_t n, int64_t lo, int64_t hi, int32
 
 // ------------------------------------------------------------------ strength
 // S_ij = 1 iff j != i, a_ij != 0 and |a_ij| >= theta * max_{k != i} |a_ik|
-__global__ void strength_kernel(CSRView A, double theta, int8_t* mask, int64_t* row_count) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+template <int G>
+__global__ __launch_bounds__(256) void strength_kernel(CSRView A, double theta, int8_t* __restrict__ mask) {
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= A.rows) return;
-  int s = A.rowptr[i], e = A.rowptr[i + 1];
+  const int s = A.rowptr[i], e = A.rowptr[i + 1];
   double m = 0.0;
-  for (int p = s; p < e; ++p)
+  for (int p = s + lane; p < e; p += G)
     if (A.col[p] != i) m = fmax(m, fabs(A.val[p]));
-  double thr = theta * m;
-  int64_t cnt = 0;
-  for (int p = s; p < e; ++p) {
-    double v = A.val[p];
-    int8_t st = (A.col[p] != i && v != 0.0 && fabs(v) >= thr) ? 1 : 0;
-    mask[p] = st;
-    cnt += st;
+#pragma unroll
+  for (int o = G / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, G));
+  const double thr = theta * m;
+  for (int p = s + lane; p < e; p += G) {
+    const double v = A.val[p];
+    mask[p] = (A.col[p] != i && v != 0.0 && fabs(v) >= thr) ? 1 : 0;
   }
-  if (row_count) row_count[i] = cnt;
 }
 
-void launch_strength(const CSR& A, double theta, int8_t* mask, int64_t* row_count, hipStream_t s) {
+void launch_strength(const CSR& A, double theta, int8_t* mask, hipStream_t s) {
   if (A.rows <= 0) return;
-  strength_kernel<<<blocks_for(A.rows, kBlock), kBlock, 0, s>>>(view(A), theta, mask, row_count);
+  const double avg = (double)A.nnz / (double)A.rows;
+#define AIRG_CALL(G, CAP) \
+  strength_kernel<G><<<blocks_for(A.rows, 256 / G), 256, 0, s>>>(view(A), theta, mask)
+  AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
   AIRG_CHECK_LAUNCH();
 }
 
@@ -198,7 +203,7 @@ __global__ void pmisr_finalize_kernel(int8_t* state, int64_t n, int32_t* undecid
   if (i >= n) return;
   int8_t s = state[i];
   if (s == kFNew) state[i] = kF;
-  else if (s == kU) atomicAdd(undecided, 1);
+  else if (s == kU) *undecided = 1;  // the host only asks whether any is left
 }
 
 void launch_pmisr_select(const CSR& A, const int8_t* mask, const int64_t* st_off,
@@ -224,25 +229,52 @@ void launch_pmisr_finalize(int8_t* state, int64_t n, int32_t* undecided, hipStre
 }
 
 // ------------------------------------------------------------------ DDC
-// r_i = sum_{j in F, j != i} |a_ij| / |a_ii| (left to right) for F rows.
-__global__ void ddc_ratio_kernel(CSRView A, const int8_t* state, const double* diag, double* r,
-                                 unsigned long long* rmax_bits, int32_t* nf) {
+// r_i = sum_{j in F, j != i} |a_ij| / |a_ii| (left to right) for F rows; the
+// largest and the number of F rows are reduced per workgroup before their
+// atomics, as the histogram's bins are (an atomic per row on one address, or on
+// few bins, took 4.6 and 23.5 ms a setup at FV 2048^2).
+__global__ __launch_bounds__(256) void ddc_ratio_kernel(CSRView A, const int8_t* state, const double* diag,
+                                                        double* r, unsigned long long* rmax_bits,
+                                                        int32_t* nf) {
+  __shared__ unsigned long long smax[4];
+  __shared__ int scnt[4];
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.rows) return;
-  if (state[i] != kF) {
-    r[i] = 0.0;
-    return;
-  }
-  double sum = 0.0;
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) {
-    int j = A.col[p];
-    if (j != i && state[j] == kF) sum = sum + fabs(A.val[p]);
-  }
-  double ri = sum / fabs(diag[i]);
-  r[i] = ri;
   // non-negative doubles order like their bit patterns
-  atomicMax(rmax_bits, (unsigned long long)__double_as_longlong(ri));
-  atomicAdd(nf, 1);
+  unsigned long long m = 0;
+  const bool f = i < A.rows && state[i] == kF;
+  if (f) {
+    double sum = 0.0;
+    for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) {
+      int j = A.col[p];
+      if (j != i && state[j] == kF) sum = sum + fabs(A.val[p]);
+    }
+    double ri = sum / fabs(diag[i]);
+    r[i] = ri;
+    m = (unsigned long long)__double_as_longlong(ri);
+  } else if (i < A.rows) {
+    r[i] = 0.0;
+  }
+  const int c = (int)__popcll(__ballot(f));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long u = __shfl_xor(m, o, 64);
+    m = u > m ? u : m;
+  }
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    smax[w] = m;
+    scnt[w] = c;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int k = 1; k < 4; ++k) {
+    smax[0] = smax[k] > smax[0] ? smax[k] : smax[0];
+    scnt[0] += scnt[k];
+  }
+  if (scnt[0] == 0) return;
+  if (smax[0] > __hip_atomic_load(rmax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(rmax_bits, smax[0]);
+  atomicAdd(nf, scnt[0]);
 }
 
 __device__ __forceinline__ int ddc_bin(double r, double rmax) {
@@ -250,13 +282,22 @@ __device__ __forceinline__ int ddc_bin(double r, double rmax) {
   return q >= 999.0 ? 999 : (int)q;
 }
 
-__global__ void ddc_hist_kernel(const double* r, const int8_t* state, int64_t n, double rmax,
-                                int32_t* counts) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (state[i] != kF) return;
-  double ri = r[i];
-  if (ri > 0.0) atomicAdd(&counts[ddc_bin(ri, rmax)], 1);
+// 16 elements per thread, the bins in LDS
+constexpr int kHistPer = 16;
+__global__ __launch_bounds__(256) void ddc_hist_kernel(const double* r, const int8_t* state, int64_t n,
+                                                       double rmax, int32_t* counts) {
+  __shared__ int32_t bins[1000];
+  for (int b = threadIdx.x; b < 1000; b += 256) bins[b] = 0;
+  __syncthreads();
+  for (int q = 0; q < kHistPer; ++q) {
+    const int64_t i = ((int64_t)blockIdx.x * kHistPer + q) * 256 + threadIdx.x;
+    if (i >= n || state[i] != kF) continue;
+    double ri = r[i];
+    if (ri > 0.0) atomicAdd(&bins[ddc_bin(ri, rmax)], 1);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < 1000; b += 256)
+    if (bins[b]) atomicAdd(&counts[b], bins[b]);
 }
 
 __global__ void ddc_convert_kernel(const double* r, int8_t* state, int64_t n, double rmax,
@@ -271,14 +312,14 @@ __global__ void ddc_convert_kernel(const double* r, int8_t* state, int64_t n, do
 void launch_ddc_ratio(const CSR& A, const int8_t* state, const double* diag, double* r,
                       unsigned long long* rmax_bits, int32_t* nf, hipStream_t s) {
   if (A.rows <= 0) return;
-  ddc_ratio_kernel<<<blocks_for(A.rows, kBlock), kBlock, 0, s>>>(view(A), state, diag, r,
+  ddc_ratio_kernel<<<blocks_for(A.rows, 256), 256, 0, s>>>(view(A), state, diag, r,
                                                                 rmax_bits, nf);
   AIRG_CHECK_LAUNCH();
 }
 void launch_ddc_hist(const double* r, const int8_t* state, int64_t n, double rmax, int32_t* counts,
                      hipStream_t s) {
   if (n <= 0) return;
-  ddc_hist_kernel<<<blocks_for(n, kBlock), kBlock, 0, s>>>(r, state, n, rmax, counts);
+  ddc_hist_kernel<<<blocks_for(n, 256 * kHistPer), 256, 0, s>>>(r, state, n, rmax, counts);
   AIRG_CHECK_LAUNCH();
 }
 void launch_ddc_convert(const double* r, int8_t* state, int64_t n, double rmax, int edge,
@@ -299,34 +340,46 @@ void launch_flag(const int8_t* state, int64_t n, int which, int64_t* out, hipStr
   AIRG_CHECK_LAUNCH();
 }
 
-__global__ void extract_count_kernel(CSRView A, const int8_t* state, int rs, int cs, int64_t* count,
-                                     const int64_t* rowidx) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The entries of the rows in state rs whose columns are in state cs: a group of
+// G lanes per row at consecutive addresses, FILL writing them, else counting.
+template <int G, bool FILL>
+__global__ __launch_bounds__(256) void extract_kernel(CSRView A, const int8_t* __restrict__ state, int rs,
+                                                      int cs, const int64_t* __restrict__ rowidx,
+                                                      const int64_t* __restrict__ colidx,
+                                                      int32_t* __restrict__ count,
+                                                      const int32_t* __restrict__ rowptr_out,
+                                                      int32_t* __restrict__ col_out,
+                                                      double* __restrict__ val_out) {
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= A.rows || state[i] != rs) return;
-  int64_t c = 0;
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) c += (state[A.col[p]] == cs);
-  count[rowidx[i]] = c;
-}
-__global__ void extract_fill_kernel(CSRView A, const int8_t* state, int rs, int cs,
-                                    const int64_t* rowidx, const int64_t* colidx,
-                                    const int32_t* rowptr_out, int32_t* col_out, double* val_out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.rows || state[i] != rs) return;
-  int64_t q = rowptr_out[rowidx[i]];
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) {
-    int j = A.col[p];
-    if (state[j] == cs) {
-      col_out[q] = (int32_t)colidx[j];
-      val_out[q] = A.val[p];
-      ++q;
+  const int s = A.rowptr[i], e = A.rowptr[i + 1];
+  const int64_t row = rowidx[i];
+  const int o = FILL ? rowptr_out[row] : 0;
+  int n = 0;
+  for (int p0 = s; p0 < e; p0 += G) {
+    const int p = p0 + lane;
+    const int j = p < e ? A.col[p] : -1;
+    const bool keep = j >= 0 && state[j] == cs;
+    const unsigned long long b = group_ballot<G>(keep);
+    if (FILL && keep) {
+      const int at = o + n + bits_below(b, lane);
+      col_out[at] = (int32_t)colidx[j];
+      val_out[at] = A.val[p];
     }
+    n += (int)__popcll(b);
   }
+  if (!FILL && lane == 0) count[row] = n;
 }
-void launch_extract_count(const CSR& A, const int8_t* state, int rs, int cs, int64_t* count,
+void launch_extract_count(const CSR& A, const int8_t* state, int rs, int cs, int32_t* count,
                           const int64_t* rowidx, hipStream_t s) {
   if (A.rows <= 0) return;
-  extract_count_kernel<<<blocks_for(A.rows, kBlock), kBlock, 0, s>>>(view(A), state, rs, cs, count,
-                                                                    rowidx);
+  const double avg = (double)A.nnz / (double)A.rows;
+#define AIRG_CALL(G, CAP)                                                                            \
+  extract_kernel<G, false><<<blocks_for(A.rows, 256 / G), 256, 0, s>>>(view(A), state, rs, cs, rowidx, \
+                                                                       nullptr, count, nullptr, nullptr, nullptr)
+  AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
   AIRG_CHECK_LAUNCH();
 }
 void launch_extract_fill(const CSR& A, const int8_t* state, int rs, int cs, const int64_t* fidx,
@@ -335,8 +388,12 @@ void launch_extract_fill(const CSR& A, const int8_t* state, int rs, int cs, cons
   if (A.rows <= 0) return;
   const int64_t* rowidx = rs == kF ? fidx : cidx;
   const int64_t* colidx = cs == kF ? fidx : cidx;
-  extract_fill_kernel<<<blocks_for(A.rows, kBlock), kBlock, 0, s>>>(
-      view(A), state, rs, cs, rowidx, colidx, rowptr_out, col_out, val_out);
+  const double avg = (double)A.nnz / (double)A.rows;
+#define AIRG_CALL(G, CAP)                                                                           \
+  extract_kernel<G, true><<<blocks_for(A.rows, 256 / G), 256, 0, s>>>(view(A), state, rs, cs, rowidx, \
+                                                                      colidx, nullptr, rowptr_out, col_out, val_out)
+  AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
   AIRG_CHECK_LAUNCH();
 }
 

@@ -130,16 +130,14 @@ int64_t flag_scan(const DBuf<int8_t>& state, int64_t n, int which, DBuf<int64_t>
 
 void extract(const CSR& A, const DBuf<int8_t>& state, int rs, int cs, const DBuf<int64_t>& fidx,
              const DBuf<int64_t>& cidx, int64_t nrows, int64_t ncols, CSR& out, hipStream_t s) {
-  DBuf<int64_t> cnt(nrows, s), off(nrows + 1, s), work(scan_work_size(nrows), s);
+  DBuf<int32_t> cnt(nrows, s);
+  DBuf<int64_t> work(rowptr_work_size(nrows), s), total(1, s);
   launch_extract_count(A, state.get(), rs, cs, cnt.get(), rs == 1 ? fidx.get() : cidx.get(), s);
-  launch_scan_i64(cnt.get(), off.get(), nrows, work.get(), s);
   out.rows = nrows;
   out.cols = ncols;
   out.rowptr.alloc(nrows + 1, s);
-  DBuf<int32_t> ovf(1, s);
-  launch_fill_i32(ovf.get(), 1, 0, s);
-  launch_offsets_to_i32(off.get(), out.rowptr.get(), nrows + 1, ovf.get(), s);
-  out.nnz = fetch(off.get() + nrows, s);
+  launch_rowptr_scan(cnt.get(), nrows, out.rowptr.get(), total.get(), work.get(), s);
+  out.nnz = fetch(total.get(), s);
   out.col.alloc(out.nnz, s);
   out.val.alloc(out.nnz, s);
   launch_extract_fill(A, state.get(), rs, cs, fidx.get(), cidx.get(), out.rowptr.get(),
@@ -151,7 +149,7 @@ void cf_split(const CSR& A, const DBuf<double>& diag, int level, const airg_para
               DBuf<int8_t>& state, int& rounds, hipStream_t s) {
   const int64_t n = A.rows;
   DBuf<int8_t> mask(A.nnz, s);
-  launch_strength(A, p.strong_threshold, mask.get(), nullptr, s);
+  launch_strength(A, p.strong_threshold, mask.get(), s);
   DBuf<int64_t> colcount(n, s), st_off(n + 1, s), cursor(n, s), work(scan_work_size(n), s);
   colcount.zero();
   launch_pattern_transpose_count(A, mask.get(), colcount.get(), s);
@@ -273,10 +271,11 @@ bool coarsen(Hierarchy& H, int lvl, const CSR& A, Level& L, CSR& Anext) {
     DBuf<int64_t> flist(L.nF, s), clist(L.nC, s);
     launch_inverse_map(L.state.get(), n, 1, L.fidx.get(), flist.get(), s);
     launch_inverse_map(L.state.get(), n, 2, L.cidx.get(), clist.get(), s);
-    CSR R, P, AP;
+    CSR R, AP;
     build_r(L.Z_nat, flist.get(), clist.get(), n, R, s);
-    build_p(L.state.get(), L.fidx.get(), L.cidx.get(), L.cmap_nat.get(), n, L.nC, P, s);
-    spgemm(A, P, AP, s);
+    DBuf<int32_t> pmap(n, s);
+    one_point_map(L.state.get(), L.fidx.get(), L.cidx.get(), L.cmap_nat.get(), n, pmap.get(), s);
+    one_point_product(A, pmap.get(), L.nC, AP, s);
     spgemm(R, AP, RAP, s);
   }
   {
@@ -506,8 +505,7 @@ void finalize_hierarchy(Hierarchy& H) {
     }
     rank_points(key[nl - 1].get(), Lc.n, Lc.pos.get(), s);
     CSR Ap;
-    permute_rows(Lc.A, Lc.pos.get(), Lc.pos.get(), Lc.n, Ap, s);
-    sort_rows(Ap, s);
+    permute_rows(Lc.A, Lc.pos.get(), Lc.pos.get(), Lc.n, Ap, s, true);
     Lc.A = std::move(Ap);
     Lc.a_permuted = true;
   } else {
@@ -532,8 +530,7 @@ void finalize_hierarchy(Hierarchy& H) {
       frank.alloc(L.nF, s);
       rank_f_points(L.state.get(), L.fidx.get(), key[l].get(), L.n, L.nF, frank.get(), s);
       if (asm_smoother) {
-        permute_rows(Ahat_setup, frank.get(), frank.get(), L.nF, L.Ahat, s);
-        sort_rows(L.Ahat, s);
+        permute_rows(Ahat_setup, frank.get(), frank.get(), L.nF, L.Ahat, s, true);
       }
       if (dinv_setup.get()) {
         L.dinv.alloc(L.nF, s);
@@ -542,15 +539,13 @@ void finalize_hierarchy(Hierarchy& H) {
       launch_nested_pos_ranked(L.state.get(), L.fidx.get(), L.cidx.get(), frank.get(), L.nF,
                                N.pos.get(), L.n, L.pos.get(), s);
       CSR Aff;
-      permute_rows(L.Aff, frank.get(), frank.get(), L.nF, Aff, s);
+      // ascending columns in the solve numbering: neighbouring lanes gather
+      // neighbouring elements
+      permute_rows(L.Aff, frank.get(), frank.get(), L.nF, Aff, s, true);
       if (H.p.keep_setup_data) L.Aff_nat = std::move(L.Aff);
       L.Aff = std::move(Aff);
       permute_rows(L.Afc_nat, frank.get(), N.pos.get(), L.nC, L.Afc, s);
-      permute_rows(L.Z_nat, N.pos.get(), frank.get(), L.nF, L.Z, s);
-      // ascending columns in the solve numbering: neighbouring lanes gather
-      // neighbouring elements
-      sort_rows(L.Aff, s);
-      sort_rows(L.Z, s);
+      permute_rows(L.Z_nat, N.pos.get(), frank.get(), L.nF, L.Z, s, true);
       launch_remap_ranked(L.cmap_nat.get(), N.pos.get(), frank.get(), L.nF, L.cmap.get(), s);
     } else {
       if (asm_smoother) L.Ahat = std::move(Ahat_setup);
@@ -576,17 +571,14 @@ void finalize_hierarchy(Hierarchy& H) {
     if (H.p.smooth_type != AIRG_SMOOTH_TYPE_F) {
       if (L.Acf_nat.rows != L.nC || L.Acc_nat.rows != L.nC || L.alpha_c.empty())
         fail(AIRG_ERR_INVALID, "C-point smoothing data missing on level " + std::to_string(l));
-      permute_rows(L.Acf_nat, N.pos.get(), order ? frank.get() : nullptr, L.nF, L.cf.m, s);
-      permute_rows(L.Acc_nat, N.pos.get(), N.pos.get(), L.nC, L.cc.m, s);
-      sort_rows(L.cf.m, s);
-      sort_rows(L.cc.m, s);
+      permute_rows(L.Acf_nat, N.pos.get(), order ? frank.get() : nullptr, L.nF, L.cf.m, s, true);
+      permute_rows(L.Acc_nat, N.pos.get(), N.pos.get(), L.nC, L.cc.m, s, true);
       L.cf.tpr = pick_tpr(L.cf.m.rows, L.cf.m.nnz);
       L.cc.tpr = pick_tpr(L.cc.m.rows, L.cc.m.nnz);
       if (asm_smoother) {
         CSR hc;
         fixed_sparsity_inverse(L.Acc_nat, L.alpha_c, hc, s);
-        permute_rows(hc, N.pos.get(), N.pos.get(), L.nC, L.hat_cc.m, s);
-        sort_rows(L.hat_cc.m, s);
+        permute_rows(hc, N.pos.get(), N.pos.get(), L.nC, L.hat_cc.m, s, true);
         L.hat_cc.tpr = pick_tpr(L.hat_cc.m.rows, L.hat_cc.m.nnz);
       }
     }
@@ -623,8 +615,7 @@ void finalize_hierarchy(Hierarchy& H) {
     H.levels[l].in_off = H.stacked_len;
     H.stacked_len += H.levels[l].n;
   }
-  permute_rows(H.A0, H.levels[0].pos.get(), H.levels[0].pos.get(), H.n0, H.Aperm, s);
-  if (order) sort_rows(H.Aperm, s);
+  permute_rows(H.A0, H.levels[0].pos.get(), H.levels[0].pos.get(), H.n0, H.Aperm, s, order);
   H.tpr_top = pick_tpr(H.Aperm.rows, H.Aperm.nnz);
   // The rows of the top matrix and of every Z are points of several blocks
   // of the nested numbering (level l's F points, then level l+1's, ...),

@@ -170,9 +170,11 @@ void launch_offset_copy_i32(int32_t* dst, const int32_t* src, int64_t n, int64_t
 // `work` needs scan_work_size(n) int64s.  in and out may alias.
 size_t scan_work_size(int64_t n);
 void launch_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* work, hipStream_t s);
-// rowptr (int32) from int64 offsets; sets *overflow = 1 if any exceeds int32.
-void launch_offsets_to_i32(const int64_t* off, int32_t* rowptr, int64_t n1, int32_t* overflow,
-                           hipStream_t s);
+// Row pointers of rows of cnt[i] entries: rowptr[i] = sum_{j<i} cnt[j] (int32),
+// i <= n, and the sum of all in 64 bits.  `work` needs rowptr_work_size(n) int64s.
+size_t rowptr_work_size(int64_t n);
+void launch_rowptr_scan(const int32_t* cnt, int64_t n, int32_t* rowptr, int64_t* total, int64_t* work,
+                        hipStream_t s);
 
 // ---------------------------------------------------------------- spmv.hip
 // Rows-per-thread-group shape of a CSR kernel (lanes per row, power of 2).
@@ -258,8 +260,7 @@ void launch_check_csr(const CSR& A, int32_t* flags, hipStream_t s);
 void launch_check_map(const int32_t* m, int64_t n, int64_t lo, int64_t hi, int32_t* flags,
                       hipStream_t s);
 // Strength: mask[p] = 1 iff entry p is a strong off-diagonal connection.
-void launch_strength(const CSR& A, double theta, int8_t* mask, int64_t* row_count,
-                     hipStream_t s);
+void launch_strength(const CSR& A, double theta, int8_t* mask, hipStream_t s);
 // Transpose of the strong pattern: ST (rowptr/col) from mask.
 void launch_pattern_transpose_count(const CSR& A, const int8_t* mask, int64_t* colcount,
                                     hipStream_t s);
@@ -283,7 +284,7 @@ void launch_ddc_convert(const double* r, int8_t* state, int64_t n, double rmax, 
 void launch_flag(const int8_t* state, int64_t n, int which, int64_t* out, hipStream_t s);
 // Sub-block extraction (rows with state rs, columns with state cs, columns
 // renumbered through idx (F index or C index)).
-void launch_extract_count(const CSR& A, const int8_t* state, int rs, int cs, int64_t* count,
+void launch_extract_count(const CSR& A, const int8_t* state, int rs, int cs, int32_t* count,
                           const int64_t* rowidx, hipStream_t s);
 void launch_extract_fill(const CSR& A, const int8_t* state, int rs, int cs,
                          const int64_t* fidx, const int64_t* cidx, const int32_t* rowptr_out,
@@ -402,14 +403,16 @@ void drop_lump(const CSR& Ain, double tol, bool lump, CSR& Aout, int32_t* bad_di
 // R = [Z I] in level numbering (rows n_c, columns n).
 void build_r(const CSR& Z, const int64_t* fpos, const int64_t* cpos, int64_t n, CSR& R,
              hipStream_t s);
-// P = [W; I] in level numbering (rows n, columns n_c).
-void build_p(const int8_t* state, const int64_t* fidx, const int64_t* cidx, const int32_t* cmap,
-             int64_t n, int64_t nc, CSR& P, hipStream_t s);
+// P = [W; I] as a map of the level's nodes to their coarse column (-1: none).
+void one_point_map(const int8_t* state, const int64_t* fidx, const int64_t* cidx, const int32_t* cmap,
+                   int64_t n, int32_t* pmap, hipStream_t s);
+// A P for the P of one_point_map (nc columns), as spgemm would form it.
+void one_point_product(const CSR& A, const int32_t* pmap, int64_t nc, CSR& AP, hipStream_t s);
 // Row permutation + column renumbering: out row newrow[i] = row i of A with
 // columns mapped through colmap (either map NULL: identity).  Column order within a row
-// is preserved.
+// is preserved, or ascending with sorted.
 void permute_rows(const CSR& A, const int32_t* newrow, const int32_t* colmap, int64_t out_cols,
-                  CSR& out, hipStream_t s);
+                  CSR& out, hipStream_t s, bool sorted = false);
 // B = A_fc + A_ff W for the one-point W given by cmap (rows ascending by
 // column; entries with equal columns summed A_fc first, then A_ff in order).
 void merge_fc_ffw(const CSR& Afc, const CSR& Aff, const int32_t* cmap, CSR& B, hipStream_t s);

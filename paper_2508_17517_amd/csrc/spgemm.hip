@@ -1,96 +1,53 @@
 // Sparse products and structural kernels of the setup (paper Eqs. z,
 // fixed_sparsity, prolong and the coarse product R A P).
 //
-// C = A B is formed row by row with a k-way merge of the sorted rows of B
-// selected by row i of A (one thread per row for short rows of A, one
-// wavefront per row for longer ones), so every c_ij is accumulated over A's
-// entries in stored (ascending k) order starting from 0.0 and the result does
-// not depend on scheduling.  Exact zeros are dropped afterwards.
+// C = A B is formed row by row: a group of lanes takes a row of A, visits its
+// entries k in stored (ascending) order one after the other and adds
+// a_ik * (row k of B), whose columns are distinct, into a table of columns in
+// LDS.  Every c_ij is so accumulated over k ascending from 0.0 and does not
+// depend on scheduling.  Exact zeros are dropped afterwards.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
 #include "kernels.hpp"
+#include "rows.hpp"
 
 namespace airg {
 
-static void scan_counts(const DBuf<int64_t>& cnt, int64_t n, DBuf<int64_t>& off, hipStream_t s) {
-  off.alloc(n + 1, s);
-  DBuf<int64_t> work(scan_work_size(n), s);
-  launch_scan_i64(cnt.get(), off.get(), n, work.get(), s);
-}
+// What a counting pass hands to the host besides its row lengths: their total
+// and three words the kernels set (zeroed here), all read in one copy.
+struct RowStat {
+  DBuf<int64_t> d;
+  int64_t h[4] = {0, 0, 0, 0};
+  explicit RowStat(hipStream_t s) : d(4, s) { launch_zero_bytes(d.get(), 4 * sizeof(int64_t), s); }
+  int32_t* flag(int k) const { return reinterpret_cast<int32_t*>(d.get() + 1 + k); }
+  int32_t value(int k) const { return (int32_t)h[1 + k]; }
+};
 
-// int32 rowptr from int64 offsets, failing on overflow.
-static int64_t offsets_to_rowptr(const DBuf<int64_t>& off, int64_t n, DBuf<int32_t>& rowptr,
-                                 hipStream_t s) {
+// Row pointers (int32) from row lengths; returns their total, failing where it
+// does not fit, and leaves st's words on the host.
+static int64_t counts_to_rowptr(const DBuf<int32_t>& cnt, int64_t n, DBuf<int32_t>& rowptr, RowStat& st,
+                                hipStream_t s) {
   rowptr.alloc(n + 1, s);
-  DBuf<int32_t> ovf(1, s);
-  launch_fill_i32(ovf.get(), 1, 0, s);
-  launch_offsets_to_i32(off.get(), rowptr.get(), n + 1, ovf.get(), s);
-  int64_t total = fetch(off.get() + n, s);
-  if (fetch(ovf.get(), s) || total > 2147483647ll)
-    fail(AIRG_ERR_NOMEM, "sparse matrix exceeds 2^31 nonzeros");
-  return total;
+  DBuf<int64_t> work(rowptr_work_size(n), s);
+  launch_rowptr_scan(cnt.get(), n, rowptr.get(), st.d.get(), work.get(), s);
+  st.d.to_host(st.h, 4);
+  AIRG_HIP(hipStreamSynchronize(s));
+  if (st.h[0] > 2147483647ll) fail(AIRG_ERR_NOMEM, "sparse matrix exceeds 2^31 nonzeros");
+  return st.h[0];
+}
+static int64_t counts_to_rowptr(const DBuf<int32_t>& cnt, int64_t n, DBuf<int32_t>& rowptr,
+                                hipStream_t s) {
+  RowStat st(s);
+  return counts_to_rowptr(cnt, n, rowptr, st, s);
 }
 
-// ------------------------------------------------------------------ k-way merge product
-__global__ void merge_init_kernel(CSRView A, CSRView B, int32_t* cur) {
+// ------------------------------------------------------------------ exact zeros
+__global__ void nonzero_count_kernel(CSRView A, int32_t* count) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= A.rows) return;
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) cur[p] = B.rowptr[A.col[p]];
-}
-
-__global__ void merge_count_kernel(CSRView A, CSRView B, int32_t* cur, int64_t* count) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.rows) return;
-  const int s = A.rowptr[i], e = A.rowptr[i + 1];
-  int64_t c = 0;
-  for (;;) {
-    int mn = 0x7fffffff;
-    for (int p = s; p < e; ++p) {
-      int q = cur[p];
-      if (q < B.rowptr[A.col[p] + 1]) mn = min(mn, B.col[q]);
-    }
-    if (mn == 0x7fffffff) break;
-    ++c;
-    for (int p = s; p < e; ++p) {
-      int q = cur[p];
-      if (q < B.rowptr[A.col[p] + 1] && B.col[q] == mn) cur[p] = q + 1;
-    }
-  }
-  count[i] = c;
-}
-
-__global__ void merge_numeric_kernel(CSRView A, CSRView B, int32_t* cur, const int32_t* rowptr,
-                                     int32_t* col, double* val) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.rows) return;
-  const int s = A.rowptr[i], e = A.rowptr[i + 1];
-  int64_t o = rowptr[i];
-  for (;;) {
-    int mn = 0x7fffffff;
-    for (int p = s; p < e; ++p) {
-      int q = cur[p];
-      if (q < B.rowptr[A.col[p] + 1]) mn = min(mn, B.col[q]);
-    }
-    if (mn == 0x7fffffff) break;
-    double acc = 0.0;
-    for (int p = s; p < e; ++p) {  // ascending k
-      int q = cur[p];
-      if (q < B.rowptr[A.col[p] + 1] && B.col[q] == mn) {
-        acc = acc + A.val[p] * B.val[q];
-        cur[p] = q + 1;
-      }
-    }
-    col[o] = mn;
-    val[o] = acc;
-    ++o;
-  }
-}
-
-__global__ void nonzero_count_kernel(CSRView A, int64_t* count) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.rows) return;
-  int64_t c = 0;
+  int32_t c = 0;
   for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) c += (A.val[p] != 0.0);
   count[i] = c;
 }
@@ -109,16 +66,15 @@ __global__ void nonzero_fill_kernel(CSRView A, const int32_t* rowptr, int32_t* c
 // Drop the explicit zeros of `in` into `out`.
 static void drop_zeros(const CSR& in, CSR& out, hipStream_t s) {
   const int64_t n = in.rows;
-  DBuf<int64_t> cnt(n, s), off;
+  DBuf<int32_t> cnt(n, s);
   unsigned nb = blocks_for(n, kBlock);
   if (n > 0) {
     nonzero_count_kernel<<<nb, kBlock, 0, s>>>(view(in), cnt.get());
     AIRG_CHECK_LAUNCH();
   }
-  scan_counts(cnt, n, off, s);
-  out.rows = n;
+    out.rows = n;
   out.cols = in.cols;
-  out.nnz = offsets_to_rowptr(off, n, out.rowptr, s);
+  out.nnz = counts_to_rowptr(cnt, n, out.rowptr, s);
   out.col.alloc(out.nnz, s);
   out.val.alloc(out.nnz, s);
   if (n > 0) {
@@ -128,154 +84,538 @@ static void drop_zeros(const CSR& in, CSR& out, hipStream_t s) {
   }
 }
 
-// The same merge with one wavefront per row of A: lane l holds the cursors of
-// A's entries s + l + 64 t (t < T), the smallest pending column is found with
-// a wave-wide min, and the products of the entries that hit it are added in
-// ascending entry order (t, then lane) -- the order of the one-thread merge,
-// so the results agree bit for bit.  Rows are visited in a wave-stride loop.
-__device__ __forceinline__ int wave_min_i32(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-  return v;
+// ------------------------------------------------------------------ merged rows
+// A stable insertion sort of entries s .. e-1 by column, by one thread.
+__device__ __forceinline__ void insertion_sort(int s, int e, int32_t* col, double* val) {
+  for (int p = s + 1; p < e; ++p) {
+    int c = col[p];
+    double v = val[p];
+    int q = p - 1;
+    while (q >= s && col[q] > c) {
+      col[q + 1] = col[q];
+      val[q + 1] = val[q];
+      --q;
+    }
+    col[q + 1] = c;
+    val[q + 1] = v;
+  }
 }
 
-template <int T, bool NUMERIC>
-__global__ __launch_bounds__(256) void wave_merge_kernel(CSRView A, CSRView B,
-                                                         const int32_t* rowptrC, int32_t* colC,
-                                                         double* valC, int64_t* count,
-                                                         int64_t nwaves) {
-  const int lane = threadIdx.x & 63;
-  const int64_t w0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (w0 >= nwaves) return;  // the grid's last block may hold spare waves
-  for (int64_t i = w0; i < A.rows; i += nwaves) {
-    const int s = A.rowptr[i], e = A.rowptr[i + 1];
-    int q[T], qe[T], head[T];
-    double a[T];
+// Position of each of the lane's entries (the t-th is entry lane + G t, of
+// column c[t]) among a row's len columns in LDS when sorted by column, equal
+// columns in entry order: the entries before it are counted, four columns a
+// read.  sc is padded with INT_MAX to a multiple of 4.
+template <int G, int T>
+__device__ __forceinline__ void rank_entries(const int32_t* sc, int len, const int (&c)[T], int lane,
+                                             int (&r)[T]) {
+#pragma unroll
+  for (int t = 0; t < T; ++t) r[t] = 0;
+  for (int j = 0; j < len; j += 4) {
+    const int4 o = *reinterpret_cast<const int4*>(sc + j);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      const int p = s + lane + 64 * t;
-      q[t] = qe[t] = 0;
-      a[t] = 0.0;
-      head[t] = 0x7fffffff;
-      if (p < e) {
-        const int k = A.col[p];
-        q[t] = B.rowptr[k];
-        qe[t] = B.rowptr[k + 1];
-        a[t] = A.val[p];
-        if (q[t] < qe[t]) head[t] = B.col[q[t]];
-      }
+      if (G * t >= len) break;
+      const int i = lane + G * t;
+      r[t] += (o.x < c[t] || (o.x == c[t] && j < i)) + (o.y < c[t] || (o.y == c[t] && j + 1 < i)) +
+              (o.z < c[t] || (o.z == c[t] && j + 2 < i)) + (o.w < c[t] || (o.w == c[t] && j + 3 < i));
     }
-    int64_t o = NUMERIC ? (int64_t)rowptrC[i] : 0;
-    int64_t c = 0;
-    for (;;) {
-      int m = 0x7fffffff;
+  }
+}
+
+// A row gathered from up to two rows with mapped columns, entries whose mapped
+// column is negative left out, sorted by column (stable) and equal columns
+// summed left to right.  Two uses:
+//   FC:  B = A_fc + A_ff W with W the one-point prolongation: row i of A_fc
+//        (columns kept), then of A_ff (column j becomes cmap[j]);
+//   !FC: A P with P one-point, cmap[j] the coarse column of node j or -1: the
+//        sums start from 0.0 and exact zeros are dropped, as in a product
+//        formed over k ascending (P's entries are 1).
+// A group of G lanes ranks the row's entries in LDS, places them, and the
+// first entry of each run of equal columns adds its run; the result goes to
+// tcol / tval at the sum of the source rows' offsets, its length to cnt.
+// As permuted rows, bound by one pass over the matrix; one thread per row with
+// insertion in global memory took 21.2 ms for the B of a setup at FV 2048^2,
+// and the k-way merges of A P 20 ms.  Rows longer than CAP are ranked from memory.
+template <int G, int CAP, bool FC>
+__global__ __launch_bounds__(256) void merge_rows_kernel(CSRView A1, CSRView A2,
+                                                         const int32_t* __restrict__ cmap,
+                                                         int32_t* __restrict__ tcol,
+                                                         double* __restrict__ tval,
+                                                         int32_t* __restrict__ cnt) {
+  constexpr int T = CAP / G;
+  __shared__ int4 sc4[256 / G][CAP / 4];
+  __shared__ double sv8[256 / G][CAP];
+  const int lane = threadIdx.x & (G - 1), g = threadIdx.x / G;
+  const int64_t i = (int64_t)blockIdx.x * (256 / G) + g;
+  if (i >= A1.rows) return;
+  const int s1 = A1.rowptr[i], len1 = A1.rowptr[i + 1] - s1;
+  const int s2 = FC ? A2.rowptr[i] : 0, len = len1 + (FC ? A2.rowptr[i + 1] - s2 : 0);
+  const int o = s1 + s2;
+  auto entry = [&](int k, int& c, double& v) {
+    if (!FC || k >= len1) {
+      const int p = FC ? s2 + k - len1 : s1 + k;
+      c = cmap[FC ? A2.col[p] : A1.col[p]];
+      v = FC ? A2.val[p] : A1.val[p];
+    } else {
+      c = A1.col[s1 + k];
+      v = A1.val[s1 + k];
+    }
+  };
+  if (len > CAP) {
+    // the same from the source rows instead of LDS; the runs by one lane
+    int e = o;
+    for (int k0 = 0; k0 < len; k0 += G) {
+      const int k = k0 + lane;
+      int c = -1, r = 0;
+      double v = 0.0;
+      if (k < len) entry(k, c, v);
+      if (c >= 0) {
+        for (int j = 0; j < len; ++j) {
+          int cj;
+          double vj;
+          entry(j, cj, vj);
+          r += cj >= 0 && (cj < c || (cj == c && j < k));
+        }
+        tcol[o + r] = c;
+        tval[o + r] = v;
+      }
+      e += (int)__popcll(group_ballot<G>(c >= 0));
+    }
+    __threadfence_block();
+    wave_order();
+    if (lane == 0) {
+      int w = o;
+      for (int p = o; p < e;) {
+        const int c = tcol[p];
+        double v = FC ? tval[p] : 0.0 + tval[p];
+        for (++p; p < e && tcol[p] == c; ++p) v = v + tval[p];
+        if (FC || v != 0.0) {
+          tcol[w] = c;
+          tval[w] = v;
+          ++w;
+        }
+      }
+      cnt[i] = w - o;
+    }
+    return;
+  }
+  int32_t* sc = reinterpret_cast<int32_t*>(sc4[g]);
+  double* sv = sv8[g];
+  int c[T], r[T];
+  double v[T];
+  int m = 0;  // entries kept
 #pragma unroll
-      for (int t = 0; t < T; ++t) m = min(m, head[t]);
-      m = wave_min_i32(m);
-      if (m == 0x7fffffff) break;
-      if constexpr (NUMERIC) {
-        double acc = 0.0;
+  for (int t = 0; t < T; ++t) {
+    c[t] = 0x7fffffff;
+    v[t] = 0.0;
+    if (G * t < len) {
+      const int k = lane + G * t;
+      bool in = k < len;
+      if (in) {
+        entry(k, c[t], v[t]);
+        in = c[t] >= 0;
+        if (!in) c[t] = 0x7fffffff;
+      }
+      m += (int)__popcll(group_ballot<G>(in));
+    }
+    if (G * t < len + 3) sc[lane + G * t] = c[t];
+  }
+  wave_order();
+  rank_entries<G, T>(sc, len, c, lane, r);
+  wave_order();
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-          const bool hit = head[t] == m;
-          double prod = 0.0;
-          if (hit) prod = a[t] * B.val[q[t]];
-          unsigned long long mask = __ballot(hit);
-          while (mask) {
-            const int l = __ffsll(mask) - 1;
-            mask &= mask - 1;
-            acc = acc + __shfl(prod, l, 64);
+  for (int t = 0; t < T; ++t)
+    if (lane + G * t < len) {
+      sc[r[t]] = c[t];
+      sv[r[t]] = v[t];
+    }
+  wave_order();
+  int w = 0;
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    if (G * t >= m) break;
+    const int p = lane + G * t;
+    bool keep = p < m && (p == 0 || sc[p - 1] != sc[p]);
+    double x = 0.0;
+    if (keep) {
+      x = FC ? sv[p] : 0.0 + sv[p];
+      for (int q = p + 1; q < m && sc[q] == sc[p]; ++q) x = x + sv[q];
+      keep = FC || x != 0.0;
+    }
+    const unsigned long long b = group_ballot<G>(keep);
+    if (keep) {
+      const int at = o + w + bits_below(b, lane);
+      tcol[at] = sc[p];
+      tval[at] = x;
+    }
+    w += (int)__popcll(b);
+  }
+  if (lane == 0) cnt[i] = w;
+}
+// rows of cnt entries at the sums of two row pointers (the second may be null)
+template <int G>
+__global__ __launch_bounds__(256) void compact_rows_kernel(int64_t rows, const int32_t* __restrict__ o1,
+                                                           const int32_t* __restrict__ o2,
+                                                           const int32_t* __restrict__ rowptr,
+                                                           const int32_t* __restrict__ tcol,
+                                                           const double* __restrict__ tval,
+                                                           int32_t* __restrict__ col,
+                                                           double* __restrict__ val) {
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
+  if (i >= rows) return;
+  const int64_t t0 = (int64_t)o1[i] + (o2 ? o2[i] : 0);
+  const int p0 = rowptr[i], len = rowptr[i + 1] - p0;
+  for (int k = lane; k < len; k += G) {
+    col[p0 + k] = tcol[t0 + k];
+    val[p0 + k] = tval[t0 + k];
+  }
+}
+template <bool FC>
+static void launch_merge_rows(const CSR& A1, const CSR& A2, const int32_t* cmap, int32_t* tcol,
+                              double* tval, int32_t* cnt, hipStream_t s) {
+  const double avg = (double)(A1.nnz + (FC ? A2.nnz : 0)) / (double)A1.rows;
+#define AIRG_CALL(G, CAP)                                                                             \
+  merge_rows_kernel<G, CAP, FC><<<blocks_for(A1.rows, 256 / G), 256, 0, s>>>(view(A1), view(A2), cmap, \
+                                                                            tcol, tval, cnt)
+  AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
+  AIRG_CHECK_LAUNCH();
+}
+
+// ------------------------------------------------------------------ hash product
+// The row-by-row product with the row of C in an LDS table of T columns (a
+// power of two; open addressing, linear probing): first pass (NUMERIC false)
+// counts each row's columns, second pass adds the products, packs the table,
+// ranks its columns and writes the row in ascending order.  A group of G lanes
+// takes the entries of one row of B at consecutive addresses; those columns
+// are distinct, so no two lanes add to one slot at a time, and the next row's
+// first entries are loaded while this row's are added.  A group stops at
+// T - G columns (*overflow: the host takes a larger table, past the largest
+// the row goes to window_product_kernel).
+//
+// Bound by the latency of the rows of B (one memory round trip each, about as
+// many in flight as the tables leave wavefronts).  The form it replaced took
+// one column of C per wavefront-wide minimum over all pending rows of B:
+// R (A P) of level 6 at FV 2048^2 (70,391 rows, 32 rows of B each, 152 columns)
+// took 0.9 + 3.4 ms, the products of a whole setup 85 ms.
+template <int G, bool NUMERIC>
+__global__ __launch_bounds__(256) void hash_product_kernel(
+    CSRView A, const int32_t* __restrict__ bptr, const int32_t* __restrict__ bcol,
+    const double* __restrict__ bval, int T, int shift, const int32_t* __restrict__ rowptr,
+    int32_t* __restrict__ col, double* __restrict__ val, int32_t* __restrict__ cnt, int32_t* overflow,
+    int32_t* longest, int32_t* zeros) {
+  extern __shared__ __align__(16) unsigned char hash_lds[];
+  const int gpb = blockDim.x / G, g = threadIdx.x / G, lane = threadIdx.x & (G - 1);
+  double* hv = reinterpret_cast<double*>(hash_lds) + (size_t)(NUMERIC ? g : 0) * T;
+  int32_t* hk = reinterpret_cast<int32_t*>(hash_lds + (NUMERIC ? (size_t)gpb * T * sizeof(double) : 0)) +
+                (size_t)g * T;
+  const int64_t i = (int64_t)blockIdx.x * gpb + g;
+  if (i >= A.rows) return;
+  for (int k = lane; k < T; k += G) {
+    hk[k] = -1;
+    if (NUMERIC) hv[k] = 0.0;
+  }
+  wave_order();
+  const int s = A.rowptr[i], e = A.rowptr[i + 1];
+  int n = 0;  // columns in the table, the same in every lane of the group
+  bool full = false;
+  for (int p0 = s; p0 < e && !full; p0 += G) {
+    // the next G entries of the row: their rows of B, one per lane
+    const int np = min(G, e - p0);
+    int b0 = 0, b1 = 0;
+    double a = 0.0;
+    if (lane < np) {
+      const int k = A.col[p0 + lane];
+      b0 = bptr[k];
+      b1 = bptr[k + 1];
+      if (NUMERIC) a = A.val[p0 + lane];
+    }
+    int q0 = __shfl(b0, 0, G), q1 = __shfl(b1, 0, G);
+    int c = -1;
+    double v = 0.0;
+    if (q0 + lane < q1) {
+      c = bcol[q0 + lane];
+      if (NUMERIC) v = bval[q0 + lane];
+    }
+    for (int t = 0; t < np; ++t) {
+      const double at = NUMERIC ? __shfl(a, t, G) : 0.0;
+      // the first entries of the next row
+      int r0 = 0, r1 = 0, cn = -1;
+      double vn = 0.0;
+      if (t + 1 < np) {
+        r0 = __shfl(b0, t + 1, G);
+        r1 = __shfl(b1, t + 1, G);
+        if (r0 + lane < r1) {
+          cn = bcol[r0 + lane];
+          if (NUMERIC) vn = bval[r0 + lane];
+        }
+      }
+      for (int q = q0; q < q1; q += G) {
+        if (n + G > T) {
+          full = true;
+          break;
+        }
+        if (q > q0) {
+          c = -1;
+          if (q + lane < q1) {
+            c = bcol[q + lane];
+            if (NUMERIC) v = bval[q + lane];
           }
         }
-        if (lane == 0) {
-          colC[o] = m;
-          valC[o] = acc;
+        bool fresh = false;
+        if (c >= 0) {
+          unsigned h = ((unsigned)c * 0x9E3779B1u) >> shift;
+          for (;;) {
+            const int old = atomicCAS(&hk[h], -1, c);
+            if (old == -1) fresh = true;
+            if (old == -1 || old == c) break;
+            h = (h + 1) & (unsigned)(T - 1);
+          }
+          if (NUMERIC) hv[h] = hv[h] + at * v;
         }
-        ++o;
-      } else {
-        ++c;
+        n += (int)__popcll(group_ballot<G>(fresh));
+        wave_order();
       }
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-        if (head[t] == m) {
-          ++q[t];
-          head[t] = q[t] < qe[t] ? B.col[q[t]] : 0x7fffffff;
-        }
+      if (full) break;
+      q0 = r0;
+      q1 = r1;
+      c = cn;
+      v = vn;
     }
-    if (!NUMERIC && lane == 0) count[i] = c;
   }
+  if constexpr (!NUMERIC) {
+    if (lane == 0) {
+      cnt[i] = full ? -1 : n;
+      if (full) atomicOr(overflow, 1);
+      // most rows find a longer one counted already and need no atomic
+      if (n > __hip_atomic_load(longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(longest, n);
+    }
+    return;
+  }
+  if (full) return;  // left to window_product_kernel
+  // pack the table to its front (a slot moves down, past slots already read)
+  int m = 0;
+  for (int k0 = 0; k0 < T; k0 += G) {
+    const int k = k0 + lane;
+    const int key = k < T ? hk[k] : -1;
+    const double x = key >= 0 ? hv[k] : 0.0;
+    wave_order();
+    const unsigned long long b = group_ballot<G>(key >= 0);
+    if (key >= 0) {
+      const int at = m + bits_below(b, lane);
+      hk[at] = key;
+      hv[at] = x;
+    }
+    m += (int)__popcll(b);
+    wave_order();
+  }
+  if (lane < 3 && m + lane < T) hk[m + lane] = 0x7fffffff;
+  wave_order();
+  const int o = rowptr[i];
+  bool zero = false;
+  for (int k = lane; k < m; k += G) {
+    const int key = hk[k];
+    int r = 0;
+    for (int j = 0; j < m; j += 4) {
+      const int4 w = *reinterpret_cast<const int4*>(hk + j);
+      r += (w.x < key) + (w.y < key) + (w.z < key) + (w.w < key);
+    }
+    const double x = hv[k];
+    col[o + r] = key;
+    val[o + r] = x;
+    zero = zero || x == 0.0;
+  }
+  if (zero) atomicOr(zeros, 1);
 }
 
-__global__ void max_row_len_kernel(CSRView A, unsigned long long* mx) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < A.rows) atomicMax(mx, (unsigned long long)(A.rowptr[i + 1] - A.rowptr[i]));
-}
+// Largest table (48 KB with its values): a row of C of up to 4096 - 64 columns.
+constexpr int kHashMax = 4096;
 
 template <bool NUMERIC>
-static void launch_wave_merge(int T, const CSR& A, const CSR& B, const int32_t* rowptrC,
-                              int32_t* colC, double* valC, int64_t* count, hipStream_t s) {
-  const int64_t nwaves = std::min<int64_t>(A.rows, (int64_t)1 << 22);
-  const unsigned nb = blocks_for(nwaves * 64, 256);
-  switch (T) {
-    case 1: wave_merge_kernel<1, NUMERIC><<<nb, 256, 0, s>>>(view(A), view(B), rowptrC, colC, valC, count, nwaves); break;
-    case 2: wave_merge_kernel<2, NUMERIC><<<nb, 256, 0, s>>>(view(A), view(B), rowptrC, colC, valC, count, nwaves); break;
-    case 4: wave_merge_kernel<4, NUMERIC><<<nb, 256, 0, s>>>(view(A), view(B), rowptrC, colC, valC, count, nwaves); break;
-    case 8: wave_merge_kernel<8, NUMERIC><<<nb, 256, 0, s>>>(view(A), view(B), rowptrC, colC, valC, count, nwaves); break;
-    default: fail(AIRG_ERR_INTERNAL, "bad cursor count");
+static void launch_hash_product(const CSR& A, const CSR& B, int G, int T, const int32_t* rowptr,
+                                int32_t* col, double* val, int32_t* cnt, const RowStat& st, hipStream_t s) {
+  // as many rows per workgroup as fit 64 KB of tables
+  const size_t table = (size_t)T * (NUMERIC ? 12 : 4);
+  int threads = 256;
+  while (threads > 64 && (size_t)(threads / G) * table > 64 * 1024) threads >>= 1;
+  const size_t lds = (size_t)(threads / G) * table;
+  int shift = 32;
+  for (int t = T; t > 1; t >>= 1) --shift;
+  const unsigned nb = blocks_for(A.rows, threads / G);
+#define AIRG_CALL(GG)                                                                                 \
+  case GG:                                                                                            \
+    hash_product_kernel<GG, NUMERIC><<<nb, threads, lds, s>>>(view(A), B.rowptr.get(), B.col.get(),   \
+                                                              B.val.get(), T, shift, rowptr, col, val, \
+                                                              cnt, st.flag(0), st.flag(1), st.flag(2)); \
+    break
+  switch (G) {
+    AIRG_CALL(4);
+    AIRG_CALL(8);
+    AIRG_CALL(16);
+    AIRG_CALL(32);
+    AIRG_CALL(64);
+    default: fail(AIRG_ERR_INTERNAL, "bad lanes per row of a product");
   }
+#undef AIRG_CALL
   AIRG_CHECK_LAUNCH();
+}
+
+static int pow2_at_least(double x) {
+  int p = 1;
+  while (p < x && p < (1 << 30)) p <<= 1;
+  return p;
+}
+
+// Rows of C too long for a table, one wavefront each: the columns are taken in
+// windows of kWindow, a window's sums in LDS at their column (the entries of a
+// sorted row of B inside a window start where a binary search says), and come
+// out ascending.  The order of every sum is that of hash_product_kernel.
+constexpr int kWindow = 4096;
+__global__ void overflow_rows_kernel(const int32_t* cnt, int64_t n, int32_t* list, int32_t* nlist) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n && cnt[i] < 0) list[atomicAdd(nlist, 1)] = (int32_t)i;
+}
+template <bool NUMERIC>
+__global__ __launch_bounds__(64) void window_product_kernel(CSRView A, CSRView B, int64_t cols,
+                                                            const int32_t* __restrict__ list,
+                                                            const int32_t* __restrict__ rowptr,
+                                                            int32_t* __restrict__ col,
+                                                            double* __restrict__ val,
+                                                            int32_t* __restrict__ cnt, int32_t* zeros) {
+  __shared__ double acc[NUMERIC ? kWindow : 1];
+  __shared__ uint32_t hit[kWindow / 32];
+  const int lane = threadIdx.x;
+  const int64_t i = list[blockIdx.x];
+  const int s = A.rowptr[i], e = A.rowptr[i + 1];
+  int n = NUMERIC ? rowptr[i] : 0;
+  bool zero = false;
+  for (int64_t w0 = 0; w0 < cols; w0 += kWindow) {
+    const int64_t w1 = w0 + kWindow;
+    for (int k = lane; k < kWindow / 32; k += 64) hit[k] = 0;
+    if (NUMERIC)
+      for (int k = lane; k < kWindow; k += 64) acc[k] = 0.0;
+    wave_order();
+    for (int p = s; p < e; ++p) {
+      const int k = A.col[p];
+      int lo = B.rowptr[k], hi = B.rowptr[k + 1];
+      const int end = hi;
+      while (lo < hi) {  // the first entry at or past w0
+        const int mid = (lo + hi) >> 1;
+        if (B.col[mid] < w0) lo = mid + 1;
+        else hi = mid;
+      }
+      const double a = A.val[p];
+      for (int q = lo + lane; q < end; q += 64) {
+        const int c = B.col[q];
+        if (c >= w1) break;
+        const int t = (int)(c - w0);
+        atomicOr(&hit[t >> 5], 1u << (t & 31));
+        if (NUMERIC) acc[t] = acc[t] + a * B.val[q];
+      }
+      wave_order();
+    }
+    for (int k0 = 0; k0 < kWindow; k0 += 64) {
+      const int t = k0 + lane;
+      const bool in = (hit[t >> 5] >> (t & 31)) & 1u;
+      const unsigned long long b = __ballot(in);
+      if (NUMERIC && in) {
+        const int at = n + bits_below(b, lane);
+        col[at] = (int32_t)(w0 + t);
+        val[at] = acc[t];
+        zero = zero || acc[t] == 0.0;
+      }
+      n += (int)__popcll(b);
+    }
+    wave_order();
+  }
+  if (!NUMERIC && lane == 0) cnt[i] = n;
+  if (NUMERIC && zero) atomicOr(zeros, 1);
 }
 
 void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s) {
   if (A.cols != B.rows) fail(AIRG_ERR_INTERNAL, "spgemm shape mismatch");
   const int64_t n = A.rows;
-  unsigned nb = blocks_for(n, kBlock);
-  // rows of A with more than 8 entries: one wavefront per row; else one thread
-  int T = 0;
-  if (n > 0) {
-    DBuf<unsigned long long> mx(1, s);
-    launch_zero_bytes(mx.get(), sizeof(unsigned long long), s);
-    max_row_len_kernel<<<nb, kBlock, 0, s>>>(view(A), mx.get());
-    AIRG_CHECK_LAUNCH();
-    const unsigned long long la = fetch(mx.get(), s);
-    if (la > 8 && la <= 512) {
-      T = 1;
-      while (64 * (unsigned long long)T < la) T <<= 1;
-    }
-  }
-  DBuf<int32_t> cur;
-  if (T == 0) cur.alloc(A.nnz, s);
-  DBuf<int64_t> cnt(n, s), off;
-  if (n > 0) {
-    if (T) {
-      launch_wave_merge<false>(T, A, B, nullptr, nullptr, nullptr, cnt.get(), s);
-    } else {
-      merge_init_kernel<<<nb, kBlock, 0, s>>>(view(A), view(B), cur.get());
-      AIRG_CHECK_LAUNCH();
-      merge_count_kernel<<<nb, kBlock, 0, s>>>(view(A), view(B), cur.get(), cnt.get());
-      AIRG_CHECK_LAUNCH();
-    }
-  }
-  scan_counts(cnt, n, off, s);
   CSR full;
   full.rows = n;
   full.cols = B.cols;
-  full.nnz = offsets_to_rowptr(off, n, full.rowptr, s);
+  if (n <= 0 || A.nnz <= 0 || B.nnz <= 0) {  // no entries
+    full.rowptr.alloc(std::max<int64_t>(n, 0) + 1, s);
+    launch_fill_i32(full.rowptr.get(), std::max<int64_t>(n, 0) + 1, 0, s);
+    C = std::move(full);
+    return;
+  }
+  const double la = (double)A.nnz / (double)n, lb = (double)B.nnz / (double)B.rows;
+  // lanes: a row of B per step.  First table: room for six rows of C that see
+  // no column twice; long rows see most of theirs many times, so not above 1024
+  // until one overflows.
+  int G = std::min(64, std::max(4, pow2_at_least(lb)));
+  int T = std::min(1024, pow2_at_least(6.0 * la * lb + 2.0 * G));
+  DBuf<int32_t> cnt(n, s), list;
+  int nlist = 0;
+  for (;;) {
+    while (G < 64 && T / G > 32) G <<= 1;
+    T = std::max(T, 2 * G);
+    RowStat st(s);
+    launch_hash_product<false>(A, B, G, T, nullptr, nullptr, nullptr, cnt.get(), st, s);
+    full.nnz = counts_to_rowptr(cnt, n, full.rowptr, st, s);  // of use unless a row overflowed
+    if (!st.value(0)) {
+      T = std::min(kHashMax, std::max(2 * G, pow2_at_least(1.5 * st.value(1) + G)));
+      break;
+    }
+    if (T >= kHashMax) {
+      DBuf<int32_t> found(1, s);
+      launch_fill_i32(found.get(), 1, 0, s);
+      list.alloc(n, s);
+      overflow_rows_kernel<<<blocks_for(n, kBlock), kBlock, 0, s>>>(cnt.get(), n, list.get(), found.get());
+      AIRG_CHECK_LAUNCH();
+      nlist = fetch(found.get(), s);
+      window_product_kernel<false><<<nlist, 64, 0, s>>>(view(A), view(B), B.cols, list.get(), nullptr,
+                                                        nullptr, nullptr, cnt.get(), nullptr);
+      AIRG_CHECK_LAUNCH();
+      full.nnz = counts_to_rowptr(cnt, n, full.rowptr, s);
+      break;  // the second pass with the same G and T leaves the same rows
+    }
+    T = std::min(kHashMax, 4 * T);
+  }
+  if (!nlist) {
+    while (G < 64 && T / G > 32) G <<= 1;
+    T = std::max(T, 2 * G);
+  }
   full.col.alloc(full.nnz, s);
   full.val.alloc(full.nnz, s);
-  if (n > 0) {
-    if (T) {
-      launch_wave_merge<true>(T, A, B, full.rowptr.get(), full.col.get(), full.val.get(), nullptr,
-                              s);
-    } else {
-      merge_init_kernel<<<nb, kBlock, 0, s>>>(view(A), view(B), cur.get());
-      AIRG_CHECK_LAUNCH();
-      merge_numeric_kernel<<<nb, kBlock, 0, s>>>(view(A), view(B), cur.get(), full.rowptr.get(),
-                                                 full.col.get(), full.val.get());
-      AIRG_CHECK_LAUNCH();
-    }
+  RowStat st(s);
+  launch_hash_product<true>(A, B, G, T, full.rowptr.get(), full.col.get(), full.val.get(), nullptr, st, s);
+  if (nlist) {
+    window_product_kernel<true><<<nlist, 64, 0, s>>>(view(A), view(B), B.cols, list.get(),
+                                                     full.rowptr.get(), full.col.get(), full.val.get(),
+                                                     nullptr, st.flag(2));
+    AIRG_CHECK_LAUNCH();
   }
-  drop_zeros(full, C, s);
+  st.d.to_host(st.h, 4);
+  AIRG_HIP(hipStreamSynchronize(s));
+  if (st.value(2)) drop_zeros(full, C, s);
+  else C = std::move(full);
+}
+
+// A P for the one-point P given by pmap (pmap[j]: the coarse column of node j,
+// or -1): a relabelled, sorted and summed copy of A (merge_rows_kernel).
+void one_point_product(const CSR& A, const int32_t* pmap, int64_t nc, CSR& AP, hipStream_t s) {
+  const int64_t n = A.rows;
+  DBuf<int32_t> cnt(n, s), tcol(A.nnz, s);
+  DBuf<double> tval(A.nnz, s);
+  if (n > 0) launch_merge_rows<false>(A, A, pmap, tcol.get(), tval.get(), cnt.get(), s);
+  AP.rows = n;
+  AP.cols = nc;
+  AP.nnz = counts_to_rowptr(cnt, n, AP.rowptr, s);
+  AP.col.alloc(AP.nnz, s);
+  AP.val.alloc(AP.nnz, s);
+  if (n > 0) {
+    compact_rows_kernel<16><<<blocks_for(n, 16), 256, 0, s>>>(n, A.rowptr.get(), nullptr, AP.rowptr.get(),
+                                                              tcol.get(), tval.get(), AP.col.get(),
+                                                              AP.val.get());
+    AIRG_CHECK_LAUNCH();
+  }
 }
 
 // ------------------------------------------------------------------ fixed sparsity
@@ -330,6 +670,170 @@ __global__ void poly_add_kernel(int64_t nnz, double a, const double* t, double* 
   if (p < nnz) v[p] = v[p] + a * t[p];
 }
 
+// All masked powers and their sum, a group of G lanes per row: row i of
+// T_k = mask(T_{k-1} Aff) depends on row i of T_{k-1} alone, so the powers stay
+// in LDS and only their sum is written.  The row's columns go into a table of
+// positions; the rows of Aff that the row's entries name are taken one after
+// the other (ascending, so every sum keeps its order), their entries across
+// the lanes, the next row's loaded while this one's are looked up.  Bound by
+// the latency of those rows, d - 1 times each.  A thread per entry with a
+// binary search in every row took 11.8 ms a setup at FV 2048^2 and wrote every
+// power to memory.  *too_long is set where a row exceeds CAP entries (the
+// caller then takes that form), *zeros where a sum is exactly 0.
+struct PolyCoeffs {
+  double a[65];
+  int n;
+};
+template <int G, int CAP>
+__global__ __launch_bounds__(256) void masked_poly_kernel(CSRView A, PolyCoeffs c, double* __restrict__ out,
+                                                          int32_t* too_long, int32_t* zeros) {
+  constexpr int T = CAP / G, kTable = 2 * CAP;
+  constexpr int kShift = 32 - __builtin_ctz(kTable);
+  __shared__ double s_t[256 / G][2][CAP];
+  __shared__ int32_t s_key[256 / G][kTable];
+  __shared__ int16_t s_pos[256 / G][kTable];
+  const int lane = threadIdx.x & (G - 1), g = threadIdx.x / G;
+  const int64_t i = (int64_t)blockIdx.x * (256 / G) + g;
+  if (i >= A.rows) return;
+  const int s = A.rowptr[i], len = A.rowptr[i + 1] - s;
+  if (len > CAP) {
+    if (lane == 0) atomicOr(too_long, 1);
+    return;
+  }
+  int32_t* key = s_key[g];
+  int16_t* pos = s_pos[g];
+  for (int k = lane; k < kTable; k += G) key[k] = -1;
+  wave_order();
+  double v[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    v[t] = 0.0;
+    const int k = lane + G * t;
+    if (k < len) {
+      const int j = A.col[s + k];
+      const double x = A.val[s + k];
+      s_t[g][0][k] = x;
+      double y = j == i ? c.a[0] : 0.0;
+      if (c.n > 1) y = y + c.a[1] * x;
+      v[t] = y;
+      unsigned h = ((unsigned)j * 0x9E3779B1u) >> kShift;
+      while (atomicCAS(&key[h], -1, j) != -1) h = (h + 1) & (kTable - 1);
+      pos[h] = (int16_t)k;
+    }
+  }
+  wave_order();
+  int cur = 0;
+  for (int k = 2; k < c.n; ++k, cur ^= 1) {
+    const double* tin = s_t[g][cur];
+    double* tout = s_t[g][cur ^ 1];
+    for (int q = lane; q < len; q += G) tout[q] = 0.0;
+    wave_order();
+    for (int p0 = 0; p0 < len; p0 += G) {
+      const int np = min(G, len - p0);
+      int b0 = 0, b1 = 0;
+      if (lane < np) {
+        const int j = A.col[s + p0 + lane];
+        b0 = A.rowptr[j];
+        b1 = A.rowptr[j + 1];
+      }
+      int q0 = __shfl(b0, 0, G), q1 = __shfl(b1, 0, G);
+      int cc = -1;
+      double x = 0.0;
+      if (q0 + lane < q1) {
+        cc = A.col[q0 + lane];
+        x = A.val[q0 + lane];
+      }
+      for (int t = 0; t < np; ++t) {
+        int r0 = 0, r1 = 0, cn = -1;
+        double xn = 0.0;
+        if (t + 1 < np) {
+          r0 = __shfl(b0, t + 1, G);
+          r1 = __shfl(b1, t + 1, G);
+          if (r0 + lane < r1) {
+            cn = A.col[r0 + lane];
+            xn = A.val[r0 + lane];
+          }
+        }
+        const double w = tin[p0 + t];
+        for (int q = q0; q < q1; q += G) {
+          if (q > q0) {
+            cc = -1;
+            if (q + lane < q1) {
+              cc = A.col[q + lane];
+              x = A.val[q + lane];
+            }
+          }
+          if (cc >= 0) {
+            unsigned h = ((unsigned)cc * 0x9E3779B1u) >> kShift;
+            int found = key[h];
+            while (found != cc && found != -1) {
+              h = (h + 1) & (kTable - 1);
+              found = key[h];
+            }
+            if (found == cc) {
+              const int at = pos[h];
+              tout[at] = tout[at] + w * x;
+            }
+          }
+          wave_order();
+        }
+        q0 = r0;
+        q1 = r1;
+        cc = cn;
+        x = xn;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      if (lane + G * t < len) v[t] = v[t] + c.a[k] * tout[lane + G * t];
+    wave_order();
+  }
+  bool zero = false;
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+    if (lane + G * t < len) {
+      out[s + lane + G * t] = v[t];
+      zero = zero || v[t] == 0.0;
+    }
+  if (zero) atomicOr(zeros, 1);
+}
+
+static bool masked_poly(const CSR& Aff, const std::vector<double>& alpha, CSR& full, CSR& out,
+                        hipStream_t s) {
+  PolyCoeffs c;
+  if (alpha.size() > sizeof(c.a) / sizeof(c.a[0])) return false;
+  c.n = (int)alpha.size();
+  std::copy(alpha.begin(), alpha.end(), c.a);
+  const double avg = (double)Aff.nnz / (double)Aff.rows;
+  // 28 KB of LDS per workgroup where rows may be 2.5 times the average or more
+  // (five workgroups a CU), 56 KB for the longest; a longer row takes the next
+  int form = avg <= 2.5 ? 0 : avg <= 6.0 ? 1 : avg <= 20.0 ? 2 : avg <= 50.0 ? 3 : avg <= 100.0 ? 4 : 5;
+  for (; form < 6; ++form) {
+    RowStat st(s);
+#define AIRG_CALL(G, CAP)                                                   \
+  masked_poly_kernel<G, CAP><<<blocks_for(Aff.rows, 256 / G), 256, 0, s>>>( \
+      view(Aff), c, full.val.get(), st.flag(0), st.flag(2));                \
+  break
+    switch (form) {
+      case 0: AIRG_CALL(4, 16);
+      case 1: AIRG_CALL(8, 32);
+      case 2: AIRG_CALL(16, 64);
+      case 3: AIRG_CALL(32, 128);
+      case 4: AIRG_CALL(32, 256);
+      default: AIRG_CALL(64, 512);
+    }
+#undef AIRG_CALL
+    AIRG_CHECK_LAUNCH();
+    st.d.to_host(st.h, 4);
+    AIRG_HIP(hipStreamSynchronize(s));
+    if (st.value(0)) continue;
+    if (st.value(2)) drop_zeros(full, out, s);
+    else out = std::move(full);
+    return true;
+  }
+  return false;
+}
+
 void fixed_sparsity_inverse(const CSR& Aff, const std::vector<double>& alpha, CSR& out,
                             hipStream_t s) {
   const int64_t n = Aff.rows;
@@ -346,6 +850,8 @@ void fixed_sparsity_inverse(const CSR& Aff, const std::vector<double>& alpha, CS
   AIRG_HIP(hipMemcpyAsync(full.col.get(), Aff.col.get(), Aff.nnz * sizeof(int32_t),
                           hipMemcpyDeviceToDevice, s));
   unsigned nb = blocks_for(n, kBlock);
+  if (n > 0 && masked_poly(Aff, alpha, full, out, s)) return;
+  // rows too long for the LDS form: one launch per power
   if (n > 0) {
     poly_init_kernel<<<nb, kBlock, 0, s>>>(view(Aff), alpha[0], alpha.size() > 1 ? alpha[1] : 0.0,
                                            alpha.size() > 1 ? 1 : 0, full.val.get());
@@ -435,124 +941,168 @@ void neumann_fixed_sparsity(const CSR& Aff, int degree, CSR& out, hipStream_t s)
 
 
 // ------------------------------------------------------------------ drops
-__global__ void rdrop_count_kernel(CSRView Z, double tol, int64_t* count) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Z.rows) return;
-  double m = 0.0;
-  for (int p = Z.rowptr[i]; p < Z.rowptr[i + 1]; ++p) m = fmax(m, fabs(Z.val[p]));
-  const double thr = tol * m;
-  int64_t c = 0;
-  for (int p = Z.rowptr[i]; p < Z.rowptr[i + 1]; ++p) c += (fabs(Z.val[p]) >= thr);
-  count[i] = c;
+// A group of G lanes per row, the row at consecutive addresses; FILL writes the
+// kept entries, else they are counted.  One thread per row took 2.9 ms for the
+// restrictor drops and 14.2 ms for the coarse matrix drops of a setup at FV
+// 2048^2 (count and fill).
+template <int G>
+__device__ __forceinline__ double group_max(double m) {
+#pragma unroll
+  for (int o = G / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, G));
+  return m;
 }
-__global__ void rdrop_fill_kernel(CSRView Z, double tol, double sign, const int32_t* rowptr,
-                                  int32_t* col, double* val) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+template <int G, bool FILL>
+__global__ __launch_bounds__(256) void rdrop_kernel(CSRView Z, double tol, double sign,
+                                                    int32_t* __restrict__ count,
+                                                    const int32_t* __restrict__ rowptr,
+                                                    int32_t* __restrict__ col, double* __restrict__ val) {
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= Z.rows) return;
+  const int s = Z.rowptr[i], e = Z.rowptr[i + 1];
   double m = 0.0;
-  for (int p = Z.rowptr[i]; p < Z.rowptr[i + 1]; ++p) m = fmax(m, fabs(Z.val[p]));
-  const double thr = tol * m;
-  int64_t o = rowptr[i];
-  for (int p = Z.rowptr[i]; p < Z.rowptr[i + 1]; ++p)
-    if (fabs(Z.val[p]) >= thr) {
-      col[o] = Z.col[p];
-      val[o] = sign * Z.val[p];
-      ++o;
+  for (int p = s + lane; p < e; p += G) m = fmax(m, fabs(Z.val[p]));
+  const double thr = tol * group_max<G>(m);
+  int n = 0;
+  const int o = FILL ? rowptr[i] : 0;
+  for (int p0 = s; p0 < e; p0 += G) {
+    const int p = p0 + lane;
+    const double v = p < e ? Z.val[p] : 0.0;
+    const bool keep = p < e && fabs(v) >= thr;
+    const unsigned long long b = group_ballot<G>(keep);
+    if (FILL && keep) {
+      const int at = o + n + bits_below(b, lane);
+      col[at] = Z.col[p];
+      val[at] = sign * v;
     }
+    n += (int)__popcll(b);
+  }
+  if (!FILL && lane == 0) count[i] = n;
 }
 
 void restrictor_drop(const CSR& Zin, double tol, bool negate, CSR& Z, hipStream_t s) {
   const int64_t n = Zin.rows;
-  DBuf<int64_t> cnt(n, s), off;
-  unsigned nb = blocks_for(n, kBlock);
+  const double avg = n > 0 ? (double)Zin.nnz / (double)n : 0.0, sign = negate ? -1.0 : 1.0;
+  DBuf<int32_t> cnt(n, s);
   if (n > 0) {
-    rdrop_count_kernel<<<nb, kBlock, 0, s>>>(view(Zin), tol, cnt.get());
+#define AIRG_CALL(G, CAP)                                                                          \
+  rdrop_kernel<G, false><<<blocks_for(n, 256 / G), 256, 0, s>>>(view(Zin), tol, sign, cnt.get(),   \
+                                                                nullptr, nullptr, nullptr)
+    AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
     AIRG_CHECK_LAUNCH();
   }
-  scan_counts(cnt, n, off, s);
   Z.rows = n;
   Z.cols = Zin.cols;
-  Z.nnz = offsets_to_rowptr(off, n, Z.rowptr, s);
+  Z.nnz = counts_to_rowptr(cnt, n, Z.rowptr, s);
   Z.col.alloc(Z.nnz, s);
   Z.val.alloc(Z.nnz, s);
   if (n > 0) {
-    rdrop_fill_kernel<<<nb, kBlock, 0, s>>>(view(Zin), tol, negate ? -1.0 : 1.0, Z.rowptr.get(),
-                                            Z.col.get(), Z.val.get());
+#define AIRG_CALL(G, CAP)                                                                         \
+  rdrop_kernel<G, true><<<blocks_for(n, 256 / G), 256, 0, s>>>(view(Zin), tol, sign, nullptr,     \
+                                                               Z.rowptr.get(), Z.col.get(), Z.val.get())
+    AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
     AIRG_CHECK_LAUNCH();
   }
 }
 
 // Off-diagonal relative drop; dropped values lumped to the diagonal as
 // d + l_1 + l_2 + ... in ascending column order.
-__global__ void adrop_count_kernel(CSRView A, double tol, int lump, int64_t* count, int32_t* bad) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.rows) return;
-  double m = 0.0;
-  bool has_diag = false;
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) {
-    if (A.col[p] != i) m = fmax(m, fabs(A.val[p]));
-    else has_diag = true;
-  }
-  const double thr = tol * m;
-  int64_t c = 0;
-  bool dropped = false;
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) {
-    bool drop = A.col[p] != i && fabs(A.val[p]) < thr;
-    c += !drop;
-    dropped |= drop;
-  }
-  if (!has_diag || (lump && dropped && !has_diag)) atomicOr(bad, 1);
-  count[i] = c;
-}
-__global__ void adrop_fill_kernel(CSRView A, double tol, int lump, const int32_t* rowptr,
-                                  int32_t* col, double* val, int32_t* bad) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+template <int G, bool FILL>
+__global__ __launch_bounds__(256) void adrop_kernel(CSRView A, double tol, int lump,
+                                                    int32_t* __restrict__ count,
+                                                    const int32_t* __restrict__ rowptr,
+                                                    int32_t* __restrict__ col, double* __restrict__ val,
+                                                    int32_t* bad) {
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= A.rows) return;
   const int s = A.rowptr[i], e = A.rowptr[i + 1];
   double m = 0.0;
-  double d = 0.0;
-  for (int p = s; p < e; ++p) {
+  for (int p = s + lane; p < e; p += G)
     if (A.col[p] != i) m = fmax(m, fabs(A.val[p]));
-    else d = A.val[p];
+  const double thr = tol * group_max<G>(m);
+  // the diagonal first: the dropped values are added to it in column order
+  double d = 0.0;
+  int dlane = -1;
+  for (int p0 = s; p0 < e; p0 += G) {
+    const int p = p0 + lane;
+    const bool diag = p < e && A.col[p] == i;
+    const unsigned long long b = group_ballot<G>(diag);
+    if (b) {
+      dlane = (int)__ffsll(b) - 1;
+      d = __shfl(diag ? A.val[p] : 0.0, dlane, G);
+      break;
+    }
   }
-  const double thr = tol * m;
-  if (lump)
-    for (int p = s; p < e; ++p)
-      if (A.col[p] != i && fabs(A.val[p]) < thr) d = d + A.val[p];
-  int64_t o = rowptr[i];
-  for (int p = s; p < e; ++p) {
-    const int j = A.col[p];
-    if (j != i && fabs(A.val[p]) < thr) continue;
-    col[o] = j;
-    val[o] = (j == i) ? d : A.val[p];
-    ++o;
+  int n = 0;
+  const int o = FILL ? rowptr[i] : 0;
+  int dat = -1;
+  for (int p0 = s; p0 < e; p0 += G) {
+    const int p = p0 + lane;
+    const int j = p < e ? A.col[p] : -1;
+    const double v = p < e ? A.val[p] : 0.0;
+    const bool drop = p < e && j != i && fabs(v) < thr;
+    const bool keep = p < e && !drop;
+    const unsigned long long b = group_ballot<G>(keep);
+    if (FILL) {
+      if (lump) {
+        unsigned long long db = group_ballot<G>(drop);
+        while (db) {
+          const int l = (int)__ffsll(db) - 1;
+          db &= db - 1;
+          d = d + __shfl(v, l, G);
+        }
+      }
+      const int at = o + n + bits_below(b, lane);
+      if (keep) {
+        col[at] = j;
+        if (j == i) dat = at;
+        else val[at] = v;
+      }
+    }
+    n += (int)__popcll(b);
   }
-  if (d == 0.0 || !isfinite(d)) atomicOr(bad, 1);
+  if constexpr (FILL) {
+    if (dat >= 0) val[dat] = d;
+    if (lane == 0 && (d == 0.0 || !isfinite(d))) atomicOr(bad, 1);
+  } else if (lane == 0) {
+    if (dlane < 0) atomicOr(bad, 1);
+    count[i] = n;
+  }
 }
 
 void drop_lump(const CSR& Ain, double tol, bool lump, CSR& Aout, int32_t* bad_diag,
                hipStream_t s) {
   const int64_t n = Ain.rows;
-  DBuf<int64_t> cnt(n, s), off;
-  unsigned nb = blocks_for(n, kBlock);
+  const double avg = n > 0 ? (double)Ain.nnz / (double)n : 0.0;
+  DBuf<int32_t> cnt(n, s);
   if (n > 0) {
-    adrop_count_kernel<<<nb, kBlock, 0, s>>>(view(Ain), tol, lump ? 1 : 0, cnt.get(), bad_diag);
+#define AIRG_CALL(G, CAP)                                                                       \
+  adrop_kernel<G, false><<<blocks_for(n, 256 / G), 256, 0, s>>>(view(Ain), tol, lump ? 1 : 0,   \
+                                                                cnt.get(), nullptr, nullptr, nullptr, bad_diag)
+    AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
     AIRG_CHECK_LAUNCH();
   }
-  scan_counts(cnt, n, off, s);
   Aout.rows = n;
   Aout.cols = Ain.cols;
-  Aout.nnz = offsets_to_rowptr(off, n, Aout.rowptr, s);
+  Aout.nnz = counts_to_rowptr(cnt, n, Aout.rowptr, s);
   Aout.col.alloc(Aout.nnz, s);
   Aout.val.alloc(Aout.nnz, s);
   if (n > 0) {
-    adrop_fill_kernel<<<nb, kBlock, 0, s>>>(view(Ain), tol, lump ? 1 : 0, Aout.rowptr.get(),
-                                            Aout.col.get(), Aout.val.get(), bad_diag);
+#define AIRG_CALL(G, CAP)                                                                      \
+  adrop_kernel<G, true><<<blocks_for(n, 256 / G), 256, 0, s>>>(view(Ain), tol, lump ? 1 : 0, nullptr, \
+                                                               Aout.rowptr.get(), Aout.col.get(),     \
+                                                               Aout.val.get(), bad_diag)
+    AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
     AIRG_CHECK_LAUNCH();
   }
 }
 
-// ------------------------------------------------------------------ R and P
+// ------------------------------------------------------------------ R and P's map
 // R row c: Z row c with F columns mapped to level indices (fpos, ascending),
 // plus 1.0 at level index cpos[c], merged in column order.
 __global__ void build_r_kernel(CSRView Z, const int64_t* fpos, const int64_t* cpos,
@@ -579,24 +1129,23 @@ __global__ void build_r_kernel(CSRView Z, const int64_t* fpos, const int64_t* cp
     val[o] = 1.0;
   }
 }
-__global__ void rowlen_plus_one_kernel(CSRView Z, int64_t* cnt) {
+__global__ void rowlen_plus_one_kernel(CSRView Z, int32_t* cnt) {
   int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < Z.rows) cnt[c] = (int64_t)(Z.rowptr[c + 1] - Z.rowptr[c]) + 1;
+  if (c < Z.rows) cnt[c] = Z.rowptr[c + 1] - Z.rowptr[c] + 1;
 }
 
 void build_r(const CSR& Z, const int64_t* fpos, const int64_t* cpos, int64_t n, CSR& R,
              hipStream_t s) {
   const int64_t nc = Z.rows;
-  DBuf<int64_t> cnt(nc, s), off;
+  DBuf<int32_t> cnt(nc, s);
   unsigned nb = blocks_for(nc, kBlock);
   if (nc > 0) {
     rowlen_plus_one_kernel<<<nb, kBlock, 0, s>>>(view(Z), cnt.get());
     AIRG_CHECK_LAUNCH();
   }
-  scan_counts(cnt, nc, off, s);
-  R.rows = nc;
+    R.rows = nc;
   R.cols = n;
-  R.nnz = offsets_to_rowptr(off, nc, R.rowptr, s);
+  R.nnz = counts_to_rowptr(cnt, nc, R.rowptr, s);
   R.col.alloc(R.nnz, s);
   R.val.alloc(R.nnz, s);
   if (nc > 0) {
@@ -606,121 +1155,137 @@ void build_r(const CSR& Z, const int64_t* fpos, const int64_t* cpos, int64_t n, 
   }
 }
 
-__global__ void p_count_kernel(const int8_t* state, const int64_t* fidx, const int32_t* cmap,
-                               int64_t n, int64_t* cnt) {
+__global__ void one_point_map_kernel(const int8_t* state, const int64_t* fidx, const int64_t* cidx,
+                                     const int32_t* cmap, int64_t n, int32_t* pmap) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  cnt[i] = (state[i] == 2) ? 1 : (cmap[fidx[i]] >= 0 ? 1 : 0);
+  if (i < n) pmap[i] = state[i] == 2 ? (int32_t)cidx[i] : cmap[fidx[i]];
 }
-__global__ void p_fill_kernel(const int8_t* state, const int64_t* fidx, const int64_t* cidx,
-                              const int32_t* cmap, int64_t n, const int32_t* rowptr, int32_t* col,
-                              double* val) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int64_t o = rowptr[i];
-  if (state[i] == 2) {
-    col[o] = (int32_t)cidx[i];
-    val[o] = 1.0;
-  } else {
-    int32_t c = cmap[fidx[i]];
-    if (c >= 0) {
-      col[o] = c;
-      val[o] = 1.0;
-    }
-  }
-}
-
-void build_p(const int8_t* state, const int64_t* fidx, const int64_t* cidx, const int32_t* cmap,
-             int64_t n, int64_t nc, CSR& P, hipStream_t s) {
-  DBuf<int64_t> cnt(n, s), off;
-  unsigned nb = blocks_for(n, kBlock);
-  if (n > 0) {
-    p_count_kernel<<<nb, kBlock, 0, s>>>(state, fidx, cmap, n, cnt.get());
-    AIRG_CHECK_LAUNCH();
-  }
-  scan_counts(cnt, n, off, s);
-  P.rows = n;
-  P.cols = nc;
-  P.nnz = offsets_to_rowptr(off, n, P.rowptr, s);
-  P.col.alloc(P.nnz, s);
-  P.val.alloc(P.nnz, s);
-  if (n > 0) {
-    p_fill_kernel<<<nb, kBlock, 0, s>>>(state, fidx, cidx, cmap, n, P.rowptr.get(), P.col.get(),
-                                        P.val.get());
-    AIRG_CHECK_LAUNCH();
-  }
+void one_point_map(const int8_t* state, const int64_t* fidx, const int64_t* cidx, const int32_t* cmap,
+                   int64_t n, int32_t* pmap, hipStream_t s) {
+  if (n <= 0) return;
+  one_point_map_kernel<<<blocks_for(n, kBlock), kBlock, 0, s>>>(state, fidx, cidx, cmap, n, pmap);
+  AIRG_CHECK_LAUNCH();
 }
 
 // ------------------------------------------------------------------ permutation / transpose
-__global__ void perm_count_kernel(CSRView A, const int32_t* newrow, int64_t* cnt) {
+__global__ void perm_count_kernel(CSRView A, const int32_t* newrow, int32_t* cnt) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < A.rows) cnt[newrow ? newrow[i] : i] = A.rowptr[i + 1] - A.rowptr[i];
 }
-__global__ void perm_fill_kernel(CSRView A, const int32_t* newrow, const int32_t* colmap,
-                                 const int32_t* rowptr, int32_t* col, double* val) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+
+// Row i of A to row newrow[i] (i itself when null) of out with its columns
+// mapped by colmap (kept when null) and, with SORT, sorted: a group of G lanes
+// loads the row at consecutive addresses, ranks its entries against the row's
+// columns in LDS and writes each to its place.  Bound by one read and one
+// write of the matrix for short rows, by len^2 / G LDS compares for long ones.
+// One thread per row copying, and another sorting by insertion in global
+// memory, were a chain of dependent cache accesses per row: the permutations
+// and sorts of a setup at FV 2048^2 took 6.8 + 37.9 ms that way.  Rows longer
+// than CAP are ranked from memory.  out may be A itself (same row pointers,
+// no column map): a row is read before it is written, and one past CAP is
+// sorted by one thread.
+template <int G, int CAP, bool SORT>
+__global__ __launch_bounds__(256) void perm_fill_kernel(CSRView A, const int32_t* newrow,
+                                                        const int32_t* colmap, const int32_t* rowptr,
+                                                        int32_t* col, double* val) {
+  constexpr int T = SORT ? CAP / G : 1;
+  __shared__ int4 sc4[256 / G][SORT ? CAP / 4 : 1];
+  const int lane = threadIdx.x & (G - 1), g = threadIdx.x / G;
+  const int64_t i = (int64_t)blockIdx.x * (256 / G) + g;
   if (i >= A.rows) return;
-  int64_t o = rowptr[newrow ? newrow[i] : i];
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p, ++o) {
-    int j = A.col[p];
-    col[o] = colmap ? colmap[j] : j;
-    val[o] = A.val[p];
+  const int s = A.rowptr[i], len = A.rowptr[i + 1] - s;
+  const int o = rowptr[newrow ? newrow[i] : i];
+  if constexpr (!SORT) {
+    for (int k = lane; k < len; k += G) {
+      const int j = A.col[s + k];
+      col[o + k] = colmap ? colmap[j] : j;
+      val[o + k] = A.val[s + k];
+    }
+    return;
   }
+  if (len > CAP) {
+    if (A.col == col) {  // in place
+      if (lane == 0) insertion_sort(o, o + len, col, val);
+      return;
+    }
+    for (int k = lane; k < len; k += G) {
+      const int c = colmap ? colmap[A.col[s + k]] : A.col[s + k];
+      int r = 0;
+      for (int j = 0; j < len; ++j) {
+        const int cj = colmap ? colmap[A.col[s + j]] : A.col[s + j];
+        r += cj < c || (cj == c && j < k);
+      }
+      col[o + r] = c;
+      val[o + r] = A.val[s + k];
+    }
+    return;
+  }
+  int32_t* sc = reinterpret_cast<int32_t*>(sc4[g]);
+  int c[T], r[T];
+  double v[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int k = lane + G * t;
+    c[t] = 0x7fffffff;
+    v[t] = 0.0;
+    if (k < len) {
+      const int j = A.col[s + k];
+      c[t] = colmap ? colmap[j] : j;
+      v[t] = A.val[s + k];
+    }
+    if (G * t < len + 3) sc[k] = c[t];
+  }
+  wave_order();
+  rank_entries<G, T>(sc, len, c, lane, r);
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+    if (lane + G * t < len) {
+      col[o + r[t]] = c[t];
+      val[o + r[t]] = v[t];
+    }
+}
+template <bool SORT>
+static void launch_perm_fill(const CSR& A, const int32_t* newrow, const int32_t* colmap,
+                             const int32_t* rowptr, int32_t* col, double* val, hipStream_t s) {
+  if (A.rows <= 0 || A.nnz <= 0) return;
+  const double avg = (double)A.nnz / (double)A.rows;
+#define AIRG_CALL(G, CAP)                                                                        \
+  perm_fill_kernel<G, CAP, SORT><<<blocks_for(A.rows, 256 / G), 256, 0, s>>>(view(A), newrow,    \
+                                                                             colmap, rowptr, col, val)
+  AIRG_ROW_GROUPS(avg, AIRG_CALL);
+#undef AIRG_CALL
+  AIRG_CHECK_LAUNCH();
 }
 
 void permute_rows(const CSR& A, const int32_t* newrow, const int32_t* colmap, int64_t out_cols,
-                  CSR& out, hipStream_t s) {
+                  CSR& out, hipStream_t s, bool sorted) {
   const int64_t n = A.rows;
-  DBuf<int64_t> cnt(n, s), off;
-  unsigned nb = blocks_for(n, kBlock);
+  DBuf<int32_t> cnt(n, s);
+  DBuf<int64_t> work(rowptr_work_size(n), s), total(1, s);
   if (n > 0) {
-    perm_count_kernel<<<nb, kBlock, 0, s>>>(view(A), newrow, cnt.get());
+    perm_count_kernel<<<blocks_for(n, kBlock), kBlock, 0, s>>>(view(A), newrow, cnt.get());
     AIRG_CHECK_LAUNCH();
   }
-  scan_counts(cnt, n, off, s);
-  out.rows = n;
-  out.cols = out_cols;
-  out.nnz = offsets_to_rowptr(off, n, out.rowptr, s);
-  out.col.alloc(out.nnz, s);
-  out.val.alloc(out.nnz, s);
-  if (n > 0) {
-    perm_fill_kernel<<<nb, kBlock, 0, s>>>(view(A), newrow, colmap, out.rowptr.get(),
-                                           out.col.get(), out.val.get());
-    AIRG_CHECK_LAUNCH();
-  }
+  out.alloc(n, out_cols, A.nnz, s);
+  launch_rowptr_scan(cnt.get(), n, out.rowptr.get(), total.get(), work.get(), s);
+  if (sorted) launch_perm_fill<true>(A, newrow, colmap, out.rowptr.get(), out.col.get(), out.val.get(), s);
+  else launch_perm_fill<false>(A, newrow, colmap, out.rowptr.get(), out.col.get(), out.val.get(), s);
 }
 
-__global__ void tcount_kernel(CSRView A, unsigned long long* cnt) {
+__global__ void tcount_kernel(CSRView A, int32_t* cnt) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= A.rows) return;
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) atomicAdd(&cnt[A.col[p]], 1ull);
+  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) atomicAdd(&cnt[A.col[p]], 1);
 }
-__global__ void tfill_kernel(CSRView A, const int32_t* rowptr, unsigned long long* cursor,
-                             int32_t* col, double* val) {
+__global__ void tfill_kernel(CSRView A, const int32_t* rowptr, int32_t* cursor, int32_t* col,
+                             double* val) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= A.rows) return;
   for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p) {
     int j = A.col[p];
-    unsigned long long k = atomicAdd(&cursor[j], 1ull);
-    col[rowptr[j] + (int64_t)k] = (int32_t)i;
-    val[rowptr[j] + (int64_t)k] = A.val[p];
-  }
-}
-__global__ void row_sort_kernel(int64_t rows, const int32_t* rowptr, int32_t* col, double* val) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows) return;
-  const int s = rowptr[i], e = rowptr[i + 1];
-  for (int p = s + 1; p < e; ++p) {
-    int c = col[p];
-    double v = val[p];
-    int q = p - 1;
-    while (q >= s && col[q] > c) {
-      col[q + 1] = col[q];
-      val[q + 1] = val[q];
-      --q;
-    }
-    col[q + 1] = c;
-    val[q + 1] = v;
+    const int k = rowptr[j] + atomicAdd(&cursor[j], 1);
+    col[k] = (int32_t)i;
+    val[k] = A.val[p];
   }
 }
 
@@ -743,39 +1308,27 @@ void spatial_row_order(CSR& A, const int32_t* rkey, hipStream_t s) {
 }
 
 void sort_rows(CSR& A, hipStream_t s) {
-  if (A.rows <= 0 || A.nnz <= 0) return;
-  row_sort_kernel<<<blocks_for(A.rows, kBlock), kBlock, 0, s>>>(A.rows, A.rowptr.get(), A.col.get(),
-                                                                A.val.get());
-  AIRG_CHECK_LAUNCH();
+  launch_perm_fill<true>(A, nullptr, nullptr, A.rowptr.get(), A.col.get(), A.val.get(), s);
 }
 
 void transpose(const CSR& A, CSR& At, hipStream_t s) {
   const int64_t m = A.cols;
-  DBuf<int64_t> cnt(m, s), off;
-  launch_zero_bytes(cnt.get(), m * sizeof(int64_t), s);
+  DBuf<int32_t> cnt(m, s);
+  launch_zero_bytes(cnt.get(), m * sizeof(int32_t), s);
   unsigned nb = blocks_for(A.rows, kBlock);
   if (A.rows > 0) {
-    tcount_kernel<<<nb, kBlock, 0, s>>>(view(A), (unsigned long long*)cnt.get());
+    tcount_kernel<<<nb, kBlock, 0, s>>>(view(A), cnt.get());
     AIRG_CHECK_LAUNCH();
   }
-  scan_counts(cnt, m, off, s);
-  At.rows = m;
-  At.cols = A.rows;
-  At.nnz = offsets_to_rowptr(off, m, At.rowptr, s);
-  At.col.alloc(At.nnz, s);
-  At.val.alloc(At.nnz, s);
-  DBuf<int64_t> cursor(m, s);
-  launch_zero_bytes(cursor.get(), m * sizeof(int64_t), s);
+  DBuf<int64_t> work(rowptr_work_size(m), s), total(1, s);
+  At.alloc(m, A.rows, A.nnz, s);
+  launch_rowptr_scan(cnt.get(), m, At.rowptr.get(), total.get(), work.get(), s);
+  launch_zero_bytes(cnt.get(), m * sizeof(int32_t), s);
   if (A.rows > 0) {
-    tfill_kernel<<<nb, kBlock, 0, s>>>(view(A), At.rowptr.get(), (unsigned long long*)cursor.get(),
-                                       At.col.get(), At.val.get());
+    tfill_kernel<<<nb, kBlock, 0, s>>>(view(A), At.rowptr.get(), cnt.get(), At.col.get(), At.val.get());
     AIRG_CHECK_LAUNCH();
   }
-  if (m > 0) {
-    row_sort_kernel<<<blocks_for(m, kBlock), kBlock, 0, s>>>(m, At.rowptr.get(), At.col.get(),
-                                                              At.val.get());
-    AIRG_CHECK_LAUNCH();
-  }
+  sort_rows(At, s);
 }
 
 void copy_csr(const CSR& A, CSR& out, hipStream_t s) {
@@ -795,100 +1348,24 @@ void copy_csr(const CSR& A, CSR& out, hipStream_t s) {
 namespace airg {
 
 // ------------------------------------------------------------------ merged F-point residual operator
-// B = A_fc + A_ff W with W the one-point prolongation (column j of A_ff moves
-// to column cmap[j] of e_c; columns with cmap[j] < 0 drop out).  Each row's
-// entries are collected (A_fc first, then A_ff in stored order), sorted by
-// column with a stable insertion sort and equal columns summed left to right.
-__global__ void fcw_count_kernel(CSRView Afc, CSRView Aff, const int32_t* cmap, int64_t* cnt) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Afc.rows) return;
-  int64_t c = Afc.rowptr[i + 1] - Afc.rowptr[i];
-  for (int p = Aff.rowptr[i]; p < Aff.rowptr[i + 1]; ++p) c += cmap[Aff.col[p]] >= 0 ? 1 : 0;
-  cnt[i] = c;
-}
-__global__ void fcw_fill_kernel(CSRView Afc, CSRView Aff, const int32_t* cmap, const int32_t* off,
-                                int32_t* col, double* val, int64_t* distinct) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Afc.rows) return;
-  const int s = off[i];
-  int e = s;
-  for (int p = Afc.rowptr[i]; p < Afc.rowptr[i + 1]; ++p, ++e) {
-    col[e] = Afc.col[p];
-    val[e] = Afc.val[p];
-  }
-  for (int p = Aff.rowptr[i]; p < Aff.rowptr[i + 1]; ++p) {
-    const int m = cmap[Aff.col[p]];
-    if (m < 0) continue;
-    col[e] = m;
-    val[e] = Aff.val[p];
-    ++e;
-  }
-  for (int p = s + 1; p < e; ++p) {  // stable: strictly greater moves right
-    const int c = col[p];
-    const double v = val[p];
-    int q = p - 1;
-    while (q >= s && col[q] > c) {
-      col[q + 1] = col[q];
-      val[q + 1] = val[q];
-      --q;
-    }
-    col[q + 1] = c;
-    val[q + 1] = v;
-  }
-  int w = s;
-  for (int p = s; p < e; ++p) {
-    if (p > s && col[p] == col[w - 1]) {
-      val[w - 1] = val[w - 1] + val[p];
-    } else {
-      col[w] = col[p];
-      val[w] = val[p];
-      ++w;
-    }
-  }
-  distinct[i] = w - s;
-}
-__global__ void fcw_compact_kernel(int64_t rows, const int32_t* off, const int32_t* rowptr,
-                                   const int32_t* tcol, const double* tval, int32_t* col,
-                                   double* val) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows) return;
-  const int s = off[i];
-  for (int p = rowptr[i], q = s; p < rowptr[i + 1]; ++p, ++q) {
-    col[p] = tcol[q];
-    val[p] = tval[q];
-  }
-}
-
+// B = A_fc + A_ff W with W the one-point prolongation (merge_rows_kernel).
 void merge_fc_ffw(const CSR& Afc, const CSR& Aff, const int32_t* cmap, CSR& B, hipStream_t s) {
-  const int64_t n = Afc.rows;
+  const int64_t n = Afc.rows, tot = Afc.nnz + Aff.nnz;
+  if (tot > 2147483647ll) fail(AIRG_ERR_NOMEM, "sparse matrix exceeds 2^31 nonzeros");
   B.rows = n;
   B.cols = Afc.cols;
-  if (n <= 0) {
-    B.nnz = 0;
-    B.rowptr.alloc(1, s);
-    launch_fill_i32(B.rowptr.get(), 1, 0, s);
-    return;
-  }
-  const unsigned nb = blocks_for(n, kBlock);
-  DBuf<int64_t> cnt(n, s), off;
-  fcw_count_kernel<<<nb, kBlock, 0, s>>>(view(Afc), view(Aff), cmap, cnt.get());
-  AIRG_CHECK_LAUNCH();
-  scan_counts(cnt, n, off, s);
-  DBuf<int32_t> toff;
-  const int64_t tot = offsets_to_rowptr(off, n, toff, s);
-  DBuf<int32_t> tcol(std::max<int64_t>(tot, 1), s);
-  DBuf<double> tval(std::max<int64_t>(tot, 1), s);
-  fcw_fill_kernel<<<nb, kBlock, 0, s>>>(view(Afc), view(Aff), cmap, toff.get(), tcol.get(),
-                                        tval.get(), cnt.get());
-  AIRG_CHECK_LAUNCH();
-  DBuf<int64_t> boff;
-  scan_counts(cnt, n, boff, s);
-  B.nnz = offsets_to_rowptr(boff, n, B.rowptr, s);
+  DBuf<int32_t> cnt(n, s), tcol(tot, s);
+  DBuf<double> tval(tot, s);
+  if (n > 0) launch_merge_rows<true>(Afc, Aff, cmap, tcol.get(), tval.get(), cnt.get(), s);
+  B.nnz = counts_to_rowptr(cnt, n, B.rowptr, s);
   B.col.alloc(B.nnz, s);
   B.val.alloc(B.nnz, s);
-  fcw_compact_kernel<<<nb, kBlock, 0, s>>>(n, toff.get(), B.rowptr.get(), tcol.get(), tval.get(),
-                                           B.col.get(), B.val.get());
-  AIRG_CHECK_LAUNCH();
+  if (n > 0) {
+    compact_rows_kernel<16><<<blocks_for(n, 16), 256, 0, s>>>(n, Afc.rowptr.get(), Aff.rowptr.get(),
+                                                              B.rowptr.get(), tcol.get(), tval.get(),
+                                                              B.col.get(), B.val.get());
+    AIRG_CHECK_LAUNCH();
+  }
 }
 
 // ------------------------------------------------------------------ compressed columns
@@ -897,34 +1374,48 @@ void merge_fc_ffw(const CSR& Afc, const CSR& Aff, const int32_t* cmap, CSR& B, h
 // (true for almost every block of a locality-ordered operator, whose rows see
 // nearby columns); a block that spans more keeps its int32 columns, marked by
 // a negative base.  Saves 2 of the 12 bytes of an FP64 entry.
-__global__ void col_span_kernel(CSRView A, int64_t nblk, int32_t* cbase, int32_t* cspan,
-                                unsigned long long* nwide, unsigned long long* maxspan) {
-  int64_t blk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// One wavefront per block: its entries are one run of addresses.  One thread
+// per block walked them one by one, 22.9 ms a setup at FV 2048^2.
+__global__ __launch_bounds__(256) void col_span_kernel(CSRView A, int64_t nblk, int32_t* cbase,
+                                                       int32_t* cspan, int32_t* stat) {
+  const int lane = threadIdx.x & 63;
+  const int64_t blk = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (blk >= nblk) return;
   const int64_t r0 = blk << kColBlockShift;
   const int64_t r1 = min(r0 + ((int64_t)1 << kColBlockShift), A.rows);
   int mn = 0x7fffffff, mx = -1;
-  for (int p = A.rowptr[r0]; p < A.rowptr[r1]; ++p) {
+  for (int p = A.rowptr[r0] + lane; p < A.rowptr[r1]; p += 64) {
     const int c = A.col[p];
     mn = min(mn, c);
     mx = max(mx, c);
   }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    mn = min(mn, __shfl_xor(mn, o, 64));
+    mx = max(mx, __shfl_xor(mx, o, 64));
+  }
+  if (lane != 0) return;
   if (mx < 0) mn = mx = 0;
   if (mx - mn > 65535) {
     cbase[blk] = -1;
     cspan[blk] = 0;
-    atomicAdd(nwide, 1ull);
+    atomicAdd(stat, 1);
   } else {
     cbase[blk] = mn;
     cspan[blk] = mx - mn + 1;
-    atomicMax(maxspan, (unsigned long long)(mx - mn + 1));
+    // most blocks find a wider one counted already and need no atomic
+    if (mx - mn + 1 > __hip_atomic_load(stat + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(stat + 1, mx - mn + 1);
   }
 }
-__global__ void col16_kernel(CSRView A, const int32_t* cbase, uint16_t* col16) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.rows) return;
-  const int b = cbase[i >> kColBlockShift];
-  for (int p = A.rowptr[i]; p < A.rowptr[i + 1]; ++p)
+__global__ __launch_bounds__(256) void col16_kernel(CSRView A, int64_t nblk, const int32_t* cbase,
+                                                    uint16_t* col16) {
+  const int64_t blk = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  if (blk >= nblk) return;
+  const int64_t r0 = blk << kColBlockShift;
+  const int64_t r1 = min(r0 + ((int64_t)1 << kColBlockShift), A.rows);
+  const int b = cbase[blk];
+  for (int p = A.rowptr[r0] + (threadIdx.x & 63); p < A.rowptr[r1]; p += 64)
     col16[p] = b >= 0 ? (uint16_t)(A.col[p] - b) : (uint16_t)0;
 }
 
@@ -935,26 +1426,25 @@ bool compress_columns(CSR& A, hipStream_t s) {
   A.max_span = 0;
   if (A.rows <= 0 || A.nnz <= 0) return false;
   const int64_t nblk = (A.rows + (1 << kColBlockShift) - 1) >> kColBlockShift;
-  DBuf<unsigned long long> stat(2, s);
-  launch_zero_bytes(stat.get(), 2 * sizeof(unsigned long long), s);
+  DBuf<int32_t> stat(2, s);  // blocks that span too much, the widest of the others
+  launch_zero_bytes(stat.get(), 2 * sizeof(int32_t), s);
   A.cbase.alloc(nblk, s);
   A.cspan.alloc(nblk, s);
-  col_span_kernel<<<blocks_for(nblk, kBlock), kBlock, 0, s>>>(view(A), nblk, A.cbase.get(),
-                                                             A.cspan.get(), stat.get(),
-                                                             stat.get() + 1);
+  col_span_kernel<<<blocks_for(nblk, 4), 256, 0, s>>>(view(A), nblk, A.cbase.get(), A.cspan.get(),
+                                                      stat.get());
   AIRG_CHECK_LAUNCH();
-  unsigned long long st[2];
+  int32_t st[2];
   stat.to_host(st, 2);
   AIRG_HIP(hipStreamSynchronize(s));
   // worth it only if nearly every block compresses
-  if (st[0] * 16 > (unsigned long long)nblk) {
+  if ((int64_t)st[0] * 16 > nblk) {
     A.cbase.release();
     A.cspan.release();
     return false;
   }
   A.max_span = (int64_t)st[1];
   A.col16.alloc(A.nnz, s);
-  col16_kernel<<<blocks_for(A.rows, kBlock), kBlock, 0, s>>>(view(A), A.cbase.get(), A.col16.get());
+  col16_kernel<<<blocks_for(nblk, 4), 256, 0, s>>>(view(A), nblk, A.cbase.get(), A.col16.get());
   AIRG_CHECK_LAUNCH();
   return true;
 }

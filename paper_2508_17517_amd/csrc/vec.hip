@@ -40,9 +40,15 @@ __global__ void fill_i32_kernel(int32_t* x, int64_t n, int32_t v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) x[i] = v;
 }
+// 16 bytes a thread where p is 16-byte aligned (every buffer's start is), the
+// rest one byte at a time
 __global__ void zero_bytes_kernel(uint8_t* p, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+  const size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 16;
+  if (i + 16 <= n && ((uintptr_t)p & 15) == 0) {
+    *reinterpret_cast<uint4*>(p + i) = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  for (size_t k = i; k < n && k < i + 16; ++k) p[k] = 0;
 }
 __global__ void copy_kernel(double* y, const double* x, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -90,7 +96,7 @@ void launch_fill_i32(int32_t* x, int64_t n, int32_t v, hipStream_t s) {
 }
 void launch_zero_bytes(void* p, size_t bytes, hipStream_t s) {
   if (!bytes) return;
-  zero_bytes_kernel<<<blocks_for((int64_t)bytes, kBlock), kBlock, 0, s>>>((uint8_t*)p, bytes);
+  zero_bytes_kernel<<<blocks_for((int64_t)bytes, 16 * kBlock), kBlock, 0, s>>>((uint8_t*)p, bytes);
   AIRG_CHECK_LAUNCH();
 }
 void launch_copy(double* y, const double* x, int64_t n, hipStream_t s) {
@@ -1095,20 +1101,74 @@ void launch_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* work, 
   AIRG_CHECK_LAUNCH();
 }
 
-__global__ void offsets_to_i32_kernel(const int64_t* off, int32_t* rp, int64_t n1, int32_t* ovf) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n1) return;
-  int64_t v = off[i];
-  if (v > 2147483647ll) {
-    atomicOr(ovf, 1);
-    v = 0;
+// Row pointers from row lengths: rowptr = exclusive sums of cnt (rowptr[n]
+// their total), the total in 64 bits to *total.  Two launches: the sums of
+// blocks of kRowptrSpan lengths, then every block adds up the sums before it
+// by itself and scans its own lengths (for up to kRowptrSpan rows the second
+// alone).
+constexpr int kRowptrSpan = 4096;
+
+__global__ __launch_bounds__(256) void rowptr_part_kernel(const int32_t* __restrict__ cnt, int64_t n,
+                                                          int64_t* __restrict__ part) {
+  __shared__ int64_t sh[256];
+  const int64_t i0 = (int64_t)blockIdx.x * kRowptrSpan;
+  int64_t v = 0;
+#pragma unroll
+  for (int q = 0; q < kRowptrSpan / 256; ++q) {
+    const int64_t i = i0 + q * 256 + threadIdx.x;
+    v += i < n ? cnt[i] : 0;
   }
-  rp[i] = (int32_t)v;
+  int64_t tot;
+  block_exclusive_scan(v, sh, &tot);
+  if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
-void launch_offsets_to_i32(const int64_t* off, int32_t* rowptr, int64_t n1, int32_t* overflow,
-                           hipStream_t s) {
-  if (n1 <= 0) return;
-  offsets_to_i32_kernel<<<blocks_for(n1, kBlock), kBlock, 0, s>>>(off, rowptr, n1, overflow);
+__global__ __launch_bounds__(256) void rowptr_scan_kernel(const int32_t* __restrict__ cnt, int64_t n,
+                                                          const int64_t* __restrict__ part,
+                                                          int32_t* __restrict__ rowptr,
+                                                          int64_t* __restrict__ total) {
+  constexpr int kPer = kRowptrSpan / 256;
+  __shared__ int64_t sh[256];
+  __shared__ int32_t lens[kRowptrSpan + kRowptrSpan / 16];  // padded: thread t reads 16 in a row
+  const int t = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * kRowptrSpan;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int k = q * 256 + t;
+    lens[k + (k >> 4)] = i0 + k < n ? cnt[i0 + k] : 0;
+  }
+  int64_t before = 0;
+  for (int64_t b = t; b < blockIdx.x; b += 256) before += part[b];
+  int64_t base;
+  block_exclusive_scan(before, sh, &base);
+  int64_t own = 0;
+  for (int q = 0; q < kPer; ++q) own += lens[17 * t + q];
+  int64_t all;
+  int64_t off = base + block_exclusive_scan(own, sh, &all);
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t l = lens[17 * t + q];
+    lens[17 * t + q] = (int32_t)off;
+    off += l;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int k = q * 256 + t;
+    if (i0 + k < n) rowptr[i0 + k] = lens[k + (k >> 4)];
+  }
+  if (blockIdx.x == gridDim.x - 1 && t == 0) {
+    rowptr[n] = (int32_t)(base + all);
+    *total = base + all;
+  }
+}
+size_t rowptr_work_size(int64_t n) { return (size_t)((n + kRowptrSpan - 1) / kRowptrSpan + 1); }
+void launch_rowptr_scan(const int32_t* cnt, int64_t n, int32_t* rowptr, int64_t* total, int64_t* work,
+                        hipStream_t s) {
+  const unsigned nb = blocks_for(n, kRowptrSpan);
+  if (nb > 1) {
+    rowptr_part_kernel<<<nb, 256, 0, s>>>(cnt, n, work);
+    AIRG_CHECK_LAUNCH();
+  }
+  rowptr_scan_kernel<<<nb, 256, 0, s>>>(cnt, n, work, rowptr, total);
   AIRG_CHECK_LAUNCH();
 }
 

@@ -79,7 +79,7 @@ typedef struct {
   int32_t keep_setup_data;   /* keep level data in setup numbering for export, 0 */
   int32_t locality_order;    /* order each level's F points and the coarsest level's
                                 points in the solve numbering by a locality key of two
-                                breadth-first distances on A + A^T (cache locality of the
+                                distances on the graph of A + A^T (cache locality of the
                                 SpMV gathers; the hierarchy itself is unchanged), 1 */
   int32_t outer;             /* airg_outer: the outer iteration, AIRG_OUTER_FGMRES */
   int32_t smoother;          /* airg_smoother: the F-point smoother, AIRG_SMOOTH_POLY */

@@ -441,12 +441,78 @@ void build_hierarchy(Hierarchy& H, CSR&& Ain) {
   H.setup_ms = now_ms() - t0;
 }
 
+// The locality keys of every level with the coarsest level's points as
+// landmarks: the coarsest level's own keys in key.back(), the others'
+// (problem-major in a batch: mult and mult_c as in finalize_hierarchy) from
+// coordinates carried up to the top.  False where the coarsest level cannot
+// serve: less than a thousandth of the points, less than three steps deep, not
+// connected (a flow along the grid lines), or so many problems that less than
+// 9 bits are left a coordinate; the top graph's own distances then give the keys.
+static bool order_from_landmarks(Hierarchy& H, std::vector<DBuf<int32_t>>& key, int64_t& mult,
+                                 int64_t& mult_c) {
+  hipStream_t s = H.s;
+  const int nl = (int)H.levels.size();
+  const Level& Lc = H.levels.back();
+  const int np = H.seg.empty() ? 0 : (int)H.seg.size() - 1, nseg = std::max(np, 1);
+  int bits = 15;
+  while (bits > 0 && ((int64_t)nseg << (2 * bits)) > (int64_t)INT32_MAX) --bits;
+  if (nl < 2 || H.n0 > 1024 * Lc.n || bits < 9) return false;
+  auto inherited = [&](const DBuf<int32_t>& k, const Level& L) {
+    DBuf<int64_t> clist(L.nC, s);
+    DBuf<int32_t> next(L.nC, s);
+    launch_inverse_map(L.state.get(), L.n, 2, L.cidx.get(), clist.get(), s);
+    inherit_keys(k.get(), clist.get(), L.nC, next.get(), s);
+    return next;
+  };
+  // the top index and the problem of each coarsest point
+  DBuf<int32_t> lm(H.n0, s), sid(np > 1 ? H.n0 : Lc.n, s);
+  launch_iota(lm.get(), H.n0, s);
+  launch_fill_i32(sid.get(), (int64_t)sid.size(), 0, s);
+  if (np > 1) problem_major_keys(sid.get(), H.n0, H.seg, 1, s);
+  for (int l = 0; l + 1 < nl; ++l) {
+    lm = inherited(lm, H.levels[l]);
+    if (np > 1) sid = inherited(sid, H.levels[l]);
+  }
+  DBuf<int32_t> kc(Lc.n, s);
+  {
+    DBuf<int32_t> d1(Lc.n, s), d2(Lc.n, s);
+    int32_t d1max = 0, d2max = 0;
+    if (!coarse_distances(Lc.A, sid.get(), nseg, d1.get(), d2.get(), &d1max, &d2max, s) || d1max < 3)
+      return false;
+    row_major_keys(kc.get(), d1.get(), d2.get(), Lc.n, d1max, d2max, s);
+  }
+  if (np > 1) {
+    mult_c = (int64_t)max_key(kc.get(), Lc.n, s) + 1;
+    if ((int64_t)np * mult_c > (int64_t)INT32_MAX) return false;
+    problem_major_keys(kc.get(), sid.get(), Lc.n, mult_c, s);
+  }
+  CSR At;
+  transpose(H.A0, At, s);
+  DBuf<double2> xy;
+  if (!landmark_coords(H.A0, At, lm.get(), sid.get(), Lc.n, nseg, xy, s)) return false;
+  for (int l = nl - 2; l >= 0; --l) {
+    const Level& L = H.levels[l];
+    coords_up(L.state.get(), L.fidx.get(), L.cidx.get(), L.Afc_nat, L.Z_nat, L.n, xy, s);
+  }
+  coords_relax(H.A0, At, xy, s);
+  key[0].alloc(H.n0, s);
+  coord_keys(xy.get(), H.n0, bits, key[0].get(), s);
+  if (np > 1) {
+    mult = (int64_t)1 << (2 * bits);
+    problem_major_keys(key[0].get(), H.n0, H.seg, mult, s);
+  }
+  for (int l = 0; l + 2 < nl; ++l) key[l + 1] = inherited(key[l], H.levels[l]);
+  key[nl - 1] = std::move(kc);
+  return true;
+}
+
 void finalize_hierarchy(Hierarchy& H) {
   hipStream_t s = H.s;
   const int nl = (int)H.levels.size();
   const bool order = H.p.locality_order != 0;
-  // locality keys, top down: the Hilbert index of two breadth-first
-  // distances on A_0 + A_0^T, inherited by the coarse points
+  // locality keys, top down: the Hilbert index of two coordinates, from the
+  // coarsest level's graph where that serves (order_from_landmarks), else two
+  // breadth-first distances on A_0 + A_0^T, inherited by the coarse points
   std::vector<DBuf<int32_t>> key(nl);
   // a batch orders every level problem-major (key = problem * mult + key), so
   // that each problem's unknowns form ranges of the nested numbering; mult
@@ -455,7 +521,12 @@ void finalize_hierarchy(Hierarchy& H) {
   const int np = H.seg.empty() ? 0 : (int)H.seg.size() - 1;
   int64_t mult = 0, mult_c = 0;
   H.granges.clear();
+  bool from_landmarks = false;
   if (order) {
+    from_landmarks = order_from_landmarks(H, key, mult, mult_c);
+    if (!from_landmarks) mult = mult_c = 0;
+  }
+  if (order && !from_landmarks) {
     key[0].alloc(H.n0, s);
     if (np > 1) {
       // every component of every problem at once
@@ -485,7 +556,9 @@ void finalize_hierarchy(Hierarchy& H) {
   Level& Lc = H.levels.back();
   Lc.pos.alloc(Lc.n, s);
   if (order) {
-    if (nl > 1) {
+    if (from_landmarks) {
+      // its keys are there
+    } else if (nl > 1) {
       DBuf<int32_t> pid;
       if (mult) {
         pid.alloc(Lc.n, s);

@@ -341,6 +341,26 @@ void locality_keys_seg(const CSR& A, const int32_t* sid, int nseg, int32_t* key,
 // The keys of every connected component at once, each component's from 0
 // (not component-major; a connected graph gets locality_keys).
 void locality_keys_by_component(const CSR& A, int32_t* key, hipStream_t s, bool hilbert);
+// Two breadth-first distances on the graph of A + A^T in every segment at once
+// (start nodes as for the keys above), for a graph a few dozen steps deep;
+// false where it is deeper than 4096 steps or a segment is not connected.
+bool coarse_distances(const CSR& A, const int32_t* sid, int nseg, int32_t* d1, int32_t* d2, int32_t* d1max,
+                      int32_t* d2max, hipStream_t s);
+// key = d1 (d2max + 1) + d2 (d1 where that does not fit or d1max < 2)
+void row_major_keys(int32_t* key, const int32_t* d1, const int32_t* d2, int64_t n, int32_t d1max,
+                    int32_t d2max, hipStream_t s);
+// Coordinates of k landmarks (lm: their points on the graph of A + A^T, sid:
+// their segments) from two distances over the landmarks; false where a
+// landmark has more than 32 neighbours or a segment's are not connected.
+bool landmark_coords(const CSR& A, const CSR& At, const int32_t* lm, const int32_t* sid, int64_t k, int nseg,
+                     DBuf<double2>& xy, hipStream_t s);
+// A level's coordinates from the next coarser level's (C points keep theirs, F
+// points take the middle of their neighbours' up and downstream); eight sweeps
+// of averages over a graph; Hilbert keys of coordinates on a 2^bits square.
+void coords_up(const int8_t* state, const int64_t* fidx, const int64_t* cidx, const CSR& Afc, const CSR& Z,
+               int64_t n, DBuf<double2>& xy, hipStream_t s);
+void coords_relax(const CSR& A, const CSR& At, DBuf<double2>& xy, hipStream_t s);
+void coord_keys(const double2* xy, int64_t n, int bits, int32_t* key, hipStream_t s);
 // Problem-major keys of a block-diagonal batch (key = p * mult + key), by the
 // row segments seg (problem p: rows seg[p] .. seg[p+1]-1) or by a problem per
 // point; the problem of each key (key / mult); the number of points of each

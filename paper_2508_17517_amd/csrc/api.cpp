@@ -3,6 +3,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
+#include <iterator>
 #include <map>
 #include <memory>
 #include <new>
@@ -31,6 +32,69 @@ void check_device_budget(size_t bytes) {
                              std::to_string(budget) + " bytes");
 }
 void set_device_budget(int64_t bytes) { g_device_budget = bytes > 0 ? bytes : 0; }
+
+thread_local SetupPool* SetupPool::cur_ = nullptr;
+
+SetupPool::SetupPool(hipStream_t s) : outer_(cur_), s_(s) {
+  if (hipHostMalloc(&page_, kPage, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    page_ = nullptr;
+  }
+  cur_ = this;
+}
+SetupPool::~SetupPool() {
+  cur_ = outer_;
+  drop();
+  if (page_) (void)hipHostFree(page_);
+}
+// eighths of a power of two: a request finds a block at most an eighth larger,
+// and repeated sizes that differ a little share blocks
+size_t SetupPool::rounded(size_t bytes) {
+  size_t p = 512;
+  while (p < bytes) p <<= 1;
+  const size_t step = p / 16;
+  return (bytes + step - 1) / step * step;
+}
+void* SetupPool::take(size_t bytes, size_t& cap) {
+  cap = rounded(bytes);
+  const auto it = free_.lower_bound(cap);
+  if (it == free_.end() || it->first > cap + cap / 8) return nullptr;
+  void* p = it->second;
+  cap = it->first;
+  kept_ -= cap;
+  free_.erase(it);
+  return p;
+}
+bool SetupPool::give(void* p, size_t cap) {
+  if (cap > kKeep) return false;
+  // the largest blocks make room
+  while (kept_ + cap > kKeep) {
+    const auto it = std::prev(free_.end());
+    kept_ -= it->first;
+    (void)hipFreeAsync(it->second, s_);
+    free_.erase(it);
+  }
+  try {
+    free_.emplace(cap, p);
+  } catch (...) {
+    return false;
+  }
+  kept_ += cap;
+  return true;
+}
+void SetupPool::drop() {
+  for (const auto& b : free_) (void)hipFreeAsync(b.second, s_);
+  free_.clear();
+  kept_ = 0;
+}
+
+void read_back(void* dst, const void* dev, size_t bytes, hipStream_t s) {
+  const SetupPool* pool = SetupPool::of(s);
+  void* to = pool && pool->page() && bytes <= SetupPool::kPage ? pool->page() : dst;
+  AIRG_HIP(hipMemcpyAsync(to, dev, bytes, hipMemcpyDeviceToHost, s));
+  AIRG_HIP(hipStreamSynchronize(s));
+  if (to != dst) std::memcpy(dst, to, bytes);
+}
 
 }  // namespace airg
 
@@ -241,9 +305,11 @@ int airg_setup(airg_handle* out, int64_t n, int64_t nnz, const int32_t* rowptr,
     std::unique_ptr<airg_ctx> c(new airg_ctx());
     c->H.p = prm;
     c->H.s = (hipStream_t)hip_stream;
+    SetupPool pool(c->H.s);
     CSR A;
     load_csr(A, n, nnz, rowptr, colidx, vals, on_device, c->H.s);
     build_hierarchy(c->H, std::move(A));
+    pool.drop();  // the workspace is of other sizes
     workspace_init(c->H, c->W);
     AIRG_HIP(hipStreamSynchronize(c->H.s));
     *out = c.release();
@@ -275,6 +341,7 @@ int airg_setup_batch(airg_handle* out, int nprob, const int64_t* n, const int64_
     c->H.p = prm;
     hipStream_t s = (hipStream_t)hip_stream;
     c->H.s = s;
+    SetupPool pool(s);
     int64_t N = 0, NZ = 0;
     std::vector<int64_t> seg(1, 0);
     for (int q = 0; q < nprob; ++q) {
@@ -302,6 +369,7 @@ int airg_setup_batch(airg_handle* out, int nprob, const int64_t* n, const int64_
     validate_csr(A, diag, s, true);
     c->H.seg = seg;
     build_hierarchy(c->H, std::move(A));
+    pool.drop();
     workspace_init(c->H, c->W);
     AIRG_HIP(hipStreamSynchronize(s));
     *out = c.release();
@@ -342,12 +410,14 @@ int airg_adjoint_solve(airg_handle h, int nrhs, const double* w, int64_t ldw, do
     airg_ctx* c = handle_of(h);
     if (!c->H.seg.empty()) fail(AIRG_ERR_INVALID, "adjoint solves take a single-problem handle");
     if (!c->Ht) {
+      SetupPool pool(c->H.s);
       std::unique_ptr<Hierarchy> Ht(new Hierarchy());
       Ht->p = c->H.p;
       Ht->s = c->H.s;
       CSR At;
       transpose(c->H.A0, At, c->H.s);
       build_hierarchy(*Ht, std::move(At));
+      pool.drop();
       std::unique_ptr<Workspace> Wt(new Workspace());
       workspace_init(*Ht, *Wt);
       c->Ht = std::move(Ht);
@@ -442,7 +512,9 @@ int airg_import_hierarchy(airg_handle* out, int nlevels, const airg_level_info* 
     std::unique_ptr<airg_ctx> c(new airg_ctx());
     c->H.p = prm;
     c->H.s = (hipStream_t)hip_stream;
+    SetupPool pool(c->H.s);
     import_hierarchy(c->H, nlevels, infos, levels);
+    pool.drop();
     workspace_init(c->H, c->W);
     AIRG_HIP(hipStreamSynchronize(c->H.s));
     *out = c.release();

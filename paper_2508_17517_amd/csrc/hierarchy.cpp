@@ -154,8 +154,7 @@ void cf_split(const CSR& A, const DBuf<double>& diag, int level, const airg_para
   colcount.zero();
   launch_pattern_transpose_count(A, mask.get(), colcount.get(), s);
   launch_scan_i64(colcount.get(), st_off.get(), n, work.get(), s);
-  int64_t nst = fetch(st_off.get() + n, s);
-  DBuf<int32_t> st_col(nst, s);
+  DBuf<int32_t> st_col(fetch(st_off.get() + n, s), s);
   cursor.zero();
   launch_pattern_transpose_fill(A, mask.get(), st_off.get(), cursor.get(), st_col.get(), s);
 
@@ -174,23 +173,23 @@ void cf_split(const CSR& A, const DBuf<double>& diag, int level, const airg_para
   }
 
   DBuf<double> r(n, s);
-  DBuf<unsigned long long> rmax(1, s);
-  DBuf<int32_t> nf(1, s), counts(1000, s);
+  DBuf<unsigned long long> rmax(2, s);
+  int32_t* const nf = reinterpret_cast<int32_t*>(rmax.get() + 1);
+  DBuf<int32_t> counts(1000, s);
   std::vector<int32_t> hc(1000);
   for (int it = 0; it < p.ddc_its; ++it) {
     rmax.zero();
-    launch_fill_i32(nf.get(), 1, 0, s);
-    launch_ddc_ratio(A, state.get(), diag.get(), r.get(), rmax.get(), nf.get(), s);
-    int32_t nF = fetch(nf.get(), s);
-    unsigned long long bits = fetch(rmax.get(), s);
+    launch_ddc_ratio(A, state.get(), diag.get(), r.get(), rmax.get(), nf, s);
+    unsigned long long found[2];  // the largest ratio's bits, the number of F rows
+    read_back(found, rmax.get(), sizeof(found), s);
+    const int32_t nF = (int32_t)found[1];
     double rm;
-    std::memcpy(&rm, &bits, sizeof(double));
+    std::memcpy(&rm, &found[0], sizeof(double));
     if (nF == 0 || rm == 0.0) break;
     const int64_t k = (int64_t)std::ceil(p.ddc_fraction * (double)nF);
     counts.zero();
     launch_ddc_hist(r.get(), state.get(), n, rm, counts.get(), s);
-    counts.to_host(hc.data(), 1000);
-    AIRG_HIP(hipStreamSynchronize(s));
+    read_back(hc.data(), counts.get(), 1000 * sizeof(int32_t), s);
     // the bin boundary whose conversion count is closest to k (a tie converts more)
     int64_t cum = 0;
     int bstar = 0;

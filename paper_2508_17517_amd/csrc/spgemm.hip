@@ -32,8 +32,7 @@ static int64_t counts_to_rowptr(const DBuf<int32_t>& cnt, int64_t n, DBuf<int32_
   rowptr.alloc(n + 1, s);
   DBuf<int64_t> work(rowptr_work_size(n), s);
   launch_rowptr_scan(cnt.get(), n, rowptr.get(), st.d.get(), work.get(), s);
-  st.d.to_host(st.h, 4);
-  AIRG_HIP(hipStreamSynchronize(s));
+  read_back(st.h, st.d.get(), sizeof(st.h), s);
   if (st.h[0] > 2147483647ll) fail(AIRG_ERR_NOMEM, "sparse matrix exceeds 2^31 nonzeros");
   return st.h[0];
 }
@@ -592,8 +591,7 @@ void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s) {
                                                      nullptr, st.flag(2));
     AIRG_CHECK_LAUNCH();
   }
-  st.d.to_host(st.h, 4);
-  AIRG_HIP(hipStreamSynchronize(s));
+  read_back(st.h, st.d.get(), sizeof(st.h), s);
   if (st.value(2)) drop_zeros(full, C, s);
   else C = std::move(full);
 }
@@ -824,8 +822,7 @@ static bool masked_poly(const CSR& Aff, const std::vector<double>& alpha, CSR& f
     }
 #undef AIRG_CALL
     AIRG_CHECK_LAUNCH();
-    st.d.to_host(st.h, 4);
-    AIRG_HIP(hipStreamSynchronize(s));
+    read_back(st.h, st.d.get(), sizeof(st.h), s);
     if (st.value(0)) continue;
     if (st.value(2)) drop_zeros(full, out, s);
     else out = std::move(full);
@@ -1434,8 +1431,7 @@ bool compress_columns(CSR& A, hipStream_t s) {
                                                       stat.get());
   AIRG_CHECK_LAUNCH();
   int32_t st[2];
-  stat.to_host(st, 2);
-  AIRG_HIP(hipStreamSynchronize(s));
+  read_back(st, stat.get(), sizeof(st), s);
   // worth it only if nearly every block compresses
   if ((int64_t)st[0] * 16 > nblk) {
     A.cbase.release();
@@ -1452,35 +1448,45 @@ bool compress_columns(CSR& A, hipStream_t s) {
 // ------------------------------------------------------------------ row blocks
 // Row blocks for the row-block product: greedy over the rows, a block takes
 // consecutive rows of one 64-row group while its entries fit in
-// kRowBlockEntries; a longer row is a block by itself.
+// kRowBlockEntries; a longer row is a block by itself.  One thread walks the
+// rows of a group (the blocks of a group do not depend on another's).
+constexpr int kRowBlockEntries = 2048;
+template <bool FILL>
+__global__ void row_blocks_kernel(const int32_t* __restrict__ rowptr, int64_t rows, int64_t groups,
+                                  int32_t* __restrict__ count, const int32_t* __restrict__ first,
+                                  int32_t* __restrict__ rblk) {
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= groups) return;
+  const int64_t r0 = g << kColBlockShift, r1 = min(r0 + ((int64_t)1 << kColBlockShift), rows);
+  int n = 0;
+  int start = rowptr[r0], end = start;
+  for (int64_t r = r0; r < r1; ++r) {
+    const int next = rowptr[r + 1];
+    // row r opens a block: the group's first, or the one before is full
+    if (r == r0 || next - start > kRowBlockEntries) {
+      if (FILL) rblk[first[g] + n] = (int32_t)r;
+      ++n;
+      start = end;
+    }
+    end = next;
+  }
+  if (!FILL) count[g] = n;
+  else if (g == groups - 1) rblk[first[g] + n] = (int32_t)rows;
+}
 void build_row_blocks(CSR& A, hipStream_t s) {
-  constexpr int64_t kRowBlockEntries = 2048;
   A.rblk.release();
   A.nrblk = 0;
   if (A.rows <= 0) return;
-  std::vector<int32_t> rp(A.rows + 1);
-  A.rowptr.to_host(rp.data(), A.rows + 1);
-  AIRG_HIP(hipStreamSynchronize(s));
-  std::vector<int32_t> rb;
-  rb.reserve(A.rows / 4 + 2);
-  int64_t r = 0;
-  rb.push_back(0);
-  while (r < A.rows) {
-    const int64_t start = r;
-    const int64_t gend = std::min<int64_t>(((r >> kColBlockShift) + 1) << kColBlockShift, A.rows);
-    int64_t nz = 0;
-    while (r < gend) {
-      const int64_t len = rp[r + 1] - rp[r];
-      if (r > start && nz + len > kRowBlockEntries) break;
-      nz += len;
-      ++r;
-    }
-    rb.push_back((int32_t)r);
-  }
-  A.nrblk = (int64_t)rb.size() - 1;
-  A.rblk.alloc(rb.size(), s);
-  A.rblk.from_host(rb.data(), rb.size());
-  AIRG_HIP(hipStreamSynchronize(s));
+  const int64_t groups = (A.rows + 63) >> kColBlockShift;
+  const unsigned nb = blocks_for(groups, kBlock);
+  DBuf<int32_t> cnt(groups, s), first;
+  row_blocks_kernel<false><<<nb, kBlock, 0, s>>>(A.rowptr.get(), A.rows, groups, cnt.get(), nullptr, nullptr);
+  AIRG_CHECK_LAUNCH();
+  A.nrblk = counts_to_rowptr(cnt, groups, first, s);
+  A.rblk.alloc(A.nrblk + 1, s);
+  row_blocks_kernel<true><<<nb, kBlock, 0, s>>>(A.rowptr.get(), A.rows, groups, nullptr, first.get(),
+                                                A.rblk.get());
+  AIRG_CHECK_LAUNCH();
 }
 
 }  // namespace airg

@@ -176,6 +176,18 @@ size_t rowptr_work_size(int64_t n);
 void launch_rowptr_scan(const int32_t* cnt, int64_t n, int32_t* rowptr, int64_t* total, int64_t* work,
                         hipStream_t s);
 
+// The setup's Arnoldi sweeps, every sum in the tree order: out[k] = V_k . w,
+// k < nv, and out[nv] = w . w; the same after w = w - sum_k h[k] V_k; the update
+// and out[0] = w . w.  nv + 1 at most kArnoldiVecs, V and w 16-byte aligned with
+// ldv even; `work` as for launch_tree_dots with nv + 1 vectors.
+constexpr int kArnoldiVecs = 64;
+void launch_arnoldi_dots(const double* V, int64_t ldv, int nv, double* w, int64_t n, double* out, double* work,
+                         hipStream_t s);
+void launch_arnoldi_update_dots(const double* V, int64_t ldv, int nv, const double* h, double* w, int64_t n,
+                                double* out, double* work, hipStream_t s);
+void launch_arnoldi_update_norm2(const double* V, int64_t ldv, int nv, const double* h, double* w, int64_t n,
+                                 double* out, double* work, hipStream_t s);
+
 // ---------------------------------------------------------------- spmv.hip
 // Rows-per-thread-group shape of a CSR kernel (lanes per row, power of 2).
 int pick_tpr(int64_t rows, int64_t nnz);

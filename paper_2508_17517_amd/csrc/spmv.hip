@@ -905,8 +905,62 @@ void spmv_x32(const OpView& A, int tpr, int K, const float* x, double* y, hipStr
 }
 
 // ------------------------------------------------------------------ FP64 wrappers
+// The setup's product: every row summed left to right from 0.  A workgroup takes
+// `per` consecutive rows, whose entries it loads in chunks of kSeqChunk at
+// consecutive addresses, leaves the products in LDS and lets a thread per row
+// add its own in order.  One lane walking each row instead reads a cache line
+// per entry and lane: from about 4 entries a row on the loads are most of the
+// product (the 230 products of the Arnoldi processes of a setup at FV 2048^2
+// took 42.3 ms that way); with the fused sweeps, the truncation tests
+// there went from 83 to 46 ms).
+constexpr int kSeqChunk = 2048;
+__global__ __launch_bounds__(256) void spmv_seq_kernel(const int32_t* __restrict__ rowptr,
+                                                       const int32_t* __restrict__ col,
+                                                       const double* __restrict__ val, int64_t rows, int per,
+                                                       const double* __restrict__ x, double* __restrict__ y) {
+  __shared__ double prod[kSeqChunk];
+  const int t = threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * per, r1 = min(r0 + per, rows);
+  const bool mine = t < r1 - r0;
+  int rs = 0, re = 0;
+  if (mine) {
+    rs = rowptr[r0 + t];
+    re = rowptr[r0 + t + 1];
+  }
+  const int p0 = rowptr[r0], p1 = rowptr[r1];
+  double sum = 0.0;
+  for (int c0 = p0; c0 < p1; c0 += kSeqChunk) {
+    const int c1 = min(c0 + kSeqChunk, p1);
+    int c[8];
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int p = c0 + t + 256 * u;
+      c[u] = p < c1 ? col[p] : -1;
+      v[u] = p < c1 ? val[p] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (c[u] >= 0) prod[t + 256 * u] = v[u] * x[c[u]];
+    __syncthreads();
+    if (mine) {
+      const int e = min(re, c1);
+      for (int p = max(rs, c0); p < e; ++p) sum = sum + prod[p - c0];
+    }
+    __syncthreads();
+  }
+  if (mine) y[r0 + t] = sum;
+}
 void spmv_seq(const CSR& A, const double* x, double* y, hipStream_t s) {
-  spmv_t(opview(A), 1, 1, x, y, s);
+  if (A.rows <= 0) return;
+  if (A.nnz < 3 * A.rows) {
+    spmv_t(opview(A), 1, 1, x, y, s);
+    return;
+  }
+  // rows for about a chunk, at most one per thread
+  const int per = (int)std::max<int64_t>(1, std::min<int64_t>(256, kSeqChunk * A.rows / A.nnz));
+  spmv_seq_kernel<<<blocks_for(A.rows, per), 256, 0, s>>>(A.rowptr.get(), A.col.get(), A.val.get(), A.rows, per, x, y);
+  AIRG_CHECK_LAUNCH();
 }
 void spmv(const CSR& A, int tpr, const double* x, double* y, hipStream_t s) {
   spmv_t(opview(A), tpr, 1, x, y, s);

@@ -240,16 +240,9 @@ size_t dot_work_size(int64_t n, int nv) {
   return (size_t)nv * (size_t)(nb + nb2 + 2);
 }
 
-void launch_tree_dots(const double* V, int64_t ldv, int nv, const double* w, int64_t n, double* out,
-                      double* work, hipStream_t s) {
-  if (nv <= 0) return;
-  if (nv > kMaxDotVecs) fail(AIRG_ERR_INVALID, "too many vectors in one dot launch");
-  int64_t nb = (n + kDotChunk - 1) / kDotChunk;
-  if (nb < 1) nb = 1;
-  double* a = work;
-  double* b = work + (size_t)nv * nb;
-  tree_dot_stage1<<<(unsigned)nb, 256, 0, s>>>(V, ldv, nv, w, n, a, nb);
-  AIRG_CHECK_LAUNCH();
+// The upper stages of nv tree sums whose chunk partials are a[k nb + q]; b is
+// scratch behind them.
+static void tree_finish(double* a, double* b, int nv, int64_t nb, double* out, hipStream_t s) {
   int64_t m = nb;
   int64_t stride = nb;
   for (;;) {
@@ -264,6 +257,96 @@ void launch_tree_dots(const double* V, int64_t ldv, int nv, const double* w, int
     m = mb;
     stride = dstride;
   }
+}
+
+void launch_tree_dots(const double* V, int64_t ldv, int nv, const double* w, int64_t n, double* out,
+                      double* work, hipStream_t s) {
+  if (nv <= 0) return;
+  if (nv > kMaxDotVecs) fail(AIRG_ERR_INVALID, "too many vectors in one dot launch");
+  int64_t nb = (n + kDotChunk - 1) / kDotChunk;
+  if (nb < 1) nb = 1;
+  tree_dot_stage1<<<(unsigned)nb, 256, 0, s>>>(V, ldv, nv, w, n, work, nb);
+  AIRG_CHECK_LAUNCH();
+  tree_finish(work, work + (size_t)nv * nb, nv, nb, out, s);
+}
+
+// One sweep of the setup's Arnoldi process in the tree order: with UPDATE
+// w = w - sum_k h[k] V_k (k ascending, as cgs_update_kernel), then the products
+// V_k . w (DOTS) and, as the last, w . w.  A block's 1024 elements of the V_k
+// are read again for the products while they are still in the XCD's L2, so a
+// sweep passes over memory once instead of twice and takes one launch less.
+template <bool UPDATE, bool DOTS>
+__global__ __launch_bounds__(256) void arnoldi_sweep_kernel(const double* __restrict__ V, int64_t ldv, int nv,
+                                                            const double* __restrict__ h, double* __restrict__ w,
+                                                            int64_t n, double* __restrict__ part, int64_t nb) {
+  __shared__ double red[DOTS ? kMaxDotVecs : 1][4];
+  const int t = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * kDotChunk + 4 * t;
+  const bool whole = i0 + 4 <= n;
+  auto load = [&](const double* p, double (&x)[4]) {
+    if (whole) {
+      const double2 a = reinterpret_cast<const double2*>(p + i0)[0], b = reinterpret_cast<const double2*>(p + i0)[1];
+      x[0] = a.x;
+      x[1] = a.y;
+      x[2] = b.x;
+      x[3] = b.y;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = i0 + q < n ? p[i0 + q] : 0.0;
+    }
+  };
+  double w4[4];
+  load(w, w4);
+  if constexpr (UPDATE) {
+    for (int k = 0; k < nv; ++k) {
+      double v[4];
+      load(V + (int64_t)k * ldv, v);
+      const double hk = h[k];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w4[q] = w4[q] - hk * v[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i0 + q < n) w[i0 + q] = w4[q];
+      else w4[q] = 0.0;
+  }
+  const int lane = t & 63, wave = t >> 6;
+  const int cnt = DOTS ? nv + 1 : 1;
+  for (int k = 0; k < cnt; ++k) {
+    double v[4];
+    if (k < cnt - 1) {
+      load(V + (int64_t)k * ldv, v);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = w4[q];
+    }
+    const double s = wave_tree((v[0] * w4[0] + v[1] * w4[1]) + (v[2] * w4[2] + v[3] * w4[3]));
+    if (lane == 0) red[k][wave] = s;
+  }
+  __syncthreads();
+  if (t < cnt) part[(int64_t)t * nb + blockIdx.x] = (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
+}
+template <bool UPDATE, bool DOTS>
+static void launch_arnoldi_sweep(const double* V, int64_t ldv, int nv, const double* h, double* w, int64_t n,
+                                 double* out, double* work, hipStream_t s) {
+  const int64_t nb = std::max<int64_t>(1, (n + kDotChunk - 1) / kDotChunk);
+  const int cnt = DOTS ? nv + 1 : 1;
+  if (cnt > kMaxDotVecs) fail(AIRG_ERR_INVALID, "too many vectors in one dot launch");
+  arnoldi_sweep_kernel<UPDATE, DOTS><<<(unsigned)nb, 256, 0, s>>>(V, ldv, nv, h, w, n, work, nb);
+  AIRG_CHECK_LAUNCH();
+  tree_finish(work, work + (size_t)cnt * nb, cnt, nb, out, s);
+}
+void launch_arnoldi_dots(const double* V, int64_t ldv, int nv, double* w, int64_t n, double* out, double* work,
+                         hipStream_t s) {
+  launch_arnoldi_sweep<false, true>(V, ldv, nv, nullptr, w, n, out, work, s);
+}
+void launch_arnoldi_update_dots(const double* V, int64_t ldv, int nv, const double* h, double* w, int64_t n,
+                                double* out, double* work, hipStream_t s) {
+  launch_arnoldi_sweep<true, true>(V, ldv, nv, h, w, n, out, work, s);
+}
+void launch_arnoldi_update_norm2(const double* V, int64_t ldv, int nv, const double* h, double* w, int64_t n,
+                                 double* out, double* work, hipStream_t s) {
+  launch_arnoldi_sweep<true, false>(V, ldv, nv, h, w, n, out, work, s);
 }
 
 __global__ void sqrt_kernel(double* v) { v[0] = sqrt(v[0]); }

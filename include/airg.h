@@ -130,7 +130,9 @@ typedef struct {
 typedef enum { AIRG_INVERSE_ARNOLDI = 0, AIRG_INVERSE_NEUMANN = 1 } airg_inverse;
 
 /* F-point smoothers.  AIRG_SMOOTH_POLY applies the GMRES polynomial
- * matrix-free (d products with A_ff, Sec. 2.2); AIRG_SMOOTH_ASSEMBLED applies
+ * matrix-free (d products with A_ff, Sec. 2.2), or, on a level where that
+ * costs less, multiplies once with the polynomial's own matrix, formed at setup
+ * with nothing dropped (the same operator to rounding); AIRG_SMOOTH_ASSEMBLED applies
  * the assembled fixed-sparsity Ahat^{-1} of Eq. fixed_sparsity (one product
  * with an operator of A_ff's pattern, kept per level). */
 typedef enum { AIRG_SMOOTH_POLY = 0, AIRG_SMOOTH_ASSEMBLED = 1 } airg_smoother;
@@ -300,7 +302,8 @@ enum airg_kernel_class {
   AIRG_K_POLY = 0,      /* every polynomial SpMV of a V-cycle: Horner smoother steps on
                            all levels and the Newton steps of the coarse solve */
   AIRG_K_HORNER = 1,    /* smoother products only: Horner or Neumann steps, or the
-                           assembled Ahat^{-1} (Sec. 2.2) */
+                           assembled Ahat^{-1} (Sec. 2.2), or the polynomial formed as one
+                           matrix */
   AIRG_K_NEWTON = 2,    /* coarse Newton steps only (Sec. 2.3) */
   AIRG_K_RESIDUAL = 3,  /* F-point residual s = r_f - (A_fc + A_ff W) e_c (Eq. f_point) */
   AIRG_K_RESTRICT = 4,  /* restriction r_c + Z r_f */
@@ -340,7 +343,8 @@ int airg_stream_probe(int kind, const void* src, void* dst, int64_t bytes, int r
 
 /* Solve operators, for the launch-shape tuner. */
 enum airg_operator {
-  AIRG_OP_FF = 0,   /* A_ff of a level (smoother steps) */
+  AIRG_OP_FF = 0,   /* the smoother's operator of a level: A_ff (Horner steps), or the
+                       polynomial of A_ff formed as one matrix where that is cheaper */
   AIRG_OP_B = 1,    /* A_fc + A_ff W of a level (F-point residual) */
   AIRG_OP_Z = 2,    /* Z of a level (restriction) */
   AIRG_OP_A = 3,    /* the coarsest matrix (Newton steps) */

@@ -674,6 +674,12 @@ void finalize_hierarchy(Hierarchy& H) {
     L.tpr_b = pick_tpr(L.B.rows, L.B.nnz);
     L.tpr_z = pick_tpr(L.Z.rows, L.Z.nnz);
     if (asm_smoother) L.tpr_hat = pick_tpr(L.Ahat.rows, L.Ahat.nnz);
+    // the GMRES polynomial as one matrix where that is cheaper; a second F
+    // smooth (FCF) keeps the matrix-free form for both
+    if (!asm_smoother && !neumann && H.p.smooth_type != AIRG_SMOOTH_TYPE_FCF &&
+        exact_polynomial(L.Aff, L.alpha, value_bytes(H.p.precision),
+                         H.p.precision == AIRG_FP64 ? 8.0 : 4.0, L.Aq, s))
+      L.tpr_q = pick_tpr(L.Aq.rows, L.Aq.nnz);
   }
   int64_t off = 0;
   for (Level& L : H.levels) {
@@ -745,6 +751,7 @@ void finalize_hierarchy(Hierarchy& H) {
       lower(L.B, L.b32, L.b16);
       lower(L.Z, L.z32, L.z16);
       if (L.Ahat.rows > 0) lower(L.Ahat, L.hat32, L.hat16);
+      if (L.Aq.rows > 0) lower(L.Aq, L.q32, L.q16);
       for (SolveOp* o : {&L.cf, &L.cc, &L.hat_cc, &L.fc})
         if (o->m.rows > 0) lower(o->m, o->v32, o->v16);
       if (L.dinv.get()) {
@@ -769,6 +776,7 @@ void finalize_hierarchy(Hierarchy& H) {
     prepare(L.B);
     prepare(L.Z);
     if (L.Ahat.rows > 0) prepare(L.Ahat);
+    if (L.Aq.rows > 0) prepare(L.Aq);
     for (SolveOp* o : {&L.cf, &L.cc, &L.hat_cc, &L.fc})
       if (o->m.rows > 0) prepare(o->m);
   }
@@ -787,6 +795,7 @@ void finalize_hierarchy(Hierarchy& H) {
       launch_check_csr(L.Aff, flags.get(), s);
       launch_check_csr(L.B, flags.get(), s);
       launch_check_csr(L.Z, flags.get(), s);
+      if (L.Aq.rows > 0) launch_check_csr(L.Aq, flags.get(), s);
       if (H.p.smoother == AIRG_SMOOTH_ASSEMBLED) {
         if (L.Ahat.rows != L.nF || L.Ahat.cols != L.nF)
           fail(AIRG_ERR_INVALID, "assembled smoother missing on level " + std::to_string(l));
@@ -849,6 +858,7 @@ void finalize_hierarchy(Hierarchy& H) {
         add(L.A, L.off);
       } else {
         add(L.Aff, L.off);
+        if (L.Aq.rows > 0) add(L.Aq, L.off);
         add(L.B, L.off);
         add(L.Z, L.off + L.nF);
       }
@@ -992,10 +1002,12 @@ void hierarchy_stats(const Hierarchy& H, airg_stats* st) {
       bytes += csr_bytes((double)L.nC, (double)L.Z.nnz) + 8.0 * (L.nF + 2 * L.nC);
       // residual: B, e_c gathered, r_f read, s written
       bytes += csr_bytes((double)L.nF, (double)L.B.nnz) + 8.0 * (L.nC + 2 * L.nF);
-      // d Horner steps (or one product with Ahat^{-1}): the operator, y
-      // gathered, s read, out written; the last one also reads cmap and
-      // gathers W e_c
-      if (asm_smoother)
+      // d Horner steps (or one product with Ahat^{-1} or with q(A_ff)): the
+      // operator, y gathered, s read, out written; the last one also reads
+      // cmap and gathers W e_c
+      if (L.Aq.rows > 0)
+        bytes += csr_bytes((double)L.nF, (double)L.Aq.nnz) + 8.0 * 3 * L.nF + 12.0 * L.nF;
+      else if (asm_smoother)
         bytes += csr_bytes((double)L.nF, (double)L.Ahat.nnz) + 8.0 * 3 * L.nF + 12.0 * L.nF;
       else
         bytes += d * (csr_bytes((double)L.nF, (double)L.Aff.nnz) + 8.0 * 3 * L.nF) + 12.0 * L.nF;

@@ -180,12 +180,12 @@ VecSet<float> vecs32(Workspace& W, float* e) {
 }
 
 struct LevelOps {
-  OpView ff, b, z, a, hat;
+  OpView ff, b, z, a, hat, q;
 };
 LevelOps ops_of(const Level& L, int prec) {
   return {op_view(L.Aff, L.ff32, L.ff16, prec), op_view(L.B, L.b32, L.b16, prec),
           op_view(L.Z, L.z32, L.z16, prec), op_view(L.A, L.a32, L.a16, prec),
-          op_view(L.Ahat, L.hat32, L.hat16, prec)};
+          op_view(L.Ahat, L.hat32, L.hat16, prec), op_view(L.Aq, L.q32, L.q16, prec)};
 }
 // the view of A with the activity masks gm (null: unmasked)
 OpView masked(OpView v, const CSR& A, const uint8_t* gm) {
@@ -193,12 +193,13 @@ OpView masked(OpView v, const CSR& A, const uint8_t* gm) {
   return v;
 }
 // The operators of a V-cycle over a problem batch's per-problem processes:
-// A_ff, B, Z and the coarsest matrix skip the row groups whose problems are
+// A_ff (or q(A_ff)), B, Z and the coarsest matrix skip the row groups whose problems are
 // inactive.  Their input there is exactly zero, so the skipped sums (0) are
 // the ones the products would give.
 LevelOps ops_of(const Level& L, int prec, const uint8_t* gm) {
   LevelOps o = ops_of(L, prec);
   o.ff = masked(o.ff, L.Aff, gm);
+  o.q = masked(o.q, L.Aq, gm);
   o.b = masked(o.b, L.B, gm);
   o.z = masked(o.z, L.Z, gm);
   o.a = masked(o.a, L.A, gm);
@@ -247,7 +248,8 @@ void horner(const Level& L, const OpView& Aff, int K, const X* sv, const X* ec, 
 }
 
 // The F-point smoother: the polynomial matrix-free (Horner), or one product
-// with the assembled Ahat^{-1} fused with the prolongation.
+// with the polynomial formed exactly (Level::Aq) or with the assembled
+// Ahat^{-1}, fused with the prolongation.
 template <class X>
 const X* dinv_of(const Level& L);
 template <>
@@ -287,18 +289,26 @@ void neumann(const Level& L, const OpView& Aff, int K, const X* sv, const X* ec,
 template <class X>
 void smooth(const Level& L, const LevelOps& o, int K, const X* sv, const X* ec, X* ef, X* y0,
             X* y1, hipStream_t s, LaunchTally* tally = nullptr) {
+  // one product with the operator Op (lanes tpr), fused with the prolongation
+  auto one_product = [&](const OpView& Op, int tpr) {
+    spmv_horner_prolong_t<X>(Op, tpr, K, sv, sv, ef, 1.0, 0.0, L.cmap.get(), ec, s);
+    if (tally) {
+      const double xb = (double)sizeof(X);
+      const int64_t n = L.nF * K;
+      tally->add(csr_bytes(L.nF, Op.nnz, vt_bytes(Op.vt)) + xb * n * 4 + 4.0 * L.nF,
+                 2.0 * (double)Op.nnz * K + 3.0 * n, col_saving(Op));
+    }
+  };
+  if (L.Aq.rows > 0) {
+    one_product(o.q, L.tpr_q);
+    return;
+  }
   if (L.Ahat.rows == 0) {
     if (L.dinv.get()) neumann<X>(L, o.ff, K, sv, ec, ef, y0, y1, s, tally);
     else horner<X>(L, o.ff, K, sv, ec, ef, y0, y1, s, tally);
     return;
   }
-  spmv_horner_prolong_t<X>(o.hat, L.tpr_hat, K, sv, sv, ef, 1.0, 0.0, L.cmap.get(), ec, s);
-  if (tally) {
-    const double xb = (double)sizeof(X);
-    const int64_t n = L.nF * K;
-    tally->add(csr_bytes(L.nF, o.hat.nnz, vt_bytes(o.hat.vt)) + xb * n * 4 + 4.0 * L.nF,
-               2.0 * (double)o.hat.nnz * K + 3.0 * n, col_saving(o.hat));
-  }
+  one_product(o.hat, L.tpr_hat);
 }
 
 // out += q(A) s by Horner with the last product accumulating into out (the
@@ -1240,7 +1250,9 @@ int autotune(Hierarchy& H, Workspace& W, int reps, std::vector<airg_tune_entry>&
   for (int l = 0; l < L; ++l) {
     Level& lv = H.levels[l];
     const LevelOps o = ops_of(lv, prec);
-    t.push_back({l, AIRG_OP_FF, o.ff, &lv.tpr_ff, !low});
+    // the smoother's operator: q(A_ff) where it is formed
+    if (lv.Aq.rows > 0) t.push_back({l, AIRG_OP_FF, o.q, &lv.tpr_q, !low});
+    else t.push_back({l, AIRG_OP_FF, o.ff, &lv.tpr_ff, !low});
     t.push_back({l, AIRG_OP_B, o.b, &lv.tpr_b, !low});
     t.push_back({l, AIRG_OP_Z, o.z, &lv.tpr_z, !low});
     if (lv.Ahat.rows > 0) t.push_back({l, AIRG_OP_HAT, o.hat, &lv.tpr_hat, !low});
@@ -1330,7 +1342,16 @@ void set_lanes(Hierarchy& H, int level, int op, int lanes, int xcd_map, int lds)
     fail(AIRG_ERR_INVALID, "this operator has no row blocks (rows shorter than 8 on average)");
   if (lds == 1 && !A->col16.get())
     fail(AIRG_ERR_INVALID, "this operator has no compressed columns for the LDS-staged product");
-  *tpr = lanes | (xcd_map << 8) | (lds == 1 ? kShapeLds : lds == 2 ? kShapeEntries : 0);
+  const int shape = lanes | (xcd_map << 8);
+  *tpr = shape | (lds == 1 ? kShapeLds : lds == 2 ? kShapeEntries : 0);
+  // a smoother that multiplies with q(A_ff) takes A_ff's shape too, with the x
+  // window in LDS only if that operator's columns are compressed, and in row
+  // blocks only if it has them
+  if (op == AIRG_OP_FF && H.levels[level].Aq.rows > 0) {
+    Level& lv = H.levels[level];
+    if (lanes == 0 && !lv.Aq.rblk.get()) return;
+    lv.tpr_q = lds == 1 && !lv.Aq.col16.get() ? shape : *tpr;
+  }
 }
 
 }  // namespace airg

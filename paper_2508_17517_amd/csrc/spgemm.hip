@@ -874,6 +874,72 @@ void fixed_sparsity_inverse(const CSR& Aff, const std::vector<double>& alpha, CS
   drop_zeros(full, out, s);
 }
 
+// ------------------------------------------------------------------ exact polynomial
+// a_ii += a; *missing is set where a row stores no diagonal
+__global__ void add_diag_kernel(int64_t rows, const int32_t* rowptr, const int32_t* col, double a,
+                                double* val, int32_t* missing) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= rows) return;
+  const int r = find_col(col, rowptr[i], rowptr[i + 1], (int)i);
+  if (r >= 0) val[r] = val[r] + a;
+  else atomicOr(missing, 1);
+}
+
+// The matrix-free smoother reads A and three vectors d times; one product with
+// Q = q(A) reads Q and the vectors once.  With few couplings between F points
+// (1.4 a row on the finest upwind level, 2.0 on the next) Q hardly fills in
+// (1.7 and 4.0 entries a row at d = 4), so the smoother is nearly d times
+// cheaper; from about 8 entries a row on, Q holds ten times A's entries and
+// loses.  Both sides are priced as launches * 2.6 us (what a small product
+// takes) plus bytes at 5 TB/s (what the large ones reach), and Q has to win
+// by a tenth.  Small levels are all launches: there Q may be 40 times denser
+// and still wins.  Smoother of one V-cycle, FV 2048^2 in FP64, measured: the
+// finest level 4 x 12.9 us in d products, 19 us in one; the next 4 x 10.1 and
+// 15 us; the third 4 x 10.8 and 33 us.
+bool exact_polynomial(const CSR& A, const std::vector<double>& alpha, double vbytes, double xbytes,
+                      CSR& Q, hipStream_t s) {
+  Q = CSR();
+  const int d = (int)alpha.size() - 1;
+  const int64_t n = A.rows;
+  if (d < 2 || n <= 0 || A.nnz < n) return false;
+  constexpr double kLaunchUs = 2.6, kBytesPerUs = 5.0e6, kWin = 0.9;
+  const double entry = vbytes + 2.0;
+  const double free_us =
+      d * (kLaunchUs + (entry * (double)A.nnz + (4.0 + 3.0 * xbytes) * (double)n) / kBytesPerUs);
+  const double max_nnz = std::min(
+      2147483647.0, ((kWin * free_us - kLaunchUs) * kBytesPerUs - (4.0 + 3.0 * xbytes) * (double)n) / entry);
+  // the growth of a power's entries over the last one's: 2.8 and more from
+  // 8 entries a row on, where a product would only find that out
+  auto hopeless = [&](double nnz, double growth, int left) {
+    double f = 0.5 * nnz;
+    for (int k = 0; k < left; ++k) f *= growth;
+    return std::min(f, (double)n * (double)n) > max_nnz;
+  };
+  if ((double)A.nnz > max_nnz || (A.nnz >= 8 * n && hopeless((double)A.nnz, 2.8, d - 1))) return false;
+  DBuf<int32_t> missing(1, s);
+  launch_fill_i32(missing.get(), 1, 0, s);
+  const unsigned nb = blocks_for(n, kBlock);
+  auto add_diag = [&](CSR& M, double a) {
+    add_diag_kernel<<<nb, kBlock, 0, s>>>(n, M.rowptr.get(), M.col.get(), a, M.val.get(), missing.get());
+    AIRG_CHECK_LAUNCH();
+  };
+  CSR P;  // alpha_d A + alpha_{d-1} I
+  copy_csr(A, P, s);
+  launch_scale(P.val.get(), A.val.get(), alpha[d], A.nnz, s);
+  add_diag(P, alpha[d - 1]);
+  for (int k = d - 2; k >= 0; --k) {
+    CSR T;
+    spgemm(A, P, T, s);
+    if ((double)T.nnz > max_nnz || (k > 0 && hopeless((double)T.nnz, (double)T.nnz / (double)P.nnz, k)))
+      return false;
+    add_diag(T, alpha[k]);
+    P = std::move(T);
+  }
+  if (fetch(missing.get(), s)) return false;
+  Q = std::move(P);
+  return true;
+}
+
 // ------------------------------------------------------------------ Neumann (nAIR)
 __global__ void row_diag_kernel(CSRView A, double* d) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -448,7 +448,6 @@ void build_hierarchy(Hierarchy& H, CSR&& Ain) {
     L.roots = std::move(roots);
     if (lvl == 0) copy_csr(H.A0, L.A, s);
     else L.A = std::move(cur);
-    L.tpr_a = pick_tpr(L.A.rows, L.A.nnz);
     break;
   }
   finalize_hierarchy(H);
@@ -651,7 +650,6 @@ void finalize_hierarchy(Hierarchy& H) {
     if (H.p.smooth_type == AIRG_SMOOTH_TYPE_FCF) {
       L.fc.m = std::move(L.Afc);
       sort_rows(L.fc.m, s);
-      L.fc.tpr = pick_tpr(L.fc.m.rows, L.fc.m.nnz);
     }
     L.Afc = CSR();
     // C-point smoothing: A_cf and A_cc in the solve numbering, and A_cc's
@@ -661,25 +659,17 @@ void finalize_hierarchy(Hierarchy& H) {
         fail(AIRG_ERR_INVALID, "C-point smoothing data missing on level " + std::to_string(l));
       permute_rows(L.Acf_nat, N.pos.get(), order ? frank.get() : nullptr, L.nF, L.cf.m, s, true);
       permute_rows(L.Acc_nat, N.pos.get(), N.pos.get(), L.nC, L.cc.m, s, true);
-      L.cf.tpr = pick_tpr(L.cf.m.rows, L.cf.m.nnz);
-      L.cc.tpr = pick_tpr(L.cc.m.rows, L.cc.m.nnz);
       if (asm_smoother) {
         CSR hc;
         fixed_sparsity_inverse(L.Acc_nat, L.alpha_c, hc, s);
         permute_rows(hc, N.pos.get(), N.pos.get(), L.nC, L.hat_cc.m, s, true);
-        L.hat_cc.tpr = pick_tpr(L.hat_cc.m.rows, L.hat_cc.m.nnz);
       }
     }
-    L.tpr_ff = pick_tpr(L.Aff.rows, L.Aff.nnz);
-    L.tpr_b = pick_tpr(L.B.rows, L.B.nnz);
-    L.tpr_z = pick_tpr(L.Z.rows, L.Z.nnz);
-    if (asm_smoother) L.tpr_hat = pick_tpr(L.Ahat.rows, L.Ahat.nnz);
     // the GMRES polynomial as one matrix where that is cheaper; a second F
     // smooth (FCF) keeps the matrix-free form for both
-    if (!asm_smoother && !neumann && H.p.smooth_type != AIRG_SMOOTH_TYPE_FCF &&
-        exact_polynomial(L.Aff, L.alpha, value_bytes(H.p.precision),
-                         H.p.precision == AIRG_FP64 ? 8.0 : 4.0, L.Aq, s))
-      L.tpr_q = pick_tpr(L.Aq.rows, L.Aq.nnz);
+    if (!asm_smoother && !neumann && H.p.smooth_type != AIRG_SMOOTH_TYPE_FCF)
+      exact_polynomial(L.Aff, L.alpha, value_bytes(H.p.precision),
+                       H.p.precision == AIRG_FP64 ? 8.0 : 4.0, L.Aq, s);
   }
   int64_t off = 0;
   for (Level& L : H.levels) {
@@ -710,7 +700,6 @@ void finalize_hierarchy(Hierarchy& H) {
     H.stacked_len += H.levels[l].n;
   }
   permute_rows(H.A0, H.levels[0].pos.get(), H.levels[0].pos.get(), H.n0, H.Aperm, s, order);
-  H.tpr_top = pick_tpr(H.Aperm.rows, H.Aperm.nnz);
   // The rows of the top matrix and of every Z are points of several blocks
   // of the nested numbering (level l's F points, then level l+1's, ...),
   // each block in locality order; taken in that order, the rows of each
@@ -761,24 +750,26 @@ void finalize_hierarchy(Hierarchy& H) {
     }
   }
   // compressed columns for every solve operator whose row blocks allow them,
-  // and row blocks for the operators with long rows
-  auto prepare = [&](CSR& A) {
+  // row blocks for the operators with long rows, and the default launch shapes
+  const int64_t xbytes = H.p.precision == AIRG_FP64 ? 8 : 4;
+  auto prepare = [&](CSR& A, OpRole role = OpRole::Plain) {
     compress_columns(A, s);
     if (A.rows > 0 && A.nnz >= 8 * A.rows) build_row_blocks(A, s);
+    return pick_shape(A, role, xbytes);
   };
-  prepare(H.Aperm);
+  H.tpr_top = prepare(H.Aperm, OpRole::Top);
   for (Level& L : H.levels) {
     if (L.coarsest) {
-      prepare(L.A);
+      L.tpr_a = prepare(L.A, OpRole::Coarsest);
       continue;
     }
-    prepare(L.Aff);
-    prepare(L.B);
-    prepare(L.Z);
-    if (L.Ahat.rows > 0) prepare(L.Ahat);
-    if (L.Aq.rows > 0) prepare(L.Aq);
+    L.tpr_ff = prepare(L.Aff, OpRole::Smooth);
+    L.tpr_b = prepare(L.B);
+    L.tpr_z = prepare(L.Z, OpRole::Restrict);
+    if (L.Ahat.rows > 0) L.tpr_hat = prepare(L.Ahat);
+    if (L.Aq.rows > 0) L.tpr_q = prepare(L.Aq, OpRole::Smooth);
     for (SolveOp* o : {&L.cf, &L.cc, &L.hat_cc, &L.fc})
-      if (o->m.rows > 0) prepare(o->m);
+      if (o->m.rows > 0) o->tpr = prepare(o->m);
   }
   // every solve-phase operator is checked once, so an inconsistent hierarchy
   // (for example a bad import) fails here instead of in a kernel
@@ -924,7 +915,6 @@ void import_hierarchy(Hierarchy& H, int nlevels, const airg_level_info* infos,
       if (l == 0) copy_csr(H.A0, L.A, s);
       else upload_csr(L.A, in.n, in.n, in.nnz_a, a.a_rowptr, a.a_col, a.a_val, s);
       for (int k = 0; k < in.n_roots; ++k) L.roots.emplace_back(a.roots_re[k], a.roots_im[k]);
-      L.tpr_a = pick_tpr(L.A.rows, L.A.nnz);
       continue;
     }
     if (in.is_coarsest || !a.state || !a.cmap || !a.alpha || in.poly_len <= 0)
@@ -1002,13 +992,13 @@ void hierarchy_stats(const Hierarchy& H, airg_stats* st) {
       bytes += csr_bytes((double)L.nC, (double)L.Z.nnz) + 8.0 * (L.nF + 2 * L.nC);
       // residual: B, e_c gathered, r_f read, s written
       bytes += csr_bytes((double)L.nF, (double)L.B.nnz) + 8.0 * (L.nC + 2 * L.nF);
-      // d Horner steps (or one product with Ahat^{-1} or with q(A_ff)): the
-      // operator, y gathered, s read, out written; the last one also reads
-      // cmap and gathers W e_c
+      // d Horner steps: the operator, y gathered, s read, out written; the last
+      // one also reads cmap and gathers W e_c.  One product with Ahat^{-1} or
+      // q(A_ff) reads s only as its gathered vector
       if (L.Aq.rows > 0)
-        bytes += csr_bytes((double)L.nF, (double)L.Aq.nnz) + 8.0 * 3 * L.nF + 12.0 * L.nF;
+        bytes += csr_bytes((double)L.nF, (double)L.Aq.nnz) + 8.0 * 2 * L.nF + 12.0 * L.nF;
       else if (asm_smoother)
-        bytes += csr_bytes((double)L.nF, (double)L.Ahat.nnz) + 8.0 * 3 * L.nF + 12.0 * L.nF;
+        bytes += csr_bytes((double)L.nF, (double)L.Ahat.nnz) + 8.0 * 2 * L.nF + 12.0 * L.nF;
       else
         bytes += d * (csr_bytes((double)L.nF, (double)L.Aff.nnz) + 8.0 * 3 * L.nF) + 12.0 * L.nF;
       if (H.p.smooth_type != AIRG_SMOOTH_TYPE_F) {

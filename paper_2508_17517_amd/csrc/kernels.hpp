@@ -189,8 +189,11 @@ void launch_arnoldi_update_norm2(const double* V, int64_t ldv, int nv, const dou
                                  double* out, double* work, hipStream_t s);
 
 // ---------------------------------------------------------------- spmv.hip
-// Rows-per-thread-group shape of a CSR kernel (lanes per row, power of 2).
+// Default launch shapes: of any product, and of a solve operator by its role and
+// its (compressed) columns for vectors of xbytes an element.
 int pick_tpr(int64_t rows, int64_t nnz);
+enum class OpRole { Plain, Restrict, Smooth, Top, Coarsest };
+int pick_shape(const CSR& A, OpRole role, int64_t xbytes);
 // Launch shape of a product: lanes per row in bits 0-7 (0: row-block kernel),
 // the XCD mapping in bit 8, the LDS-staged kernel in bit 9, the
 // entry-staged kernel (256 consecutive rows per workgroup, one lane per row)
@@ -224,6 +227,10 @@ void spmv_residual_t(const OpView& B, int tpr, int K, const X* ec, const X* rf, 
                      hipStream_t s);
 // Last Horner step fused with the one-point prolongation:
 //   ef = W e_c + a (A y) + b s,  (W e_c)[i] = ec[cmap[i]] (0 where cmap[i] < 0)
+// e_f = W e_c + A y
+template <class X>
+void spmv_prolong_t(const OpView& A, int tpr, int K, const X* y, X* ef, const int32_t* cmap, const X* ec,
+                    hipStream_t s);
 template <class X>
 void spmv_horner_prolong_t(const OpView& A, int tpr, int K, const X* y, const X* sv, X* ef,
                            double a, double b, const int32_t* cmap, const X* ec, hipStream_t st);

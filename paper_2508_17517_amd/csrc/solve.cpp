@@ -291,12 +291,13 @@ void smooth(const Level& L, const LevelOps& o, int K, const X* sv, const X* ec, 
             X* y1, hipStream_t s, LaunchTally* tally = nullptr) {
   // one product with the operator Op (lanes tpr), fused with the prolongation
   auto one_product = [&](const OpView& Op, int tpr) {
-    spmv_horner_prolong_t<X>(Op, tpr, K, sv, sv, ef, 1.0, 0.0, L.cmap.get(), ec, s);
+    spmv_prolong_t<X>(Op, tpr, K, sv, ef, L.cmap.get(), ec, s);
     if (tally) {
       const double xb = (double)sizeof(X);
       const int64_t n = L.nF * K;
-      tally->add(csr_bytes(L.nF, Op.nnz, vt_bytes(Op.vt)) + xb * n * 4 + 4.0 * L.nF,
-                 2.0 * (double)Op.nnz * K + 3.0 * n, col_saving(Op));
+      // s and W e_c gathered, out written, cmap read
+      tally->add(csr_bytes(L.nF, Op.nnz, vt_bytes(Op.vt)) + xb * n * 3 + 4.0 * L.nF,
+                 2.0 * (double)Op.nnz * K + n, col_saving(Op));
     }
   };
   if (L.Aq.rows > 0) {

@@ -582,14 +582,59 @@ static void launch_spmv(const OpView& A, int tpr, int K, const float* x, Epi epi
   }
 }
 
+// The launch shape an operator gets without the tuner.  Lanes per row grow with
+// the mean row length, more slowly than its quarter so that every lane has a
+// few pairs in flight, and further where a short operator would leave the
+// device empty (fewer than 400,000 lanes; more than 16 a row only pay below
+// 16,384 rows); each XCD takes a contiguous eighth of the rows.  Measured over
+// the operators of FV 2048^2 (FP64), FV 1501 x 999 (FP32) and DG 1024^2 (BF16)
+// against the former rule (a lane per 4 entries, rows dealt out round robin):
+// products of 8 to 40 entries a row 10.7-15.1 us then, 9.1-14.3 now; the top
+// product of FV 2048^2 44.4 and 36.2 us.
 int pick_tpr(int64_t rows, int64_t nnz) {
-  double avg = rows > 0 ? (double)nnz / (double)rows : 0.0;
-  if (avg <= 4.0) return 1;
-  if (avg <= 8.0) return 2;
-  if (avg <= 16.0) return 4;
-  if (avg <= 32.0) return 8;
-  if (avg <= 96.0) return 16;
-  return 32;
+  const double avg = rows > 0 ? (double)nnz / (double)rows : 0.0;
+  const int most = rows < 16384 ? 32 : 16;
+  int lanes = avg <= 3.5 ? 1 : avg <= 10.0 ? 2 : avg <= 24.0 ? 4 : 8;
+  while (lanes < most && rows * lanes < 400000 && avg >= 4.0 * lanes) lanes <<= 1;
+  return lanes | kShapeXcd;
+}
+int pick_shape(const CSR& A, OpRole role, int64_t xbytes) {
+  const double avg = A.rows > 0 ? (double)A.nnz / (double)A.rows : 0.0;
+  // The entry-staged kernel loads the entries of 256 rows at consecutive
+  // addresses, so more gathers are in flight than one lane a row keeps; below
+  // 512 workgroups of it the device is not full and a row's entries in turn are
+  // the whole time (FV 64^2 level 1: 8.3 us, 2.8 with 4 lanes a row).
+  const bool entries = A.rows >= (int64_t)1 << 17;
+  switch (role) {
+    case OpRole::Restrict:
+      // rows of about 3 entries that gather all over a level's F block (level 1
+      // of FV 2048^2: 18.5 us with one lane a row, 15.9); where rows are longer
+      // two lanes are even or better (level 2: 15.2, 15.8)
+      if (entries && avg > 2.4 && avg <= 3.5) return 1 | kShapeEntries | kShapeXcd;
+      break;
+    case OpRole::Smooth:
+      // FV 2048^2 levels 0 and 1 (1.7 and 4.0 entries a row): 17.0 -> 15.0 and
+      // 16.6 -> 15.7 us; 5.3 entries on FV 1501 x 999 9.8 -> 7.6; a diagonal
+      // (1 entry) and rows of 9 are better with lanes
+      if (entries && avg > 1.2 && avg <= 5.5) return 1 | kShapeEntries | kShapeXcd;
+      break;
+    case OpRole::Top:
+      // 5 entries a row (DG 1024^2: 86.0 -> 82.4 us); past 8 M rows the vectors
+      // outgrow the caches and eighths of the rows only spread the traffic over
+      // more pages (FV 4096^2: 229 -> 212; with 4 M rows 36.2 and 37.0)
+      if (entries && ((avg > 3.5 && avg <= 8.0) || A.rows > (int64_t)8 << 20)) return 1 | kShapeEntries;
+      break;
+    case OpRole::Coarsest:
+      // ordered for narrow windows: x from LDS where the windows leave at least
+      // two workgroups a CU and there are groups for the chip (FV 2048^2
+      // 18.0 -> 16.7 us); below that, a row's length in as few turns as it takes
+      // (3,458 rows: 3.2 us)
+      if (A.col16.get() && A.rows >= 8192 && avg >= 48.0 && A.max_span * xbytes <= 64 * 1024)
+        return (A.rows >= 32768 && xbytes == 8 ? 8 : 16) | kShapeLds | kShapeXcd;
+      break;
+    case OpRole::Plain: break;
+  }
+  return pick_tpr(A.rows, A.nnz);
 }
 
 // ------------------------------------------------------------------ epilogues
@@ -713,6 +758,24 @@ struct EpiHornerProlong {
   __device__ void operator()(int64_t i, X t, const Pre& p) const { out[i] = p.e + (a * t + b * p.s); }
 };
 
+// a smoother that is one product: e_f = W e_c + t
+template <class X>
+struct EpiProlong {
+  X* out;
+  const int32_t* cmap;
+  const X* ec;
+  int kshift;
+  struct Pre {
+    X e;
+  };
+  __device__ Pre pre(int64_t i) const {
+    const int64_t row = i >> kshift;
+    const int m = cmap[row];
+    return {m >= 0 ? ec[((int64_t)m << kshift) + (i - (row << kshift))] : X(0)};
+  }
+  __device__ void operator()(int64_t i, X t, const Pre& p) const { out[i] = p.e + t; }
+};
+
 // nAIR's Jacobi-scaled Neumann step y' = y + D^{-1} (s - A y), and the last
 // step fused with the prolongation: e_f = W e_c + (y + D^{-1} (s - A y)).
 // y is the gathered vector; D^{-1} is per row.
@@ -797,6 +860,12 @@ template <class X>
 void spmv_horner_prolong_t(const OpView& A, int tpr, int K, const X* y, const X* sv, X* ef,
                            double a, double b, const int32_t* cmap, const X* ec, hipStream_t st) {
   launch_spmv(A, tpr, K, y, EpiHornerProlong<X>{ef, sv, cmap, ec, (X)a, (X)b, log2_of(K)}, st);
+}
+
+template <class X>
+void spmv_prolong_t(const OpView& A, int tpr, int K, const X* y, X* ef, const int32_t* cmap, const X* ec,
+                    hipStream_t st) {
+  launch_spmv(A, tpr, K, y, EpiProlong<X>{ef, cmap, ec, log2_of(K)}, st);
 }
 
 template <class X>
@@ -885,6 +954,8 @@ void axpy_first_t(X* x, const X* w, double a, bool first, int64_t n, hipStream_t
   template void spmv_residual_t<X>(const OpView&, int, int, const X*, const X*, X*, hipStream_t);  \
   template void spmv_horner_prolong_t<X>(const OpView&, int, int, const X*, const X*, X*, double,  \
                                          double, const int32_t*, const X*, hipStream_t);           \
+  template void spmv_prolong_t<X>(const OpView&, int, int, const X*, X*, const int32_t*, const X*, \
+                                  hipStream_t);                                                    \
   template void prolong_axpy_t<X>(X*, const X*, const int32_t*, const X*, double, int64_t, int,    \
                                   hipStream_t);                                                    \
   template void spmv_neumann_t<X>(const OpView&, int, int, const X*, const X*, const X*, X*,       \

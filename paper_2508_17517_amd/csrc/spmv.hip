@@ -64,32 +64,22 @@ static CSRT<MV, C16> csr_t(const OpView& A) {
 template <int TPR>
 constexpr int unroll_for() { return 4; }
 
-// Column index transforms for row_dot: the CSR column itself, or the column
-// looked up in a map (entries whose mapped index is negative are skipped).
-struct IdxPlain {
-  __device__ __forceinline__ int operator()(int c) const { return c; }
-};
-struct IdxMap {
-  const int32_t* __restrict__ m;
-  __device__ __forceinline__ int operator()(int c) const { return m[c]; }
-};
-
-// sum over entries p = s + lane, s + lane + TPR, ... < e of val[p] * x[idx(col[p]) * K + c]
-template <int TPR, int U, int K, class MV, bool C16, class X, class XI, class Idx>
-__device__ __forceinline__ X row_dot_cols(const CSRT<MV, C16>& A, int s, int e, int b, int lane,
-                                          const XI* __restrict__ x, int c, Idx idx, X sum) {
-  for (int p0 = s + lane; p0 < e; p0 += TPR * U) {
+// sum over entries p = s, s + 1, ... < e of val[p] * x[col[p]], in that order
+template <int U, class MV, bool C16, class X, class XI>
+__device__ __forceinline__ X row_dot_cols(const CSRT<MV, C16>& A, int s, int e, int b,
+                                          const XI* __restrict__ x, X sum) {
+  for (int p0 = s; p0 < e; p0 += U) {
     int col[U];
     X v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int p = p0 + u * TPR;
-      col[u] = p < e ? idx(A.column(p, b)) : -1;
+      const int p = p0 + u;
+      col[u] = p < e ? A.column(p, b) : -1;
       v[u] = p < e ? (X)ldv(A.val[p]) : X(0);
     }
     X xv[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) xv[u] = col[u] >= 0 ? (X)x[(int64_t)col[u] * K + c] : X(0);
+    for (int u = 0; u < U; ++u) xv[u] = col[u] >= 0 ? (X)x[col[u]] : X(0);
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (col[u] >= 0) sum = sum + v[u] * xv[u];
@@ -99,16 +89,16 @@ __device__ __forceinline__ X row_dot_cols(const CSRT<MV, C16>& A, int s, int e, 
 // b: the row's column base in the compressed form; a negative base (a block
 // that kept int32 columns) takes the int32 path.  Rows of one wavefront lie
 // in one 64-row block, so the branch is uniform.
-template <int TPR, int U, int K, class MV, bool C16, class X, class XI, class Idx>
-__device__ __forceinline__ X row_dot(const CSRT<MV, C16>& A, int s, int e, int b, int lane,
-                                     const XI* __restrict__ x, int c, Idx idx, X sum) {
+template <int U, class MV, bool C16, class X, class XI>
+__device__ __forceinline__ X row_dot(const CSRT<MV, C16>& A, int s, int e, int b,
+                                     const XI* __restrict__ x, X sum) {
   if constexpr (C16) {
     if (b < 0) {
       const CSRT<MV, false> W{A.rowptr, A.col, nullptr, nullptr, A.val, A.rows, nullptr, nullptr};
-      return row_dot_cols<TPR, U, K>(W, s, e, 0, lane, x, c, idx, sum);
+      return row_dot_cols<U>(W, s, e, 0, x, sum);
     }
   }
-  return row_dot_cols<TPR, U, K>(A, s, e, b, lane, x, c, idx, sum);
+  return row_dot_cols<U>(A, s, e, b, x, sum);
 }
 
 // Pair loads (K = 1, two or more lanes per row): a lane takes the aligned
@@ -252,7 +242,7 @@ __global__ __launch_bounds__(256) void spmv_kernel(CSRT<MV, C16> A, const XI* __
     if constexpr (TPR >= 2)
       sum = row_dot_pairs<TPR, unroll_for<TPR>()>(A, rs, re, A.base(row), lane, x, sum);
     else
-      sum = row_dot<1, 4, 1>(A, rs, re, A.base(row), 0, x, 0, IdxPlain{}, sum);
+      sum = row_dot<4>(A, rs, re, A.base(row), x, sum);
   }
   if constexpr (TPR > 1) {
 #pragma unroll
@@ -261,19 +251,77 @@ __global__ __launch_bounds__(256) void spmv_kernel(CSRT<MV, C16> A, const XI* __
   if (lane == 0 && live) epi(A.out_row(row), sum, pre);
 }
 
-// column-per-lane kernel (K > 1 interleaved columns): each column's row sum
-// runs left to right from 0, as the TPR = 1 kernel does
-template <int K, class MV, bool C16, class X, class Epi, class XI>
-__global__ __launch_bounds__(256) void spmm_kernel(CSRT<MV, C16> A, const XI* __restrict__ x,
-                                                   Epi epi, int xcd) {
-  const int c = threadIdx.x & (K - 1);
-  const int64_t row = row_block_index(xcd) * (256 / K) + threadIdx.x / K;
-  if (row >= A.rows) return;
-  const int64_t orow = A.out_row(row);
-  const typename Epi::Pre pre = epi.pre(orow * K + c);
-  const X sum = row_dot<1, 4, K>(A, A.rowptr[row], A.rowptr[row + 1], A.base(row), 0, x, c,
-                                 IdxPlain{}, X(0));
-  epi(orow * K + c, sum, pre);
+// K > 1 interleaved columns: a thread takes C consecutive columns of a row
+// (16 bytes of x an entry, all columns if that is fewer), 2^gs threads cover
+// the row's columns and 2^ls such groups share its entries: entry lane l takes
+// entries l, l + 2^ls, ... in order, and the lanes of a column combine by the
+// shuffle tree.
+template <class T, int C>
+struct ColVec {  // only the element's own alignment is promised
+  typedef T type __attribute__((ext_vector_type(C), aligned(sizeof(T))));
+};
+template <int C, class MV, bool C16, class X, class XI>
+__device__ __forceinline__ void row_dot_cols_block(const CSRT<MV, C16>& A, int s, int e, int step, int b,
+                                                   const XI* __restrict__ x, int kshift, X (&sum)[C]) {
+  using V = typename ColVec<XI, C>::type;
+  constexpr int U = 4;
+  for (int p0 = s; p0 < e; p0 += U * step) {
+    int col[U];
+    X v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = p0 + u * step;
+      col[u] = p < e ? A.column(p, b) : -1;
+      v[u] = p < e ? (X)ldv(A.val[p]) : X(0);
+    }
+    V xv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (col[u] >= 0) xv[u] = *reinterpret_cast<const V*>(x + ((int64_t)col[u] << kshift));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (col[u] >= 0) {
+#pragma unroll
+        for (int q = 0; q < C; ++q) sum[q] = sum[q] + v[u] * (X)xv[u][q];
+      }
+  }
+}
+
+template <int C, class MV, bool C16, class X, class Epi, class XI>
+__global__ __launch_bounds__(256) void spmm_kernel(CSRT<MV, C16> A, const XI* __restrict__ x, Epi epi,
+                                                   int kshift, int gs, int ls, int xcd) {
+  const int t = threadIdx.x;
+  const int c = (t & ((1 << gs) - 1)) * C;
+  const int lane = (t >> gs) & ((1 << ls) - 1);
+  const int64_t row = row_block_index(xcd) * (256 >> (gs + ls)) + (t >> (gs + ls));
+  if (row >= A.rows) return;  // the same for all threads of a row
+  const int64_t i0 = (A.out_row(row) << kshift) + c;
+  typename Epi::Pre pre[C];
+  if (lane == 0) {
+#pragma unroll
+    for (int q = 0; q < C; ++q) pre[q] = epi.pre(i0 + q);
+  }
+  X sum[C];
+#pragma unroll
+  for (int q = 0; q < C; ++q) sum[q] = X(0);
+  const int rs = A.rowptr[row] + lane, re = A.rowptr[row + 1], b = A.base(row);
+  bool wide = true;  // uniform over the wavefront: its rows lie in one 64-row block
+  if constexpr (C16) {
+    if (b < 0) {
+      const CSRT<MV, false> W{A.rowptr, A.col, nullptr, nullptr, A.val, A.rows, nullptr, nullptr};
+      row_dot_cols_block<C>(W, rs, re, 1 << ls, 0, x + c, kshift, sum);
+      wide = false;
+    }
+  }
+  if (wide) row_dot_cols_block<C>(A, rs, re, 1 << ls, b, x + c, kshift, sum);
+  for (int o = 1 << (gs + ls); (o >>= 1) >= 1 << gs;) {
+#pragma unroll
+    for (int q = 0; q < C; ++q) sum[q] = sum[q] + __shfl_down(sum[q], o, 64);
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int q = 0; q < C; ++q) epi(i0 + q, sum[q], pre[q]);
+  }
 }
 
 // Row-block kernel (K = 1, selected with tpr = 0): a workgroup takes one row
@@ -485,6 +533,34 @@ __global__ __launch_bounds__(64 * TPR) void spmv_lds_kernel(CSRT<MV, true> A,
   if (lane == 0 && live) epi(A.out_row(row), sum, pre);
 }
 
+static int log2_of(int K) {
+  int k = 0;
+  while ((1 << k) < K) ++k;
+  return k;
+}
+// A row of K columns takes the threads its one-column product would take, or
+// the groups its columns need if that is more, and further entry lanes where
+// the launch would have fewer than 400,000 threads and the row has 4 entries a
+// lane.  One thread a row and column walked the long rows of the coarse levels
+// serially; with lanes, a solve of 2 columns of FV 1000^2 (FP32) went from 19.9
+// to 5.0 ms, of 8 from 21.8 to 9.7 and of 32 from 44.5 to 28.5 (250 x 250:
+// 7.2, 6.2 and 7.2 to 1.8, 2.2 and 3.6); 100,000 threads 30.5 with 32 columns.
+template <class MV, bool C16, class X, class XI, class Epi>
+static void launch_spmm(const CSRT<MV, C16>& A, int64_t nnz, int K, const XI* x, Epi epi, int xcd,
+                        hipStream_t s) {
+  constexpr int W = (int)(16 / sizeof(XI));
+  const int ks = log2_of(K), C = K < W ? K : W, gs = ks - log2_of(C);
+  const double avg = (double)nnz / (double)A.rows;
+  const int base = pick_tpr(A.rows, nnz) & 0xff;
+  int ls = 0;
+  while (gs + ls < 6 && A.rows << (gs + ls + 1) <= (int64_t)INT32_MAX &&
+         ((A.rows << (gs + ls) < 400000 && avg >= 4 << ls) || 1 << (gs + ls) < base))
+    ++ls;
+  const unsigned nb = grid_for(A.rows, 256 >> (gs + ls), xcd);
+  if (C == 2) spmm_kernel<2, MV, C16, X, Epi, XI><<<nb, 256, 0, s>>>(A, x, epi, ks, gs, ls, xcd);
+  else if constexpr (W == 4) spmm_kernel<4, MV, C16, X, Epi, XI><<<nb, 256, 0, s>>>(A, x, epi, ks, gs, ls, xcd);
+}
+
 // shape: lanes per row in bits 0-7 (0: the row-block kernel), the XCD
 // mapping in bit 8, the LDS-staged kernel in bit 9, the entry-staged kernel in
 // bit 10
@@ -542,16 +618,8 @@ static void launch_spmv_t(const OpView& Av, int shape, int K, const XI* x, Epi e
       default: fail(AIRG_ERR_INTERNAL, "bad lanes-per-row");
     }
   } else {
-    unsigned nb = grid_for(Av.rows, 256 / K, xcd);
-    switch (K) {
-      case 2: spmm_kernel<2, MV, C16, X, Epi, XI><<<nb, 256, 0, s>>>(A, x, epi, xcd); break;
-      case 4: spmm_kernel<4, MV, C16, X, Epi, XI><<<nb, 256, 0, s>>>(A, x, epi, xcd); break;
-      case 8: spmm_kernel<8, MV, C16, X, Epi, XI><<<nb, 256, 0, s>>>(A, x, epi, xcd); break;
-      case 16: spmm_kernel<16, MV, C16, X, Epi, XI><<<nb, 256, 0, s>>>(A, x, epi, xcd); break;
-      case 32: spmm_kernel<32, MV, C16, X, Epi, XI><<<nb, 256, 0, s>>>(A, x, epi, xcd); break;
-      case 64: spmm_kernel<64, MV, C16, X, Epi, XI><<<nb, 256, 0, s>>>(A, x, epi, xcd); break;
-      default: fail(AIRG_ERR_INTERNAL, "column count must be a power of two <= 64");
-    }
+    if (K > 64 || (K & (K - 1)) != 0) fail(AIRG_ERR_INTERNAL, "column count must be a power of two <= 64");
+    launch_spmm<MV, C16, X>(A, Av.nnz, K, x, epi, xcd, s);
   }
   AIRG_CHECK_LAUNCH();
 }
@@ -814,12 +882,6 @@ struct EpiNeumannProlong {
     out[i] = p.e + (p.y + p.d * (p.s - t));
   }
 };
-
-static int log2_of(int K) {
-  int k = 0;
-  while ((1 << k) < K) ++k;
-  return k;
-}
 
 template <class X>
 void spmv_t(const OpView& A, int tpr, int K, const X* x, X* y, hipStream_t s) {

@@ -180,8 +180,28 @@ void load_csr(CSR& A, int64_t n, int64_t nnz, const int32_t* rowptr, const int32
   validate_csr(A, diag, s, true);
 }
 
+// How many of cnt columns to solve together.  The kernels take a power of two,
+// so the next one carries zero columns: on a large system each costs as much as
+// a real one.  Taking the largest power of two below and the rest by itself
+// adds a solve's fixed cost, which measured as 4 columns' time of a system of
+// 10^6 unknowns and 23 of one of 62,500 (both FP32): 4 + 1.2e6 / n.  20 columns
+// of FV 1000^2 (FP32): 28.6 ms as 32, 22.4 as 16 and 4; 9 of FV 500^2 5.5 as 16, and as 8 and 1
+// the fixed costs would add 2.0 to 3.6.
+int columns_together(int64_t n, int cnt) {
+  auto padded = [](int c) {
+    int k = 1;
+    while (k < c) k <<= 1;
+    return k;
+  };
+  const int whole = padded(cnt), part = whole / 2;
+  if (cnt < 2 || cnt == whole) return cnt;
+  const int saved = whole - (part + padded(cnt - part));
+  return (double)saved > 4.0 + 1.2e6 / (double)n ? part : cnt;
+}
+
 // Up to 64 columns are solved together as K interleaved columns, K the next
-// power of two (padding columns are zero), fewer when n K would pass 2^31.
+// power of two (padding columns are zero), fewer when n K would pass 2^31 or
+// the padding would cost more than another solve.
 int solve_columns(Hierarchy& H, Workspace& W, std::map<int, std::unique_ptr<Workspace>>& Wk,
                   int nrhs, const double* b, int64_t ldb, double* x, int64_t ldx, int guess,
                   airg_solve_info* info) {
@@ -195,7 +215,7 @@ int solve_columns(Hierarchy& H, Workspace& W, std::map<int, std::unique_ptr<Work
     // K interleaved columns, with n K elements addressable by one launch
     int kmax = 64;
     while (kmax > 1 && H.n0 * (int64_t)kmax > (int64_t)INT32_MAX) kmax >>= 1;
-    const int cnt = std::min(kmax, nrhs - k0);
+    const int cnt = columns_together(H.n0, std::min(kmax, nrhs - k0));
     int K = 1;
     while (K < cnt) K <<= 1;
     Workspace* ws = &W;

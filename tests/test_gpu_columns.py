@@ -30,3 +30,28 @@ def test_columns_match_one_column(nx, ny, nrhs, prec):
         x = s.solve(B[c])[0].cpu().numpy()
         assert np.abs(X[c] - x).max() <= 1e4 * u * np.abs(x).max()
     s.close()
+
+
+@pytest.mark.parametrize("nrhs", [5, 9, 20])
+@pytest.mark.parametrize("guess", [False, True])
+def test_columns_split_over_solves(nrhs, guess):
+    # large enough that 9 and 20 columns are solved as 8 + 1 and 16 + 4
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_17517_amd import Solver
+    p = workloads.fv_random(700, 0.6, True, ny=640)
+    s = Solver(p.indptr, p.indices, p.data)
+    rng = np.random.default_rng(nrhs)
+    B = torch.from_numpy(p.b[None, :] * rng.uniform(0.5, 1.5, (nrhs, 1))).cuda()
+    X0 = torch.zeros_like(B)
+    X0[::2] = 1.0
+    X, infos = s.solve(B, X0.clone(), guess=True) if guess else s.solve(B)
+    assert len(infos) == nrhs
+    A = p.scipy()
+    for c in range(nrhs):
+        x, info = s.solve(B[c], X0[c].clone(), guess=True) if guess else s.solve(B[c])
+        assert infos[c]["converged"] == 1 and infos[c]["iterations"] == info["iterations"]
+        b = B[c].cpu().numpy()
+        # the default tolerance, and the rounding of forming the residual here
+        assert np.linalg.norm(b - A @ X[c].cpu().numpy()) <= 1e-10 * (1 + 1e-3) * np.linalg.norm(b)
+    s.close()

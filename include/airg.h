@@ -347,7 +347,8 @@ enum airg_operator {
                        polynomial of A_ff formed as one matrix where that is cheaper */
   AIRG_OP_B = 1,    /* A_fc + A_ff W of a level (F-point residual) */
   AIRG_OP_Z = 2,    /* Z of a level (restriction) */
-  AIRG_OP_A = 3,    /* the coarsest matrix (Newton steps) */
+  AIRG_OP_A = 3,    /* the coarsest matrix (Newton steps), or its Newton polynomial formed
+                       as one matrix where the level is small */
   AIRG_OP_TOP = 4,  /* the top matrix of the outer loop (level 0) */
   AIRG_OP_HAT = 5   /* the assembled Ahat^{-1} of a level (AIRG_SMOOTH_ASSEMBLED) */
 };

@@ -365,6 +365,125 @@ int coarse_plan_error(const CoarsePlan& pc, hipStream_t s) {
   return e;
 }
 
+// ------------------------------------------------------------------ dense form
+// The Newton polynomial of a small coarsest matrix as one dense matrix: column
+// j is q(A) e_j by the steps of newton_apply_t in FP64.  Applying it is one
+// product where the steps are some 20, each of which on so small a matrix is a
+// launch and a round trip to memory and nothing else: FV 64^2 (733 rows, 17
+// entries a row) 20 x 3.0 us a cycle, 3.9 us in one product; its solve 1.01 and
+// 0.53 ms, its setup no longer than the runs differ.
+//
+// A workgroup forms 4 columns, with their three Newton vectors in LDS (96 KB
+// at the largest n), so that no vector leaves it and a step ends at a
+// workgroup barrier; the matrix comes from the caches.  4 lanes share a row,
+// add its entries and then take a column's update each.  1024 rows make 256
+// workgroups, one a CU: past that a second wave of workgroups and larger
+// vectors lengthen the setup faster than a solve gains.
+constexpr int kDenseRows = 1024;
+constexpr int kDenseCols = 4;
+
+__global__ __launch_bounds__(1024) void dense_newton_kernel(int n, const int32_t* __restrict__ rowptr,
+                                                            const int32_t* __restrict__ col,
+                                                            const double* __restrict__ val,
+                                                            const double2* __restrict__ roots, int m,
+                                                            double* __restrict__ q) {
+  extern __shared__ double dense_sh[];
+  double* w = dense_sh;
+  double* t = w + (int64_t)n * kDenseCols;
+  double* x = t + (int64_t)n * kDenseCols;
+  const int tid = threadIdx.x, lane = tid & 3;
+  const int j0 = blockIdx.x * kDenseCols;
+  for (int e = tid; e < n * kDenseCols; e += 1024) {
+    w[e] = (e >> 2) == j0 + (e & 3) ? 1.0 : 0.0;
+    x[e] = 0.0;
+  }
+  __syncthreads();
+  // f(e, (A v)_e) for every element e of the 4 columns
+  auto product = [&](const double* v, auto&& f) {
+    for (int r = tid >> 2; r < n; r += 256) {
+      double s[kDenseCols] = {0.0, 0.0, 0.0, 0.0};
+      const int e = rowptr[r + 1];
+      for (int p = rowptr[r] + lane; p < e; p += 4) {
+        const double a = val[p];
+        const double* vk = v + 4 * col[p];
+#pragma unroll
+        for (int c = 0; c < kDenseCols; ++c) s[c] = s[c] + a * vk[c];
+      }
+#pragma unroll
+      for (int c = 0; c < kDenseCols; ++c) {
+        s[c] = s[c] + __shfl_xor(s[c], 1, 4);
+        s[c] = s[c] + __shfl_xor(s[c], 2, 4);
+      }
+      f(4 * r + lane, lane == 0 ? s[0] : lane == 1 ? s[1] : lane == 2 ? s[2] : s[3]);
+    }
+    __syncthreads();
+  };
+  for (int i = 0; i < m;) {
+    const double a = roots[i].x, b = roots[i].y;
+    if (b == 0.0) {
+      const double inv = 1.0 / a;
+      if (i == m - 1) {  // last root: no product with A
+        for (int e = tid; e < n * kDenseCols; e += 1024) x[e] = x[e] + w[e] * inv;
+        __syncthreads();
+        break;
+      }
+      product(w, [&](int e, double s) {
+        x[e] = x[e] + w[e] * inv;
+        t[e] = w[e] - s * inv;
+      });
+      double* const u = w;
+      w = t;
+      t = u;
+      i += 1;
+    } else {
+      const double mod2 = a * a + b * b;
+      const double c1 = 2.0 * a / mod2, c2 = 1.0 / mod2;
+      product(w, [&](int e, double s) {
+        t[e] = s;
+        x[e] = x[e] + (c1 * w[e] - c2 * s);
+      });
+      if (i + 1 == m - 1) break;  // last pair
+      product(t, [&](int e, double s) { w[e] = w[e] - c1 * t[e] + c2 * s; });
+      i += 2;
+    }
+  }
+  for (int e = tid; e < n * kDenseCols; e += 1024)
+    if (j0 + (e & 3) < n) q[(int64_t)(e >> 2) * n + j0 + (e & 3)] = x[e];
+}
+
+__global__ void dense_pattern_kernel(int n, int32_t* rowptr, int32_t* col) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p < (int64_t)n * n) col[p] = (int32_t)(p % n);
+  if (p <= n) rowptr[p] = (int32_t)(p * n);
+}
+
+bool dense_newton(const CSR& A, const std::vector<cplx>& roots, CSR& Q, hipStream_t s) {
+  Q = CSR();
+  const int n = (int)A.rows, m = (int)roots.size();
+  // 3 products or more: one with the dense matrix takes as long as one or two
+  if (n < 1 || n > kDenseRows || m < 4) return false;
+  std::vector<double> h(2 * (size_t)m);
+  for (int i = 0; i < m; ++i) {
+    h[2 * i] = roots[i].real();
+    h[2 * i + 1] = roots[i].imag();
+  }
+  DBuf<double> d(h.size(), s);
+  d.from_host(h.data(), h.size());
+  const int64_t nnz = (int64_t)n * n;
+  Q.rows = Q.cols = n;
+  Q.nnz = nnz;
+  Q.rowptr.alloc(n + 1, s);
+  Q.col.alloc(nnz, s);
+  Q.val.alloc(nnz, s);
+  dense_pattern_kernel<<<blocks_for(nnz + 1, kBlock), kBlock, 0, s>>>(n, Q.rowptr.get(), Q.col.get());
+  AIRG_CHECK_LAUNCH();
+  const size_t lds = sizeof(double) * 3 * kDenseCols * (size_t)n;
+  dense_newton_kernel<<<(unsigned)((n + kDenseCols - 1) / kDenseCols), 1024, lds, s>>>(
+      n, A.rowptr.get(), A.col.get(), A.val.get(), (const double2*)d.get(), m, Q.val.get());
+  AIRG_CHECK_LAUNCH();
+  return true;
+}
+
 template void coarse_persistent_t<double>(const CoarsePlan&, const OpView&, const double*, double*,
                                           hipStream_t);
 template void coarse_persistent_t<float>(const CoarsePlan&, const OpView&, const float*, float*,

@@ -671,6 +671,12 @@ void finalize_hierarchy(Hierarchy& H) {
       exact_polynomial(L.Aff, L.alpha, value_bytes(H.p.precision),
                        H.p.precision == AIRG_FP64 ? 8.0 : 4.0, L.Aq, s);
   }
+  // a small coarsest level's Newton polynomial as one matrix; a batch's is
+  // block diagonal, and its steps skip the finished problems
+  if (np == 0 && !H.p.coarse_persistent) {
+    Level& Lc = H.levels.back();
+    dense_newton(Lc.A, Lc.roots, Lc.Aq, s);
+  }
   int64_t off = 0;
   for (Level& L : H.levels) {
     L.off = off;
@@ -734,6 +740,11 @@ void finalize_hierarchy(Hierarchy& H) {
     for (Level& L : H.levels) {
       if (L.coarsest) {
         lower(L.A, L.a32, L.a16);
+        // with BF16 storage too: the steps round A, not the polynomial
+        if (L.Aq.rows > 0) {
+          L.q32.alloc(L.Aq.nnz, s);
+          convert_d2f(L.q32.get(), L.Aq.val.get(), L.Aq.nnz, s);
+        }
         continue;
       }
       lower(L.Aff, L.ff32, L.ff16);
@@ -761,6 +772,7 @@ void finalize_hierarchy(Hierarchy& H) {
   for (Level& L : H.levels) {
     if (L.coarsest) {
       L.tpr_a = prepare(L.A, OpRole::Coarsest);
+      if (L.Aq.rows > 0) L.tpr_q = prepare(L.Aq);
       continue;
     }
     L.tpr_ff = prepare(L.Aff, OpRole::Smooth);
@@ -781,6 +793,7 @@ void finalize_hierarchy(Hierarchy& H) {
       const Level& L = H.levels[l];
       if (L.coarsest) {
         launch_check_csr(L.A, flags.get(), s);
+        if (L.Aq.rows > 0) launch_check_csr(L.Aq, flags.get(), s);
         continue;
       }
       launch_check_csr(L.Aff, flags.get(), s);
@@ -975,8 +988,10 @@ void hierarchy_stats(const Hierarchy& H, airg_stats* st) {
       const double spmvs = (double)L.roots.size() - 1.0;
       cyc += spmvs * (double)L.A.nnz;
       sto += (double)L.A.nnz;
-      // per product: the matrix, w gathered, wn written, x read and written
-      bytes += spmvs * (csr_bytes((double)L.n, (double)L.A.nnz) + 8.0 * 4 * L.n);
+      // per product: the matrix, w gathered, wn written, x read and written; or
+      // one product with the polynomial
+      bytes += L.Aq.rows > 0 ? csr_bytes((double)L.n, (double)L.Aq.nnz) + 8.0 * 2 * L.n
+                             : spmvs * (csr_bytes((double)L.n, (double)L.A.nnz) + 8.0 * 4 * L.n);
       st->coarse_roots = (int)L.roots.size();
     } else {
       const int d = (int)L.alpha.size() - 1;

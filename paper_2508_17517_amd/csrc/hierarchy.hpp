@@ -51,7 +51,9 @@ struct Level {
   CSR B;                    // A_fc + A_ff W: the F-point residual operator on e_c
   CSR Ahat;                 // assembled Ahat^{-1} (AIRG_SMOOTH_ASSEMBLED), A_ff's pattern
   CSR Aq;                   // q(A_ff) formed exactly, where one product with it costs less
-                            // than the Horner steps (exact_polynomial); else empty
+                            // than the Horner steps (exact_polynomial); on the coarsest level
+                            // its Newton polynomial, where that is small (dense_newton);
+                            // else empty
   DBuf<double> dinv;        // 1 / diag(A_ff) for the matrix-free Neumann smoother
   DBuf<float> dinv32;
   DBuf<int32_t> cmap;       // nested position on level l+1, or -1
@@ -142,6 +144,9 @@ template <class X>
 void coarse_persistent_t(const CoarsePlan& pc, const OpView& A, const X* r, X* x, hipStream_t s);
 // nonzero when a launch's barrier wait gave up (cleared by the call)
 int coarse_plan_error(const CoarsePlan& pc, hipStream_t s);
+// Q = the Newton polynomial of A as a dense matrix (every row stores every
+// column); false, and Q empty, where A is too large or the polynomial too short
+bool dense_newton(const CSR& A, const std::vector<cplx>& roots, CSR& Q, hipStream_t s);
 
 // Build the hierarchy for A (device CSR, validated) with parameters p.
 void build_hierarchy(Hierarchy& H, CSR&& A);

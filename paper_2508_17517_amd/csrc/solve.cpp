@@ -185,7 +185,8 @@ struct LevelOps {
 LevelOps ops_of(const Level& L, int prec) {
   return {op_view(L.Aff, L.ff32, L.ff16, prec), op_view(L.B, L.b32, L.b16, prec),
           op_view(L.Z, L.z32, L.z16, prec), op_view(L.A, L.a32, L.a16, prec),
-          op_view(L.Ahat, L.hat32, L.hat16, prec), op_view(L.Aq, L.q32, L.q16, prec)};
+          op_view(L.Ahat, L.hat32, L.hat16, prec),
+          op_view(L.Aq, L.q32, L.q16, L.coarsest && prec == AIRG_BF16 ? AIRG_FP32 : prec)};
 }
 // the view of A with the activity masks gm (null: unmasked)
 OpView masked(OpView v, const CSR& A, const uint8_t* gm) {
@@ -364,6 +365,21 @@ void smooth_c(const Hierarchy& H, const Level& L, const LevelOps& o, int K, cons
     horner_acc<X>(o.ff, L.tpr_ff, L.alpha, L.nF, K, v.sv, ef, v.y0, v.y1, s);
 }
 
+// The coarsest level: its Newton polynomial as one matrix where that is formed,
+// else step by step.
+template <class X>
+void coarse_solve(const Level& lc, const LevelOps& o, int K, const X* r, X* e, X* w0, X* w1, X* t,
+                  hipStream_t s, LaunchTally* tally = nullptr) {
+  if (lc.Aq.rows == 0) {
+    newton_apply_t<X>(o.a, lc.tpr_a, K, lc.roots, r, e, w0, w1, t, s, tally);
+    return;
+  }
+  spmv_t<X>(o.q, lc.tpr_q, K, r, e, s);
+  if (tally)
+    tally->add(csr_bytes(lc.n, o.q.nnz, vt_bytes(o.q.vt)) + (double)sizeof(X) * 2 * lc.n * K,
+               2.0 * (double)o.q.nnz * K, col_saving(o.q));
+}
+
 template <class X>
 void vcycle_t(const Hierarchy& H, const VecSet<X>& v, int K, hipStream_t s) {
   const int prec = H.p.precision;
@@ -386,8 +402,7 @@ void vcycle_t(const Hierarchy& H, const VecSet<X>& v, int K, hipStream_t s) {
   if (v.pc && K == 1)
     coarse_persistent_t<X>(*v.pc, ops_of(lc, prec, v.gmask).a, rc, v.e + lc.off, s);
   else
-    newton_apply_t<X>(ops_of(lc, prec, v.gmask).a, lc.tpr_a, K, lc.roots, rc, v.e + lc.off * K,
-                      v.cw0, v.cw1, v.ct, s);
+    coarse_solve<X>(lc, ops_of(lc, prec, v.gmask), K, rc, v.e + lc.off * K, v.cw0, v.cw1, v.ct, s);
   for (int l = L - 1; l >= 0; --l) {
     const Level& lv = H.levels[l];
     const LevelOps o = ops_of(lv, prec, v.gmask);
@@ -1138,8 +1153,7 @@ void time_pass(const Hierarchy& H, const VecSet<X>& v, int cls, LaunchTally* t) 
         t->add(csr_bytes(lc.n, lc.A.nnz, vb) + xb * lc.n * (2.0 + 2.0 * v.pc->nsteps),
                2.0 * lc.A.nnz * v.pc->nsteps + 6.0 * lc.n * v.pc->nsteps);
     } else {
-      newton_apply_t<X>(ops_of(lc, prec).a, lc.tpr_a, 1, lc.roots, v.rr + lc.off, v.e + lc.off,
-                        v.cw0, v.cw1, v.ct, s, t);
+      coarse_solve<X>(lc, ops_of(lc, prec), 1, v.rr + lc.off, v.e + lc.off, v.cw0, v.cw1, v.ct, s, t);
     }
   }
   if (cls == AIRG_K_RESIDUAL)
@@ -1259,7 +1273,8 @@ int autotune(Hierarchy& H, Workspace& W, int reps, std::vector<airg_tune_entry>&
     if (lv.Ahat.rows > 0) t.push_back({l, AIRG_OP_HAT, o.hat, &lv.tpr_hat, !low});
   }
   Level& lc = H.levels[L];
-  t.push_back({L, AIRG_OP_A, ops_of(lc, prec).a, &lc.tpr_a, !low});
+  if (lc.Aq.rows > 0) t.push_back({L, AIRG_OP_A, ops_of(lc, prec).q, &lc.tpr_q, !low});
+  else t.push_back({L, AIRG_OP_A, ops_of(lc, prec).a, &lc.tpr_a, !low});
   t.push_back({0, AIRG_OP_TOP, opview(H.Aperm), &H.tpr_top, true});
   double* x64 = W.V.get();
   launch_fill(x64, H.n0, 1.0, s);
@@ -1345,11 +1360,11 @@ void set_lanes(Hierarchy& H, int level, int op, int lanes, int xcd_map, int lds)
     fail(AIRG_ERR_INVALID, "this operator has no compressed columns for the LDS-staged product");
   const int shape = lanes | (xcd_map << 8);
   *tpr = shape | (lds == 1 ? kShapeLds : lds == 2 ? kShapeEntries : 0);
-  // a smoother that multiplies with q(A_ff) takes A_ff's shape too, with the x
-  // window in LDS only if that operator's columns are compressed, and in row
-  // blocks only if it has them
-  if (op == AIRG_OP_FF && H.levels[level].Aq.rows > 0) {
-    Level& lv = H.levels[level];
+  // a smoother that multiplies with q(A_ff) takes A_ff's shape too (the coarsest
+  // level's polynomial the coarsest matrix's), with the x window in LDS only if
+  // that operator's columns are compressed, and in row blocks only if it has them
+  Level& lv = H.levels[op == AIRG_OP_A ? L : op == AIRG_OP_FF ? level : 0];
+  if ((op == AIRG_OP_FF || op == AIRG_OP_A) && lv.Aq.rows > 0) {
     if (lanes == 0 && !lv.Aq.rblk.get()) return;
     lv.tpr_q = lds == 1 && !lv.Aq.col16.get() ? shape : *tpr;
   }

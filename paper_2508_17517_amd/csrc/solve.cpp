@@ -1022,10 +1022,7 @@ int fgmres_solve(const Hierarchy& H, Workspace& W, const double* b, int64_t ldb,
           spmv_t<double>(opview(H.Aperm), H.tpr_top, K, zj, W.w.get(), s);
         }
         if (j + 1 <= kFusedVecs) {
-          launch_cgs_dots(V, ld, j + 1, W.w.get(), n, hd, W.fused_work.get(), s);
-          launch_cgs_update_dots(W.w.get(), V, ld, hd, j + 1, n, hd + (R + 1), W.fused_work.get(), s);
-          launch_cgs_update_norm2(W.w.get(), V, ld, hd + (R + 1), j + 1, n, hd + 2 * (R + 1),
-                                  W.fused_work.get(), s);
+          launch_cgs2(W.w.get(), V, ld, j + 1, n, hd, hd + (R + 1), hd + 2 * (R + 1), W.fused_work.get(), s);
         } else {
           dots(V, ld, j + 1, W.w.get(), n, hd, W, s);
           launch_cgs_update(W.w.get(), V, ld, hd, j + 1, n, s);

@@ -671,9 +671,10 @@ int pick_shape(const CSR& A, OpRole role, int64_t xbytes) {
   const double avg = A.rows > 0 ? (double)A.nnz / (double)A.rows : 0.0;
   // The entry-staged kernel loads the entries of 256 rows at consecutive
   // addresses, so more gathers are in flight than one lane a row keeps; below
-  // 512 workgroups of it the device is not full and a row's entries in turn are
-  // the whole time (FV 64^2 level 1: 8.3 us, 2.8 with 4 lanes a row).
-  const bool entries = A.rows >= (int64_t)1 << 17;
+  // four workgroups of it a CU the device is not full and a row's entries in
+  // turn are the whole time (FV 64^2 level 1: 8.3 us, 2.8 with 4 lanes a row;
+  // 173,000 rows of 2 entries 3.8 and 3.1, 236,000 of 5 entries 6.1 and 5.2).
+  const bool entries = A.rows >= (int64_t)1 << 18;
   switch (role) {
     case OpRole::Restrict:
       // rows of about 3 entries that gather all over a level's F block (level 1
@@ -688,10 +689,12 @@ int pick_shape(const CSR& A, OpRole role, int64_t xbytes) {
       if (entries && avg > 1.2 && avg <= 5.5) return 1 | kShapeEntries | kShapeXcd;
       break;
     case OpRole::Top:
-      // 5 entries a row (DG 1024^2: 86.0 -> 82.4 us); past 8 M rows the vectors
-      // outgrow the caches and eighths of the rows only spread the traffic over
-      // more pages (FV 4096^2: 229 -> 212; with 4 M rows 36.2 and 37.0)
-      if (entries && ((avg > 3.5 && avg <= 8.0) || A.rows > (int64_t)8 << 20)) return 1 | kShapeEntries;
+      // a matrix beyond three quarters of the 256 MB cache streams from HBM: short
+      // rows then gain from consecutive addresses, and eighths of the rows only
+      // spread the traffic over more pages (250 MB, DG 1024^2: 86.0 -> 82.4 us;
+      // 604 MB, FV 4096^2: 229 -> 212; but 151 MB, FV 2048^2: 36.2 and 37.0, and
+      // 60 MB, 10^6 DG unknowns: 17.9 and 28.9)
+      if (avg <= 8.0 && 12.0 * (double)A.nnz > 192e6) return 1 | kShapeEntries;
       break;
     case OpRole::Coarsest:
       // ordered for narrow windows: x from LDS where the windows leave at least

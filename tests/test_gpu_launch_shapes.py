@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("nx,ny", [
     (3, 2),       # fewer rows than lanes
     (64, 64),     # short operators, up to 32 lanes a row
-    (511, 257),   # 2^17 rows and a little at the top, fewer on level 0
-    (601, 449),   # entry-staged products on level 0
+    (511, 257),   # 2^17 rows and a little at the top
+    (901, 749),   # entry-staged products on level 0
 ])
 @pytest.mark.parametrize("prec", [0, 1, 2])
 @pytest.mark.parametrize("dg", [False, True])

@@ -453,7 +453,10 @@ int airg_fv_gradients_noalloc(int64_t nx, int64_t ny, double theta, const int32_
  * the device were out of memory (the call that needed it returns that code
  * and releases what it had allocated).  bytes <= 0 removes the budget.
  * *in_use (may be NULL) receives the bytes the library's buffers hold now,
- * over every handle of the process. */
+ * over every handle of the process and with what a running setup keeps for its
+ * next buffers.  Without a budget a setup's blocks may be an eighth (at most 16
+ * MB) larger than their buffers twice over, and count at their own size; under
+ * a budget they are as large as their buffers. */
 int airg_set_alloc_budget(int64_t bytes, int64_t* in_use);
 
 /* Failure-handling hook (for tests): a grid-wide barrier wait of a

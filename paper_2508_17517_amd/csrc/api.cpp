@@ -1,5 +1,6 @@
 // C ABI of the AIRG library (declared in include/airg.h).  Every entry point
 // catches the library's exceptions and turns them into status codes.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -47,31 +48,30 @@ SetupPool::~SetupPool() {
   drop();
   if (page_) (void)hipHostFree(page_);
 }
-// eighths of a power of two: a request finds a block at most an eighth larger,
-// and repeated sizes that differ a little share blocks
-size_t SetupPool::rounded(size_t bytes) {
-  size_t p = 512;
-  while (p < bytes) p <<= 1;
-  const size_t step = p / 16;
-  return (bytes + step - 1) / step * step;
-}
 void* SetupPool::take(size_t bytes, size_t& cap) {
-  cap = rounded(bytes);
+  size_t p2 = 512;
+  while (p2 < bytes) p2 <<= 1;
+  const size_t step = std::min(p2 / 16, kSlack);  // eighths of a power of two
+  cap = (bytes + step - 1) / step * step;
   const auto it = free_.lower_bound(cap);
-  if (it == free_.end() || it->first > cap + cap / 8) return nullptr;
+  if (it == free_.end() || it->first > cap + std::min(cap / 8, kSlack)) return nullptr;
   void* p = it->second;
   cap = it->first;
   kept_ -= cap;
   free_.erase(it);
   return p;
 }
+static void free_block(void* p, size_t cap, hipStream_t s) {
+  (void)hipFreeAsync(p, s);
+  account_device_bytes(-(int64_t)cap);
+}
 bool SetupPool::give(void* p, size_t cap) {
-  if (cap > kKeep) return false;
+  if (cap > kKeep || g_device_budget > 0) return false;
   // the largest blocks make room
   while (kept_ + cap > kKeep) {
     const auto it = std::prev(free_.end());
     kept_ -= it->first;
-    (void)hipFreeAsync(it->second, s_);
+    free_block(it->second, it->first, s_);
     free_.erase(it);
   }
   try {
@@ -83,9 +83,37 @@ bool SetupPool::give(void* p, size_t cap) {
   return true;
 }
 void SetupPool::drop() {
-  for (const auto& b : free_) (void)hipFreeAsync(b.second, s_);
+  for (const auto& b : free_) free_block(b.second, b.first, s_);
   free_.clear();
   kept_ = 0;
+}
+
+void* take_block(size_t bytes, hipStream_t s, size_t& cap) {
+  cap = bytes;
+  SetupPool* pool = SetupPool::of(s);
+  if (pool && g_device_budget > 0) {
+    pool->drop();  // blocks kept before the budget was set
+    pool = nullptr;
+  }
+  void* p = pool ? pool->take(bytes, cap) : nullptr;
+  if (p) return p;
+  check_device_budget(cap);
+  hipError_t e = hipMallocAsync(&p, cap, s);
+  if (e == hipErrorOutOfMemory && pool) {
+    (void)hipGetLastError();
+    pool->drop();
+    AIRG_HIP(hipStreamSynchronize(s));
+    cap = bytes;
+    e = hipMallocAsync(&p, cap, s);
+  }
+  if (e != hipSuccess) (void)hipGetLastError();  // the next launch check is not about this
+  AIRG_HIP(e);
+  account_device_bytes((int64_t)cap);
+  return p;
+}
+void give_block(void* p, size_t cap, hipStream_t s) {
+  SetupPool* pool = SetupPool::of(s);
+  if (!pool || !pool->give(p, cap)) free_block(p, cap, s);
 }
 
 void read_back(void* dst, const void* dev, size_t bytes, hipStream_t s) {
@@ -325,11 +353,12 @@ int airg_setup(airg_handle* out, int64_t n, int64_t nnz, const int32_t* rowptr,
     std::unique_ptr<airg_ctx> c(new airg_ctx());
     c->H.p = prm;
     c->H.s = (hipStream_t)hip_stream;
-    SetupPool pool(c->H.s);
-    CSR A;
-    load_csr(A, n, nnz, rowptr, colidx, vals, on_device, c->H.s);
-    build_hierarchy(c->H, std::move(A));
-    pool.drop();  // the workspace is of other sizes
+    {
+      SetupPool pool(c->H.s);
+      CSR A;
+      load_csr(A, n, nnz, rowptr, colidx, vals, on_device, c->H.s);
+      build_hierarchy(c->H, std::move(A));
+    }  // the workspace, of other sizes, takes no kept block
     workspace_init(c->H, c->W);
     AIRG_HIP(hipStreamSynchronize(c->H.s));
     *out = c.release();
@@ -361,7 +390,7 @@ int airg_setup_batch(airg_handle* out, int nprob, const int64_t* n, const int64_
     c->H.p = prm;
     hipStream_t s = (hipStream_t)hip_stream;
     c->H.s = s;
-    SetupPool pool(s);
+    auto pool = std::make_unique<SetupPool>(s);
     int64_t N = 0, NZ = 0;
     std::vector<int64_t> seg(1, 0);
     for (int q = 0; q < nprob; ++q) {
@@ -389,7 +418,7 @@ int airg_setup_batch(airg_handle* out, int nprob, const int64_t* n, const int64_
     validate_csr(A, diag, s, true);
     c->H.seg = seg;
     build_hierarchy(c->H, std::move(A));
-    pool.drop();
+    pool.reset();
     workspace_init(c->H, c->W);
     AIRG_HIP(hipStreamSynchronize(s));
     *out = c.release();
@@ -430,14 +459,14 @@ int airg_adjoint_solve(airg_handle h, int nrhs, const double* w, int64_t ldw, do
     airg_ctx* c = handle_of(h);
     if (!c->H.seg.empty()) fail(AIRG_ERR_INVALID, "adjoint solves take a single-problem handle");
     if (!c->Ht) {
-      SetupPool pool(c->H.s);
+      auto pool = std::make_unique<SetupPool>(c->H.s);
       std::unique_ptr<Hierarchy> Ht(new Hierarchy());
       Ht->p = c->H.p;
       Ht->s = c->H.s;
       CSR At;
       transpose(c->H.A0, At, c->H.s);
       build_hierarchy(*Ht, std::move(At));
-      pool.drop();
+      pool.reset();
       std::unique_ptr<Workspace> Wt(new Workspace());
       workspace_init(*Ht, *Wt);
       c->Ht = std::move(Ht);
@@ -532,9 +561,10 @@ int airg_import_hierarchy(airg_handle* out, int nlevels, const airg_level_info* 
     std::unique_ptr<airg_ctx> c(new airg_ctx());
     c->H.p = prm;
     c->H.s = (hipStream_t)hip_stream;
-    SetupPool pool(c->H.s);
-    import_hierarchy(c->H, nlevels, infos, levels);
-    pool.drop();
+    {
+      SetupPool pool(c->H.s);
+      import_hierarchy(c->H, nlevels, infos, levels);
+    }
     workspace_init(c->H, c->W);
     AIRG_HIP(hipStreamSynchronize(c->H.s));
     *out = c.release();

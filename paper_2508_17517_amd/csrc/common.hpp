@@ -44,10 +44,16 @@ void set_device_budget(int64_t bytes);
 // a block released here serves the next request of about its size on the same
 // stream, whose order makes that safe.  (With the pinned page and row blocks
 // made on the device, setup and one solve at FV 2048^2 went from 370 to 267 ms,
-// the differentiable FV 512^2 from 181 to 128 ms, FV 64^2 from 25.6 to 16.3.)  At most kKeep bytes are kept, and all
-// of them go back when the setup ends or an allocation fails.  A scope belongs
-// to the thread that opened it; buffers released later, or by other threads,
-// or on other streams, go back to the allocator.
+// the differentiable FV 512^2 from 181 to 128 ms, FV 64^2 from 25.6 to 16.3.)
+// Blocks are asked for at rounded sizes, so that sizes that differ a little
+// share blocks, and a kept one may serve a smaller request: each by an eighth
+// of it and at most kSlack.  (Without both the setups above take 5 to 8% longer,
+// with neither for the arrays that stay with the handle 8 to 13%.)  At most
+// kKeep bytes are kept.  Blocks count as held at their own size, kept ones too,
+// and all kept ones go back when the setup ends or an allocation fails; under an
+// allocation budget nothing is rounded or kept, so that a setup needs what its
+// buffers need.  A scope belongs to the thread that opened it; buffers released
+// later, or by other threads, or on other streams, go back to the allocator.
 class SetupPool {
  public:
   explicit SetupPool(hipStream_t s);
@@ -56,15 +62,15 @@ class SetupPool {
   SetupPool& operator=(const SetupPool&) = delete;
   // the calling thread's scope for stream s, or null
   static SetupPool* of(hipStream_t s) { return cur_ && cur_->s_ == s ? cur_ : nullptr; }
-  void* take(size_t bytes, size_t& cap);    // null: nothing kept fits
+  // a kept block of cap >= bytes, or null and cap the size to ask for
+  void* take(size_t bytes, size_t& cap);
   bool give(void* p, size_t cap);           // false: not kept
   void drop();                              // everything kept goes back
-  static size_t rounded(size_t bytes);      // the size to ask the allocator for
   void* page() const { return page_; }      // kPage bytes of pinned host memory, or null
   static constexpr size_t kPage = 16384;
 
  private:
-  static constexpr size_t kKeep = (size_t)8 << 30;
+  static constexpr size_t kKeep = (size_t)8 << 30, kSlack = (size_t)16 << 20;
   static thread_local SetupPool* cur_;
   SetupPool* outer_;
   hipStream_t s_;
@@ -72,6 +78,12 @@ class SetupPool {
   size_t kept_ = 0;
   void* page_ = nullptr;
 };
+
+// A block of at least `bytes` of device memory on stream s, from the running
+// setup's blocks or the stream-ordered allocator, cap its size: checked against
+// the budget and counted as held until it goes back to the allocator.
+void* take_block(size_t bytes, hipStream_t s, size_t& cap);
+void give_block(void* p, size_t cap, hipStream_t s);
 
 // `bytes` of device memory on the host, waited for; small reads pass through
 // the setup's pinned page.
@@ -99,34 +111,11 @@ class DBuf {
   void alloc(size_t n, hipStream_t s) {
     release();
     s_ = s;
-    if (n) {
-      const size_t bytes = n * sizeof(T) + 256;
-      check_device_budget(bytes);
-      cap_ = bytes;
-      SetupPool* pool = SetupPool::of(s);
-      if (pool) p_ = (T*)pool->take(bytes, cap_);
-      if (!p_) {
-        hipError_t e = hipMallocAsync((void**)&p_, cap_, s);
-        if (e == hipErrorOutOfMemory && pool) {
-          (void)hipGetLastError();
-          pool->drop();
-          AIRG_HIP(hipStreamSynchronize(s));
-          cap_ = bytes;
-          e = hipMallocAsync((void**)&p_, cap_, s);
-        }
-        if (e != hipSuccess) p_ = nullptr;
-        AIRG_HIP(e);
-      }
-      account_device_bytes((int64_t)bytes);
-    }
+    if (n) p_ = (T*)take_block(n * sizeof(T) + 256, s, cap_);
     n_ = n;
   }
   void release() {
-    if (p_) {
-      SetupPool* pool = SetupPool::of(s_);
-      if (!pool || !pool->give(p_, cap_)) (void)hipFreeAsync(p_, s_);
-      account_device_bytes(-(int64_t)(n_ * sizeof(T) + 256));
-    }
+    if (p_) give_block(p_, cap_, s_);
     p_ = nullptr;
     n_ = 0;
   }

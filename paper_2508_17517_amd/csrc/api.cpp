@@ -208,6 +208,21 @@ void load_csr(CSR& A, int64_t n, int64_t nnz, const int32_t* rowptr, const int32
   validate_csr(A, diag, s, true);
 }
 
+// Runs f; where it finds no memory, once more after the handle's formed
+// polynomials (the solve works without them) have given theirs back.
+template <class F>
+void make_room(airg_ctx* c, F&& f) {
+  try {
+    return f();
+  } catch (const Error& e) {
+    if (e.code != AIRG_ERR_NOMEM) throw;
+    const bool some = drop_formed(c->H), more = c->Ht && drop_formed(*c->Ht);
+    if (!some && !more) throw;
+  }
+  AIRG_HIP(hipStreamSynchronize(c->H.s));  // the blocks are free when the stream is
+  f();
+}
+
 // How many of cnt columns to solve together.  The kernels take a power of two,
 // so the next one carries zero columns: on a large system each costs as much as
 // a real one.  Taking the largest power of two below and the rest by itself
@@ -230,7 +245,7 @@ int columns_together(int64_t n, int cnt) {
 // Up to 64 columns are solved together as K interleaved columns, K the next
 // power of two (padding columns are zero), fewer when n K would pass 2^31 or
 // the padding would cost more than another solve.
-int solve_columns(Hierarchy& H, Workspace& W, std::map<int, std::unique_ptr<Workspace>>& Wk,
+int solve_columns(airg_ctx* c, Hierarchy& H, Workspace& W, std::map<int, std::unique_ptr<Workspace>>& Wk,
                   int nrhs, const double* b, int64_t ldb, double* x, int64_t ldx, int guess,
                   airg_solve_info* info) {
   if (nrhs < 0) fail(AIRG_ERR_INVALID, "nrhs must be >= 0");
@@ -251,7 +266,7 @@ int solve_columns(Hierarchy& H, Workspace& W, std::map<int, std::unique_ptr<Work
       auto it = Wk.find(K);
       if (it == Wk.end()) {
         std::unique_ptr<Workspace> w(new Workspace());
-        workspace_init(H, *w, K);
+        make_room(c, [&]() { workspace_init(H, *w, K); });
         it = Wk.emplace(K, std::move(w)).first;
       }
       ws = it->second.get();
@@ -359,7 +374,7 @@ int airg_setup(airg_handle* out, int64_t n, int64_t nnz, const int32_t* rowptr,
       load_csr(A, n, nnz, rowptr, colidx, vals, on_device, c->H.s);
       build_hierarchy(c->H, std::move(A));
     }  // the workspace, of other sizes, takes no kept block
-    workspace_init(c->H, c->W);
+    make_room(c.get(), [&]() { workspace_init(c->H, c->W); });
     AIRG_HIP(hipStreamSynchronize(c->H.s));
     *out = c.release();
     return (int)AIRG_OK;
@@ -370,7 +385,7 @@ int airg_solve(airg_handle h, int nrhs, const double* b, int64_t ldb, double* x,
                int use_x_as_guess, airg_solve_info* info) {
   return guard([&]() {
     airg_ctx* c = handle_of(h);
-    return solve_columns(c->H, c->W, c->Wk, nrhs, b, ldb, x, ldx, use_x_as_guess, info);
+    return solve_columns(c, c->H, c->W, c->Wk, nrhs, b, ldb, x, ldx, use_x_as_guess, info);
   });
 }
 
@@ -419,7 +434,7 @@ int airg_setup_batch(airg_handle* out, int nprob, const int64_t* n, const int64_
     c->H.seg = seg;
     build_hierarchy(c->H, std::move(A));
     pool.reset();
-    workspace_init(c->H, c->W);
+    make_room(c.get(), [&]() { workspace_init(c->H, c->W); });
     AIRG_HIP(hipStreamSynchronize(s));
     *out = c.release();
     return (int)AIRG_OK;
@@ -435,7 +450,11 @@ int airg_solve_batch(airg_handle h, const double* const* b, double* const* x,
     if (!b || !x) fail(AIRG_ERR_INVALID, "null pointer array");
     hipStream_t s = c->H.s;
     const int np = (int)seg.size() - 1;
-    DBuf<double> bc(c->H.n0, s), xc(c->H.n0, s);
+    DBuf<double> bc, xc;
+    make_room(c, [&]() {
+      bc.alloc(c->H.n0, s);
+      xc.alloc(c->H.n0, s);
+    });
     for (int q = 0; q < np; ++q) {
       if (!b[q] || !x[q]) fail(AIRG_ERR_INVALID, "null vector pointer");
       const size_t bytes = (seg[q + 1] - seg[q]) * sizeof(double);
@@ -459,20 +478,27 @@ int airg_adjoint_solve(airg_handle h, int nrhs, const double* w, int64_t ldw, do
     airg_ctx* c = handle_of(h);
     if (!c->H.seg.empty()) fail(AIRG_ERR_INVALID, "adjoint solves take a single-problem handle");
     if (!c->Ht) {
-      auto pool = std::make_unique<SetupPool>(c->H.s);
-      std::unique_ptr<Hierarchy> Ht(new Hierarchy());
-      Ht->p = c->H.p;
-      Ht->s = c->H.s;
-      CSR At;
-      transpose(c->H.A0, At, c->H.s);
-      build_hierarchy(*Ht, std::move(At));
-      pool.reset();
+      std::unique_ptr<Hierarchy> Ht;
+      make_room(c, [&]() {
+        SetupPool pool(c->H.s);
+        Ht.reset(new Hierarchy());
+        Ht->p = c->H.p;
+        Ht->s = c->H.s;
+        CSR At;
+        transpose(c->H.A0, At, c->H.s);
+        build_hierarchy(*Ht, std::move(At));
+      });
       std::unique_ptr<Workspace> Wt(new Workspace());
-      workspace_init(*Ht, *Wt);
       c->Ht = std::move(Ht);
+      try {
+        make_room(c, [&]() { workspace_init(*c->Ht, *Wt); });
+      } catch (...) {
+        c->Ht.reset();
+        throw;
+      }
       c->Wt = std::move(Wt);
     }
-    return solve_columns(*c->Ht, *c->Wt, c->Wtk, nrhs, w, ldw, lam, ldl, use_guess, info);
+    return solve_columns(c, *c->Ht, *c->Wt, c->Wtk, nrhs, w, ldw, lam, ldl, use_guess, info);
   });
 }
 
@@ -565,7 +591,7 @@ int airg_import_hierarchy(airg_handle* out, int nlevels, const airg_level_info* 
       SetupPool pool(c->H.s);
       import_hierarchy(c->H, nlevels, infos, levels);
     }
-    workspace_init(c->H, c->W);
+    make_room(c.get(), [&]() { workspace_init(c->H, c->W); });
     AIRG_HIP(hipStreamSynchronize(c->H.s));
     *out = c.release();
     return (int)AIRG_OK;

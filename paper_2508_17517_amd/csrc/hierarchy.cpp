@@ -665,17 +665,6 @@ void finalize_hierarchy(Hierarchy& H) {
         permute_rows(hc, N.pos.get(), N.pos.get(), L.nC, L.hat_cc.m, s, true);
       }
     }
-    // the GMRES polynomial as one matrix where that is cheaper; a second F
-    // smooth (FCF) keeps the matrix-free form for both
-    if (!asm_smoother && !neumann && H.p.smooth_type != AIRG_SMOOTH_TYPE_FCF)
-      exact_polynomial(L.Aff, L.alpha, value_bytes(H.p.precision),
-                       H.p.precision == AIRG_FP64 ? 8.0 : 4.0, L.Aq, s);
-  }
-  // a small coarsest level's Newton polynomial as one matrix; a batch's is
-  // block diagonal, and its steps skip the finished problems
-  if (np == 0 && !H.p.coarse_persistent) {
-    Level& Lc = H.levels.back();
-    dense_newton(Lc.A, Lc.roots, Lc.Aq, s);
   }
   int64_t off = 0;
   for (Level& L : H.levels) {
@@ -726,34 +715,28 @@ void finalize_hierarchy(Hierarchy& H) {
     }
   }
   // value copies in the storage precision of the mixed-precision V-cycle
+  auto lower = [&](const CSR& A, DBuf<float>& v32, DBuf<bf16>& v16, bool bf) {
+    if (bf) {
+      v16.alloc(A.nnz, s);
+      convert_d2bf(v16.get(), A.val.get(), A.nnz, s);
+    } else {
+      v32.alloc(A.nnz, s);
+      convert_d2f(v32.get(), A.val.get(), A.nnz, s);
+    }
+  };
+  const bool bf = H.p.precision == AIRG_BF16;
   if (H.p.precision != AIRG_FP64) {
-    const bool bf = H.p.precision == AIRG_BF16;
-    auto lower = [&](const CSR& A, DBuf<float>& v32, DBuf<bf16>& v16) {
-      if (bf) {
-        v16.alloc(A.nnz, s);
-        convert_d2bf(v16.get(), A.val.get(), A.nnz, s);
-      } else {
-        v32.alloc(A.nnz, s);
-        convert_d2f(v32.get(), A.val.get(), A.nnz, s);
-      }
-    };
     for (Level& L : H.levels) {
       if (L.coarsest) {
-        lower(L.A, L.a32, L.a16);
-        // with BF16 storage too: the steps round A, not the polynomial
-        if (L.Aq.rows > 0) {
-          L.q32.alloc(L.Aq.nnz, s);
-          convert_d2f(L.q32.get(), L.Aq.val.get(), L.Aq.nnz, s);
-        }
+        lower(L.A, L.a32, L.a16, bf);
         continue;
       }
-      lower(L.Aff, L.ff32, L.ff16);
-      lower(L.B, L.b32, L.b16);
-      lower(L.Z, L.z32, L.z16);
-      if (L.Ahat.rows > 0) lower(L.Ahat, L.hat32, L.hat16);
-      if (L.Aq.rows > 0) lower(L.Aq, L.q32, L.q16);
+      lower(L.Aff, L.ff32, L.ff16, bf);
+      lower(L.B, L.b32, L.b16, bf);
+      lower(L.Z, L.z32, L.z16, bf);
+      if (L.Ahat.rows > 0) lower(L.Ahat, L.hat32, L.hat16, bf);
       for (SolveOp* o : {&L.cf, &L.cc, &L.hat_cc, &L.fc})
-        if (o->m.rows > 0) lower(o->m, o->v32, o->v16);
+        if (o->m.rows > 0) lower(o->m, o->v32, o->v16, bf);
       if (L.dinv.get()) {
         L.dinv32.alloc(L.nF, s);
         convert_d2f(L.dinv32.get(), L.dinv.get(), L.nF, s);
@@ -772,16 +755,36 @@ void finalize_hierarchy(Hierarchy& H) {
   for (Level& L : H.levels) {
     if (L.coarsest) {
       L.tpr_a = prepare(L.A, OpRole::Coarsest);
-      if (L.Aq.rows > 0) L.tpr_q = prepare(L.Aq);
       continue;
     }
     L.tpr_ff = prepare(L.Aff, OpRole::Smooth);
     L.tpr_b = prepare(L.B);
     L.tpr_z = prepare(L.Z, OpRole::Restrict);
     if (L.Ahat.rows > 0) L.tpr_hat = prepare(L.Ahat);
-    if (L.Aq.rows > 0) L.tpr_q = prepare(L.Aq, OpRole::Smooth);
     for (SolveOp* o : {&L.cf, &L.cc, &L.hat_cc, &L.fc})
       if (o->m.rows > 0) o->tpr = prepare(o->m);
+  }
+  // The polynomials as one matrix where that is cheaper (a second F smooth, FCF,
+  // keeps the matrix-free form for both; a batch's coarsest level is block
+  // diagonal, and its steps skip the finished problems).  They come last, from
+  // the memory that the rest leaves: where it runs out, the steps remain.
+  const bool form_q = H.p.smoother == AIRG_SMOOTH_POLY && H.p.inverse_type == AIRG_INVERSE_ARNOLDI &&
+                      H.p.smooth_type != AIRG_SMOOTH_TYPE_FCF;
+  const bool form_coarsest = np == 0 && !H.p.coarse_persistent;
+  for (Level& L : H.levels) {
+    try {
+      if (L.coarsest ? !form_coarsest || !dense_newton(L.A, L.roots, L.Aq, s)
+                     : !form_q || !exact_polynomial(L.Aff, L.alpha, value_bytes(H.p.precision), (double)xbytes,
+                                                    L.Aq, s))
+        continue;
+      // the coarsest polynomial in FP32 with BF16 storage too: the steps round A,
+      // not the polynomial
+      if (H.p.precision != AIRG_FP64) lower(L.Aq, L.q32, L.q16, bf && !L.coarsest);
+      L.tpr_q = prepare(L.Aq, L.coarsest ? OpRole::Plain : OpRole::Smooth);
+    } catch (const Error& e) {
+      if (e.code != AIRG_ERR_NOMEM) throw;
+      L.drop_formed();
+    }
   }
   // every solve-phase operator is checked once, so an inconsistent hierarchy
   // (for example a bad import) fails here instead of in a kernel
@@ -963,6 +966,13 @@ void import_hierarchy(Hierarchy& H, int nlevels, const airg_level_info* infos,
       fail(AIRG_ERR_INVALID, "coarsest matrix: index out of range");
   }
   finalize_hierarchy(H);
+}
+
+bool drop_formed(Hierarchy& H) {
+  bool any = false;
+  for (Level& L : H.levels) any = L.drop_formed() || any;
+  if (any) ++H.shape_epoch;  // captured V-cycles hold the matrices' addresses
+  return any;
 }
 
 void hierarchy_stats(const Hierarchy& H, airg_stats* st) {

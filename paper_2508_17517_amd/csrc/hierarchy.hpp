@@ -78,6 +78,15 @@ struct Level {
   DBuf<float> ff32, b32, z32, a32, hat32, q32;
   DBuf<bf16> ff16, b16, z16, a16, hat16, q16;
 
+  // back to the polynomial's steps; false where it was not formed
+  bool drop_formed() {
+    const bool any = Aq.rows > 0;
+    Aq = CSR();
+    q32.release();
+    q16.release();
+    return any;
+  }
+
   // statistics
   int64_t nnz_a = 0, nnz_fc = 0;
   int pmisr_rounds = 0;
@@ -152,6 +161,9 @@ bool dense_newton(const CSR& A, const std::vector<cplx>& roots, CSR& Q, hipStrea
 void build_hierarchy(Hierarchy& H, CSR&& A);
 // Nested numbering and solve-form operators; frees setup data unless kept.
 void finalize_hierarchy(Hierarchy& H);
+// Gives the formed polynomials of every level back (an allocation that fails may
+// then fit); false where there are none.
+bool drop_formed(Hierarchy& H);
 // Build from host arrays in setup numbering (see airg_import_hierarchy).
 void import_hierarchy(Hierarchy& H, int nlevels, const airg_level_info* infos,
                       const airg_level_arrays* arr);

@@ -420,6 +420,9 @@ double stream_probe(int kind, const void* src, void* dst, int64_t bytes, int rep
 
 // ---------------------------------------------------------------- spgemm.hip
 // C = A B with c_ij accumulated over k ascending from 0.0, exact zeros dropped.
+// False, and C empty, where C would have more than max_nnz entries (exact zeros
+// counted); known before C's arrays are made.
+bool spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s, int64_t max_nnz);
 void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s);
 // Masked powers and the fixed-sparsity inverse on the pattern of Aff:
 //   out = alpha_0 I + alpha_1 A + alpha_2 A~^2 + ..., zeros dropped.

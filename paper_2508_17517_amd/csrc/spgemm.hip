@@ -25,21 +25,26 @@ struct RowStat {
   int32_t value(int k) const { return (int32_t)h[1 + k]; }
 };
 
-// Row pointers (int32) from row lengths; returns their total, failing where it
-// does not fit, and leaves st's words on the host.
-static int64_t counts_to_rowptr(const DBuf<int32_t>& cnt, int64_t n, DBuf<int32_t>& rowptr, RowStat& st,
-                                hipStream_t s) {
+// Row pointers (int32) from row lengths; returns their total (the pointers are
+// of use up to 2^31 - 1) and leaves st's words on the host.
+constexpr int64_t kMaxNnz = 2147483647;
+static int64_t count_rows(const DBuf<int32_t>& cnt, int64_t n, DBuf<int32_t>& rowptr, RowStat& st,
+                          hipStream_t s) {
   rowptr.alloc(n + 1, s);
   DBuf<int64_t> work(rowptr_work_size(n), s);
   launch_rowptr_scan(cnt.get(), n, rowptr.get(), st.d.get(), work.get(), s);
   read_back(st.h, st.d.get(), sizeof(st.h), s);
-  if (st.h[0] > 2147483647ll) fail(AIRG_ERR_NOMEM, "sparse matrix exceeds 2^31 nonzeros");
   return st.h[0];
+}
+static void check_nnz(int64_t nnz) {
+  if (nnz > kMaxNnz) fail(AIRG_ERR_NOMEM, "sparse matrix exceeds 2^31 nonzeros");
 }
 static int64_t counts_to_rowptr(const DBuf<int32_t>& cnt, int64_t n, DBuf<int32_t>& rowptr,
                                 hipStream_t s) {
   RowStat st(s);
-  return counts_to_rowptr(cnt, n, rowptr, st, s);
+  const int64_t nnz = count_rows(cnt, n, rowptr, st, s);
+  check_nnz(nnz);
+  return nnz;
 }
 
 // ------------------------------------------------------------------ exact zeros
@@ -533,6 +538,10 @@ __global__ __launch_bounds__(64) void window_product_kernel(CSRView A, CSRView B
 }
 
 void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s) {
+  if (!spgemm(A, B, C, s, kMaxNnz)) check_nnz(kMaxNnz + 1);
+}
+bool spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s, int64_t max_nnz) {
+  C = CSR();
   if (A.cols != B.rows) fail(AIRG_ERR_INTERNAL, "spgemm shape mismatch");
   const int64_t n = A.rows;
   CSR full;
@@ -542,7 +551,7 @@ void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s) {
     full.rowptr.alloc(std::max<int64_t>(n, 0) + 1, s);
     launch_fill_i32(full.rowptr.get(), std::max<int64_t>(n, 0) + 1, 0, s);
     C = std::move(full);
-    return;
+    return true;
   }
   const double la = (double)A.nnz / (double)n, lb = (double)B.nnz / (double)B.rows;
   // lanes: a row of B per step.  First table: room for six rows of C that see
@@ -557,7 +566,7 @@ void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s) {
     T = std::max(T, 2 * G);
     RowStat st(s);
     launch_hash_product<false>(A, B, G, T, nullptr, nullptr, nullptr, cnt.get(), st, s);
-    full.nnz = counts_to_rowptr(cnt, n, full.rowptr, st, s);  // of use unless a row overflowed
+    full.nnz = count_rows(cnt, n, full.rowptr, st, s);  // of use unless a row overflowed
     if (!st.value(0)) {
       T = std::min(kHashMax, std::max(2 * G, pow2_at_least(1.5 * st.value(1) + G)));
       break;
@@ -572,7 +581,8 @@ void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s) {
       window_product_kernel<false><<<nlist, 64, 0, s>>>(view(A), view(B), B.cols, list.get(), nullptr,
                                                         nullptr, nullptr, cnt.get(), nullptr);
       AIRG_CHECK_LAUNCH();
-      full.nnz = counts_to_rowptr(cnt, n, full.rowptr, s);
+      RowStat all(s);
+      full.nnz = count_rows(cnt, n, full.rowptr, all, s);
       break;  // the second pass with the same G and T leaves the same rows
     }
     T = std::min(kHashMax, 4 * T);
@@ -581,6 +591,7 @@ void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s) {
     while (G < 64 && T / G > 32) G <<= 1;
     T = std::max(T, 2 * G);
   }
+  if (full.nnz > std::min(max_nnz, kMaxNnz)) return false;
   full.col.alloc(full.nnz, s);
   full.val.alloc(full.nnz, s);
   RowStat st(s);
@@ -594,6 +605,7 @@ void spgemm(const CSR& A, const CSR& B, CSR& C, hipStream_t s) {
   read_back(st.h, st.d.get(), sizeof(st.h), s);
   if (st.value(2)) drop_zeros(full, C, s);
   else C = std::move(full);
+  return true;
 }
 
 // A P for the one-point P given by pmap (pmap[j]: the coarse column of node j,
@@ -929,8 +941,7 @@ bool exact_polynomial(const CSR& A, const std::vector<double>& alpha, double vby
   add_diag(P, alpha[d - 1]);
   for (int k = d - 2; k >= 0; --k) {
     CSR T;
-    spgemm(A, P, T, s);
-    if ((double)T.nnz > max_nnz || (k > 0 && hopeless((double)T.nnz, (double)T.nnz / (double)P.nnz, k)))
+    if (!spgemm(A, P, T, s, (int64_t)max_nnz) || (k > 0 && hopeless((double)T.nnz, (double)T.nnz / (double)P.nnz, k)))
       return false;
     add_diag(T, alpha[k]);
     P = std::move(T);

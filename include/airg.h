@@ -395,7 +395,11 @@ int airg_autotune(airg_handle h, int reps, airg_tune_entry* out, int max_out, in
  * and AIRG_OP_A).  AIRG_ERR_INVALID for an unknown operator, lanes not 0 or a
  * power of two in 1..64, 0 for an operator without row blocks, xcd_map not 0
  * or 1, lds not 0, 1 or 2, lds = 1 with lanes outside 2..16 or for an operator
- * without compressed columns, or lds = 2 with lanes other than 1. */
+ * without compressed columns, or lds = 2 with lanes other than 1.  Where a
+ * polynomial is formed as one matrix (AIRG_OP_FF, AIRG_OP_A), the entry sets the
+ * shape of that matrix and of the one it was formed from, and is valid if either
+ * has the row blocks or compressed columns it asks for; the other then takes the
+ * lanes without staging, or keeps its shape where lanes is 0. */
 int airg_set_lanes(airg_handle h, int level, int op, int lanes, int xcd_map, int lds);
 
 /* ---- differentiable advection solve -------------------------------------

@@ -1326,7 +1326,6 @@ void set_lanes(Hierarchy& H, int level, int op, int lanes, int xcd_map, int lds)
     fail(AIRG_ERR_INVALID, "the LDS-staged product takes 2, 4, 8 or 16 lanes per row");
   if (lds == 2 && lanes != 1)
     fail(AIRG_ERR_INVALID, "the entry-staged product takes one lane per row");
-  ++H.shape_epoch;
   const int L = (int)H.levels.size() - 1;
   const CSR* A = nullptr;
   int* tpr = nullptr;
@@ -1351,20 +1350,24 @@ void set_lanes(Hierarchy& H, int level, int op, int lanes, int xcd_map, int lds)
       default: fail(AIRG_ERR_INVALID, "unknown operator");
     }
   }
-  if (lanes == 0 && !A->rblk.get())
+  // a polynomial formed as one matrix is what the level multiplies with (and what
+  // the tuner times): the entry is for it, and for the matrix of the steps too
+  Level* lv = op == AIRG_OP_A ? &H.levels[L] : op == AIRG_OP_FF ? &H.levels[level] : nullptr;
+  CSR* Aq = lv && lv->Aq.rows > 0 ? &lv->Aq : nullptr;
+  auto blocks = [&](const CSR* M) { return M && M->rblk.get(); };
+  auto windows = [&](const CSR* M) { return M && M->col16.get(); };
+  if (lanes == 0 && !blocks(A) && !blocks(Aq))
     fail(AIRG_ERR_INVALID, "this operator has no row blocks (rows shorter than 8 on average)");
-  if (lds == 1 && !A->col16.get())
+  if (lds == 1 && !windows(A) && !windows(Aq))
     fail(AIRG_ERR_INVALID, "this operator has no compressed columns for the LDS-staged product");
-  const int shape = lanes | (xcd_map << 8);
-  *tpr = shape | (lds == 1 ? kShapeLds : lds == 2 ? kShapeEntries : 0);
-  // a smoother that multiplies with q(A_ff) takes A_ff's shape too (the coarsest
-  // level's polynomial the coarsest matrix's), with the x window in LDS only if
-  // that operator's columns are compressed, and in row blocks only if it has them
-  Level& lv = H.levels[op == AIRG_OP_A ? L : op == AIRG_OP_FF ? level : 0];
-  if ((op == AIRG_OP_FF || op == AIRG_OP_A) && lv.Aq.rows > 0) {
-    if (lanes == 0 && !lv.Aq.rblk.get()) return;
-    lv.tpr_q = lds == 1 && !lv.Aq.col16.get() ? shape : *tpr;
-  }
+  const int plain = lanes | (xcd_map << 8);
+  const int shape = plain | (lds == 1 ? kShapeLds : lds == 2 ? kShapeEntries : 0);
+  auto set = [&](const CSR* M, int& of) {
+    if (lanes > 0 || blocks(M)) of = lds == 1 && !windows(M) ? plain : shape;
+  };
+  set(A, *tpr);
+  if (Aq) set(Aq, lv->tpr_q);
+  ++H.shape_epoch;
 }
 
 }  // namespace airg

@@ -206,4 +206,6 @@ def load_host_dense():
     lib.airg_host_newton_roots.restype = ip
     lib.airg_host_numerical_rank.argtypes = [dp, ip, ip, c_dbl]
     lib.airg_host_numerical_rank.restype = ip
+    lib.airg_host_default_shape.argtypes = [ip, c_i64, c_i64, ip, ip, ip, c_i64]
+    lib.airg_host_default_shape.restype = ip
     return lib

@@ -1,10 +1,11 @@
-// Host-only C entry points over the dense routines, for CPU tests of the
-// library's least-squares and eigenvalue code (not part of the public ABI).
+// Host-only C entry points over the dense routines and the launch-shape rule,
+// for CPU tests (not part of the public ABI).
 #include <cstring>
 #include <vector>
 
 #include "dense.hpp"
 #include "error.hpp"
+#include "shapes.hpp"
 
 using namespace airg;
 
@@ -60,6 +61,12 @@ int airg_host_numerical_rank(const double* H, int ld, int k, double tol) {
   } catch (...) {
     return -1;
   }
+}
+
+// The default launch shape of an operator (role as in OpRole).
+int airg_host_default_shape(int role, int64_t rows, int64_t nnz, int vbytes, int xbytes, int windows,
+                            int64_t max_span) {
+  return default_shape({rows, nnz, vbytes, xbytes, windows != 0, max_span}, (OpRole)role);
 }
 
 }  // extern "C"

@@ -745,24 +745,24 @@ void finalize_hierarchy(Hierarchy& H) {
   }
   // compressed columns for every solve operator whose row blocks allow them,
   // row blocks for the operators with long rows, and the default launch shapes
-  const int64_t xbytes = H.p.precision == AIRG_FP64 ? 8 : 4;
-  auto prepare = [&](CSR& A, OpRole role = OpRole::Plain) {
+  const int xbytes = H.p.precision == AIRG_FP64 ? 8 : 4, vbytes = (int)value_bytes(H.p.precision);
+  auto prepare = [&](CSR& A, OpRole role, int value) {
     compress_columns(A, s);
     if (A.rows > 0 && A.nnz >= 8 * A.rows) build_row_blocks(A, s);
-    return pick_shape(A, role, xbytes);
+    return pick_shape(A, role, value, xbytes);
   };
-  H.tpr_top = prepare(H.Aperm, OpRole::Top);
+  H.tpr_top = prepare(H.Aperm, OpRole::Top, 8);
   for (Level& L : H.levels) {
     if (L.coarsest) {
-      L.tpr_a = prepare(L.A, OpRole::Coarsest);
+      L.tpr_a = prepare(L.A, OpRole::Coarsest, vbytes);
       continue;
     }
-    L.tpr_ff = prepare(L.Aff, OpRole::Smooth);
-    L.tpr_b = prepare(L.B);
-    L.tpr_z = prepare(L.Z, OpRole::Restrict);
-    if (L.Ahat.rows > 0) L.tpr_hat = prepare(L.Ahat);
+    L.tpr_ff = prepare(L.Aff, OpRole::Smooth, vbytes);
+    L.tpr_b = prepare(L.B, OpRole::Plain, vbytes);
+    L.tpr_z = prepare(L.Z, OpRole::Restrict, vbytes);
+    if (L.Ahat.rows > 0) L.tpr_hat = prepare(L.Ahat, OpRole::Plain, vbytes);
     for (SolveOp* o : {&L.cf, &L.cc, &L.hat_cc, &L.fc})
-      if (o->m.rows > 0) o->tpr = prepare(o->m);
+      if (o->m.rows > 0) o->tpr = prepare(o->m, OpRole::CPoint, vbytes);
   }
   // The polynomials as one matrix where that is cheaper (a second F smooth, FCF,
   // keeps the matrix-free form for both; a batch's coarsest level is block
@@ -780,7 +780,7 @@ void finalize_hierarchy(Hierarchy& H) {
       // the coarsest polynomial in FP32 with BF16 storage too: the steps round A,
       // not the polynomial
       if (H.p.precision != AIRG_FP64) lower(L.Aq, L.q32, L.q16, bf && !L.coarsest);
-      L.tpr_q = prepare(L.Aq, L.coarsest ? OpRole::Plain : OpRole::Smooth);
+      L.tpr_q = prepare(L.Aq, L.coarsest ? OpRole::Plain : OpRole::Smooth, L.coarsest ? xbytes : vbytes);
     } catch (const Error& e) {
       if (e.code != AIRG_ERR_NOMEM) throw;
       L.drop_formed();

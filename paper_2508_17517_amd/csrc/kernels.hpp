@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "shapes.hpp"
 
 namespace airg {
 
@@ -185,18 +186,11 @@ void launch_arnoldi_update_norm2(const double* V, int64_t ldv, int nv, const dou
                                  double* out, double* work, hipStream_t s);
 
 // ---------------------------------------------------------------- spmv.hip
-// Default launch shapes: of any product, and of a solve operator by its role and
-// its (compressed) columns for vectors of xbytes an element.
+// The default launch shapes (shapes.hpp) of a product with FP64 values and plain
+// columns, and of a solve operator by its role, for values and vector elements
+// of vbytes and xbytes.
 int pick_tpr(int64_t rows, int64_t nnz);
-enum class OpRole { Plain, Restrict, Smooth, Top, Coarsest };
-int pick_shape(const CSR& A, OpRole role, int64_t xbytes);
-// Launch shape of a product: lanes per row in bits 0-7 (0: row-block kernel),
-// the XCD mapping in bit 8, the LDS-staged kernel in bit 9, the
-// entry-staged kernel (256 consecutive rows per workgroup, one lane per row)
-// in bit 10.
-constexpr int kShapeXcd = 1 << 8;
-constexpr int kShapeLds = 1 << 9;
-constexpr int kShapeEntries = 1 << 10;
+int pick_shape(const CSR& A, OpRole role, int vbytes, int xbytes);
 // y = A x, every row summed left to right from 0.0 by one lane (setup order).
 void spmv_seq(const CSR& A, const double* x, double* y, hipStream_t s);
 // y = A x with `tpr` lanes per row.

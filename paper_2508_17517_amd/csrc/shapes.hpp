@@ -1,0 +1,122 @@
+// Launch shapes of the products and the shape an operator gets without the
+// tuner.  Plain host code, so that the rule is tested without a device.
+#pragma once
+
+#include <cstdint>
+
+namespace airg {
+
+// Launch shape of a product: lanes per row in bits 0-7 (0: row-block kernel),
+// the XCD mapping in bit 8, the LDS-staged kernel in bit 9, the
+// entry-staged kernel (256 consecutive rows per workgroup, one lane per row)
+// in bit 10.
+constexpr int kShapeXcd = 1 << 8;
+constexpr int kShapeLds = 1 << 9;
+constexpr int kShapeEntries = 1 << 10;
+
+enum class OpRole { Plain, CPoint, Restrict, Smooth, Top, Coarsest };
+
+// What the rule looks at: the operator's size, the bytes of a stored value and
+// of a vector element, and with compressed columns the widest 64-row window.
+struct OpShape {
+  int64_t rows, nnz;
+  int vbytes, xbytes;
+  bool windows;
+  int64_t max_span;
+};
+
+// A matrix past three quarters of the 256 MB cache is read from HBM by every
+// product; below that it mostly comes from the caches.
+constexpr double kCachedBytes = 192e6;
+
+// Lanes per row, with the XCD mapping (each XCD takes a contiguous eighth of the
+// rows) where xcd allows it.  Measured over every operator of 31 systems (FV
+// 64^2 to 8192^2, DG 1024^2, FD 1803^2 to 3606^2 with all up-smooths, 500 x
+// 26000, batches of 16 and 48, in FP64, FP32 and BF16), the mean time of the
+// shape over the best one's in brackets.
+//
+// From the caches: two lanes from 3.5 entries a row (1.06; one 1.16), 4 from 10
+// (1.01; 2 lanes 1.08), 8 from 24 (1.02; 4 lanes 1.09), 16 from 50 (1.01; 8 lanes
+// 1.05, from 80 on 1.15), 32 from 160 (equal there).  Eighths of the rows gain up
+// to 20% on short rows and lose from about 100 entries a row on, where a row's
+// gathers reach far anyway (130-170 entries: 16 lanes 1.08 with, 1.00 without).
+//
+// From HBM the mapping only spreads the traffic over more pages (FV 8192^2, 1.2 GB
+// of B: 222.8 us with, 213.8 without) and lanes are needed earlier, to keep as
+// many gathers in flight (FV 4096^2, 22.5 entries a row: 188 us with 4 lanes, 174
+// with 8; FV 8192^2, 72.9: 109 with 8, 95.5 with 16).
+//
+// Short operators take more lanes while the launch has fewer than 400,000: up to
+// 8 (from 10 to 24 entries 1.02, 4 lanes 1.10), below 16,384 rows up to 32, and a
+// wavefront a row for rows of 256 and more (733 dense rows: 4.9 us with 32, 3.9
+// with 64).
+inline int default_lanes(int64_t rows, int64_t nnz, double bytes, bool xcd) {
+  const double avg = rows > 0 ? (double)nnz / (double)rows : 0.0;
+  if (bytes > kCachedBytes)
+    return avg <= 3.5 ? 1 : avg <= 10.0 ? 2 : avg <= 16.0 ? 4 : avg <= 40.0 ? 8 : avg <= 160.0 ? 16 : 32;
+  int lanes = avg <= 3.5 ? 1 : avg <= 10.0 ? 2 : avg <= 24.0 ? 4 : avg <= 50.0 ? 8 : avg <= 160.0 ? 16 : 32;
+  const int most = rows >= 16384 ? 8 : rows >= 4096 || avg < 256.0 ? 32 : 64;
+  while (lanes < most && rows * lanes < 400000 && avg >= 4.0 * lanes) lanes <<= 1;
+  return lanes | (xcd && avg <= 100.0 ? kShapeXcd : 0);
+}
+
+inline int default_shape(const OpShape& A, OpRole role) {
+  const double avg = A.rows > 0 ? (double)A.nnz / (double)A.rows : 0.0;
+  // the top matrix's rows are so short that their pointers weigh as an index does
+  const double bytes = (double)(A.vbytes + (A.windows && role != OpRole::Top ? 2 : 4)) * (double)A.nnz;
+  // The entry-staged kernel loads the entries of 256 rows at consecutive
+  // addresses, so more gathers are in flight than one lane a row keeps; below
+  // four workgroups of it a CU the device is not full and a row's entries in
+  // turn are the whole time (FV 64^2 level 1: 8.3 us, 2.8 with 4 lanes a row;
+  // 173,000 rows of 2 entries 3.8 and 3.1, 236,000 of 5 entries 6.1 and 5.2).
+  const bool entries = A.rows >= (int64_t)1 << 18;
+  bool xcd = true;
+  switch (role) {
+    case OpRole::CPoint:
+      // the rows of A_cf and A_cc lie block after block of the nested order, so
+      // eighths of them sweep the domain at once and share nothing (FD 3606^2
+      // level 1, 2.3 entries a row: 82.7 us with the mapping, 61.4 without)
+      xcd = false;
+      break;
+    case OpRole::Restrict:
+      // rows of about 3 entries that gather all over a level's F block (level 1
+      // of FV 2048^2: 18.5 us with one lane a row, 15.9); where rows are longer
+      // two lanes are even or better (level 2: 15.2, 15.8)
+      if (entries && avg > 2.4 && avg <= 3.5) return 1 | kShapeEntries | kShapeXcd;
+      break;
+    case OpRole::Smooth:
+      // FV 2048^2 levels 0 and 1 (1.7 and 4.1 entries a row): 17.6 -> 15.1 and
+      // 16.6 -> 15.7 us; a diagonal (1 entry) and rows of 9 are better with
+      // lanes, and so are rows of 5 where an entry is 6 bytes or less (DG 1024^2
+      // level 1: 16.9 and 16.7 in FP64, 14.9 and 14.2 in FP32, 16.6 and 12.4 in BF16)
+      if (entries && avg > 1.2 && avg <= (A.vbytes == 8 ? 5.5 : 3.5)) return 1 | kShapeEntries | kShapeXcd;
+      break;
+    case OpRole::Top:
+      // read from HBM in consecutive addresses: 5 entries a row gain from 250 MB
+      // on (DG 1024^2: 82.8 us, 82.0), 3 far above it (FV 8192^2, 2.4 GB: 855,
+      // 790; FV 4096^2, 604 MB: 212, 211; batch of 229 MB: 80.6, 87.3)
+      if (avg <= 8.0 && bytes > (avg > 4.0 ? kCachedBytes : 1e9)) return 1 | kShapeEntries;
+      break;
+    case OpRole::Coarsest:
+      // ordered for narrow windows of x, which a workgroup of 64 rows stages in
+      // LDS where it reads each element twice or more (FD 3606^2 with degree 100,
+      // 1.3 times: 112 us staged, 102 with 32 lanes) and two workgroups fit a CU.
+      // In FP64 16 lanes, or 8 where the matrix stays in the caches (FV 2048^2
+      // 16.7 us, 32 lanes unstaged 18.3; FV 4096^2, 139 MB, 26.5, 29.1, with 16
+      // lanes 28.8; the batch of 48, 188 MB, 36.1 with 16, 38.2 with 8, unstaged
+      // 38.9; FV 8192^2, 408 MB, 87, 110, 122), and unstaged below 32,768 rows (25,111
+      // rows 8.2 and 8.6); in FP32 and BF16 from 8192 rows on (13,463 rows 5.5 us,
+      // unstaged 6.2).  The XCD mapping, which leaves a step's result where the next
+      // step reads it, pays while the vectors are short (7,926 rows: a solve of 2.12
+      // ms without and 2.06 with; batch of 48, 139,245 rows: 41.8 and 43.8).
+      if (A.windows && avg >= 48.0 && A.max_span * A.xbytes <= 64 * 1024 && 64.0 * avg >= 2.0 * (double)A.max_span &&
+          A.rows >= (A.xbytes == 8 ? 32768 : 8192))
+        return (A.xbytes == 8 && bytes <= 160e6 ? 8 : 16) | kShapeLds;
+      xcd = A.rows < 8192;
+      break;
+    case OpRole::Plain: break;
+  }
+  return default_lanes(A.rows, A.nnz, bytes, xcd);
+}
+
+}  // namespace airg

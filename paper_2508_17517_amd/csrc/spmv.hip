@@ -650,63 +650,9 @@ static void launch_spmv(const OpView& A, int tpr, int K, const float* x, Epi epi
   }
 }
 
-// The launch shape an operator gets without the tuner.  Lanes per row grow with
-// the mean row length, more slowly than its quarter so that every lane has a
-// few pairs in flight, and further where a short operator would leave the
-// device empty (fewer than 400,000 lanes; more than 16 a row only pay below
-// 16,384 rows, a wavefront a row for rows of 256 and more: 733 dense rows 4.9 us
-// with 32 lanes, 3.9 with 64); each XCD takes a contiguous eighth of the rows.  Measured over
-// the operators of FV 2048^2 (FP64), FV 1501 x 999 (FP32) and DG 1024^2 (BF16)
-// against the former rule (a lane per 4 entries, rows dealt out round robin):
-// products of 8 to 40 entries a row 10.7-15.1 us then, 9.1-14.3 now; the top
-// product of FV 2048^2 44.4 and 36.2 us.
-int pick_tpr(int64_t rows, int64_t nnz) {
-  const double avg = rows > 0 ? (double)nnz / (double)rows : 0.0;
-  const int most = rows >= 16384 ? 16 : rows >= 4096 || avg < 256.0 ? 32 : 64;
-  int lanes = avg <= 3.5 ? 1 : avg <= 10.0 ? 2 : avg <= 24.0 ? 4 : 8;
-  while (lanes < most && rows * lanes < 400000 && avg >= 4.0 * lanes) lanes <<= 1;
-  return lanes | kShapeXcd;
-}
-int pick_shape(const CSR& A, OpRole role, int64_t xbytes) {
-  const double avg = A.rows > 0 ? (double)A.nnz / (double)A.rows : 0.0;
-  // The entry-staged kernel loads the entries of 256 rows at consecutive
-  // addresses, so more gathers are in flight than one lane a row keeps; below
-  // four workgroups of it a CU the device is not full and a row's entries in
-  // turn are the whole time (FV 64^2 level 1: 8.3 us, 2.8 with 4 lanes a row;
-  // 173,000 rows of 2 entries 3.8 and 3.1, 236,000 of 5 entries 6.1 and 5.2).
-  const bool entries = A.rows >= (int64_t)1 << 18;
-  switch (role) {
-    case OpRole::Restrict:
-      // rows of about 3 entries that gather all over a level's F block (level 1
-      // of FV 2048^2: 18.5 us with one lane a row, 15.9); where rows are longer
-      // two lanes are even or better (level 2: 15.2, 15.8)
-      if (entries && avg > 2.4 && avg <= 3.5) return 1 | kShapeEntries | kShapeXcd;
-      break;
-    case OpRole::Smooth:
-      // FV 2048^2 levels 0 and 1 (1.7 and 4.0 entries a row): 17.0 -> 15.0 and
-      // 16.6 -> 15.7 us; 5.3 entries on FV 1501 x 999 9.8 -> 7.6; a diagonal
-      // (1 entry) and rows of 9 are better with lanes
-      if (entries && avg > 1.2 && avg <= 5.5) return 1 | kShapeEntries | kShapeXcd;
-      break;
-    case OpRole::Top:
-      // a matrix beyond three quarters of the 256 MB cache streams from HBM: short
-      // rows then gain from consecutive addresses, and eighths of the rows only
-      // spread the traffic over more pages (250 MB, DG 1024^2: 86.0 -> 82.4 us;
-      // 604 MB, FV 4096^2: 229 -> 212; but 151 MB, FV 2048^2: 36.2 and 37.0, and
-      // 60 MB, 10^6 DG unknowns: 17.9 and 28.9)
-      if (avg <= 8.0 && 12.0 * (double)A.nnz > 192e6) return 1 | kShapeEntries;
-      break;
-    case OpRole::Coarsest:
-      // ordered for narrow windows: x from LDS where the windows leave at least
-      // two workgroups a CU and there are groups for the chip (FV 2048^2
-      // 18.0 -> 16.7 us); below that, a row's length in as few turns as it takes
-      // (3,458 rows: 3.2 us)
-      if (A.col16.get() && A.rows >= 8192 && avg >= 48.0 && A.max_span * xbytes <= 64 * 1024)
-        return (A.rows >= 32768 && xbytes == 8 ? 8 : 16) | kShapeLds | kShapeXcd;
-      break;
-    case OpRole::Plain: break;
-  }
-  return pick_tpr(A.rows, A.nnz);
+int pick_tpr(int64_t rows, int64_t nnz) { return default_lanes(rows, nnz, 12.0 * (double)nnz, true); }
+int pick_shape(const CSR& A, OpRole role, int vbytes, int xbytes) {
+  return default_shape({A.rows, A.nnz, vbytes, xbytes, A.col16.get() != nullptr, A.max_span}, role);
 }
 
 // ------------------------------------------------------------------ epilogues

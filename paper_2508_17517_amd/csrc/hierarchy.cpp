@@ -715,28 +715,28 @@ void finalize_hierarchy(Hierarchy& H) {
     }
   }
   // value copies in the storage precision of the mixed-precision V-cycle
-  auto lower = [&](const CSR& A, DBuf<float>& v32, DBuf<bf16>& v16, bool bf) {
-    if (bf) {
-      v16.alloc(A.nnz, s);
-      convert_d2bf(v16.get(), A.val.get(), A.nnz, s);
-    } else {
-      v32.alloc(A.nnz, s);
-      convert_d2f(v32.get(), A.val.get(), A.nnz, s);
-    }
-  };
-  const bool bf = H.p.precision == AIRG_BF16;
   if (H.p.precision != AIRG_FP64) {
+    const bool bf = H.p.precision == AIRG_BF16;
+    auto lower = [&](const CSR& A, DBuf<float>& v32, DBuf<bf16>& v16) {
+      if (bf) {
+        v16.alloc(A.nnz, s);
+        convert_d2bf(v16.get(), A.val.get(), A.nnz, s);
+      } else {
+        v32.alloc(A.nnz, s);
+        convert_d2f(v32.get(), A.val.get(), A.nnz, s);
+      }
+    };
     for (Level& L : H.levels) {
       if (L.coarsest) {
-        lower(L.A, L.a32, L.a16, bf);
+        lower(L.A, L.a32, L.a16);
         continue;
       }
-      lower(L.Aff, L.ff32, L.ff16, bf);
-      lower(L.B, L.b32, L.b16, bf);
-      lower(L.Z, L.z32, L.z16, bf);
-      if (L.Ahat.rows > 0) lower(L.Ahat, L.hat32, L.hat16, bf);
+      lower(L.Aff, L.ff32, L.ff16);
+      lower(L.B, L.b32, L.b16);
+      lower(L.Z, L.z32, L.z16);
+      if (L.Ahat.rows > 0) lower(L.Ahat, L.hat32, L.hat16);
       for (SolveOp* o : {&L.cf, &L.cc, &L.hat_cc, &L.fc})
-        if (o->m.rows > 0) lower(o->m, o->v32, o->v16, bf);
+        if (o->m.rows > 0) lower(o->m, o->v32, o->v16);
       if (L.dinv.get()) {
         L.dinv32.alloc(L.nF, s);
         convert_d2f(L.dinv32.get(), L.dinv.get(), L.nF, s);
@@ -774,13 +774,14 @@ void finalize_hierarchy(Hierarchy& H) {
   for (Level& L : H.levels) {
     try {
       if (L.coarsest ? !form_coarsest || !dense_newton(L.A, L.roots, L.Aq, s)
-                     : !form_q || !exact_polynomial(L.Aff, L.alpha, value_bytes(H.p.precision), (double)xbytes,
-                                                    L.Aq, s))
+                     : !form_q || !exact_polynomial(L.Aff, L.alpha, vbytes, xbytes, L.Aq, s))
         continue;
-      // the coarsest polynomial in FP32 with BF16 storage too: the steps round A,
-      // not the polynomial
-      if (H.p.precision != AIRG_FP64) lower(L.Aq, L.q32, L.q16, bf && !L.coarsest);
-      L.tpr_q = prepare(L.Aq, L.coarsest ? OpRole::Plain : OpRole::Smooth, L.coarsest ? xbytes : vbytes);
+      // in FP32 with BF16 storage too: the steps round A, not the coefficients
+      if (H.p.precision != AIRG_FP64) {
+        L.q32.alloc(L.Aq.nnz, s);
+        convert_d2f(L.q32.get(), L.Aq.val.get(), L.Aq.nnz, s);
+      }
+      L.tpr_q = prepare(L.Aq, L.coarsest ? OpRole::Plain : OpRole::Smooth, xbytes);
     } catch (const Error& e) {
       if (e.code != AIRG_ERR_NOMEM) throw;
       L.drop_formed();

@@ -75,15 +75,15 @@ struct Level {
   bool a_permuted = false;
 
   // low-precision copies of the solve operators' values (FP32 or BF16 storage)
+  // (a formed polynomial is in FP32 under BF16 storage too)
   DBuf<float> ff32, b32, z32, a32, hat32, q32;
-  DBuf<bf16> ff16, b16, z16, a16, hat16, q16;
+  DBuf<bf16> ff16, b16, z16, a16, hat16;
 
   // back to the polynomial's steps; false where it was not formed
   bool drop_formed() {
     const bool any = Aq.rows > 0;
     Aq = CSR();
     q32.release();
-    q16.release();
     return any;
   }
 

@@ -428,8 +428,9 @@ void neumann_fixed_sparsity(const CSR& Aff, int degree, CSR& out, hipStream_t s)
 void diag_inverse(const CSR& A, DBuf<double>& dinv, hipStream_t s);
 // Q = alpha_0 I + alpha_1 A + ... + alpha_d A^d with nothing dropped but exact
 // zeros, by Horner's rule; false (Q left empty) where one product with Q would
-// not be cheaper than the d products of the matrix-free form.  vbytes and
-// xbytes are the bytes of a stored value and of a vector element in the solve.
+// not be cheaper than the d products of the matrix-free form.  vbytes are the
+// bytes of A's stored value in the solve, xbytes those of a vector element and of
+// Q's value.
 bool exact_polynomial(const CSR& A, const std::vector<double>& alpha, double vbytes, double xbytes,
                       CSR& Q, hipStream_t s);
 // Drop |z| < tol * max_j |z_ij| per row (no lumping), optionally negating.

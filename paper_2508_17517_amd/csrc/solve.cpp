@@ -186,7 +186,7 @@ LevelOps ops_of(const Level& L, int prec) {
   return {op_view(L.Aff, L.ff32, L.ff16, prec), op_view(L.B, L.b32, L.b16, prec),
           op_view(L.Z, L.z32, L.z16, prec), op_view(L.A, L.a32, L.a16, prec),
           op_view(L.Ahat, L.hat32, L.hat16, prec),
-          op_view(L.Aq, L.q32, L.q16, L.coarsest && prec == AIRG_BF16 ? AIRG_FP32 : prec)};
+          op_view(L.Aq, L.q32, DBuf<bf16>(), prec == AIRG_BF16 ? AIRG_FP32 : prec)};
 }
 // the view of A with the activity masks gm (null: unmasked)
 OpView masked(OpView v, const CSR& A, const uint8_t* gm) {

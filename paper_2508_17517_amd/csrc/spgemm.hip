@@ -915,11 +915,11 @@ bool exact_polynomial(const CSR& A, const std::vector<double>& alpha, double vby
   const int64_t n = A.rows;
   if (d < 2 || n <= 0 || A.nnz < n) return false;
   constexpr double kLaunchUs = 2.6, kBytesPerUs = 5.0e6, kWin = 0.9;
-  const double entry = vbytes + 2.0;
   const double free_us =
-      d * (kLaunchUs + (entry * (double)A.nnz + (4.0 + 3.0 * xbytes) * (double)n) / kBytesPerUs);
-  const double max_nnz = std::min(
-      2147483647.0, ((kWin * free_us - kLaunchUs) * kBytesPerUs - (4.0 + 3.0 * xbytes) * (double)n) / entry);
+      d * (kLaunchUs + ((vbytes + 2.0) * (double)A.nnz + (4.0 + 3.0 * xbytes) * (double)n) / kBytesPerUs);
+  const double max_nnz =
+      std::min(2147483647.0, ((kWin * free_us - kLaunchUs) * kBytesPerUs - (4.0 + 3.0 * xbytes) * (double)n) /
+                                 (xbytes + 2.0));
   // the growth of a power's entries over the last one's: 2.8 and more from
   // 8 entries a row on, where a product would only find that out
   auto hopeless = [&](double nnz, double growth, int left) {

@@ -900,26 +900,32 @@ __global__ void add_diag_kernel(int64_t rows, const int32_t* rowptr, const int32
 // The matrix-free smoother reads A and three vectors d times; one product with
 // Q = q(A) reads Q and the vectors once.  With few couplings between F points
 // (1.4 a row on the finest upwind level, 2.0 on the next) Q hardly fills in
-// (1.7 and 4.0 entries a row at d = 4), so the smoother is nearly d times
+// (1.7 and 4.1 entries a row at d = 4), so the smoother is nearly d times
 // cheaper; from about 8 entries a row on, Q holds ten times A's entries and
 // loses.  Both sides are priced as launches * 2.6 us (what a small product
-// takes) plus bytes at 5 TB/s (what the large ones reach), and Q has to win
-// by a tenth.  Small levels are all launches: there Q may be 40 times denser
-// and still wins.  Smoother of one V-cycle, FV 2048^2 in FP64, measured: the
-// finest level 4 x 12.9 us in d products, 19 us in one; the next 4 x 10.1 and
-// 15 us; the third 4 x 10.8 and 33 us.
+// takes) plus bytes at the rate that products reach inside a solve, where the
+// rest of the cycle has been through the caches: 3.8 TB/s for A's short rows, 3.3
+// for Q, whose rows gather further (an entry with an FP32 value counts 8 bytes for
+// that, not 6); and Q has to win by a tenth.  (Back to back
+// on warm caches both reach 4.6 to 5, and by that level 2 of FV 2048^2, 22 entries
+// a row, would win.)  One V-cycle's smoother with Q against the steps, from
+// solves of both, FP64: FV 2048^2 level 0 -59 us, level 1 -40, level 2 -5 of some 45;
+// in FP32 -36, -18 and 0; FV 4096^2 -199, -73 and, level 2, +33; the batch of 48 -312, -147 and +30; FD
+// 3606^2 level 1 (d = 6) -131; DG 1024^2 level 0 -18.  Small levels are all
+// launches: Q may be ten times denser there and still wins (FV 512^2, all levels:
+// -48 us of 278 a cycle).
 bool exact_polynomial(const CSR& A, const std::vector<double>& alpha, double vbytes, double xbytes,
                       CSR& Q, hipStream_t s) {
   Q = CSR();
   const int d = (int)alpha.size() - 1;
   const int64_t n = A.rows;
   if (d < 2 || n <= 0 || A.nnz < n) return false;
-  constexpr double kLaunchUs = 2.6, kBytesPerUs = 5.0e6, kWin = 0.9;
+  constexpr double kLaunchUs = 2.6, kStepBytesPerUs = 3.8e6, kBytesPerUs = 3.3e6, kWin = 0.9;
   const double free_us =
-      d * (kLaunchUs + ((vbytes + 2.0) * (double)A.nnz + (4.0 + 3.0 * xbytes) * (double)n) / kBytesPerUs);
+      d * (kLaunchUs + ((vbytes + 2.0) * (double)A.nnz + (4.0 + 3.0 * xbytes) * (double)n) / kStepBytesPerUs);
   const double max_nnz =
       std::min(2147483647.0, ((kWin * free_us - kLaunchUs) * kBytesPerUs - (4.0 + 3.0 * xbytes) * (double)n) /
-                                 (xbytes + 2.0));
+                                 (6.0 + 0.5 * xbytes));
   // the growth of a power's entries over the last one's: 2.8 and more from
   // 8 entries a row on, where a product would only find that out
   auto hopeless = [&](double nnz, double growth, int left) {

@@ -757,7 +757,7 @@ void finalize_hierarchy(Hierarchy& H) {
       L.tpr_a = prepare(L.A, OpRole::Coarsest, vbytes);
       continue;
     }
-    L.tpr_ff = prepare(L.Aff, OpRole::Smooth, vbytes);
+    L.tpr_ff = prepare(L.Aff, OpRole::Steps, vbytes);
     L.tpr_b = prepare(L.B, OpRole::Plain, vbytes);
     L.tpr_z = prepare(L.Z, OpRole::Restrict, vbytes);
     if (L.Ahat.rows > 0) L.tpr_hat = prepare(L.Ahat, OpRole::Plain, vbytes);
@@ -781,7 +781,7 @@ void finalize_hierarchy(Hierarchy& H) {
         L.q32.alloc(L.Aq.nnz, s);
         convert_d2f(L.q32.get(), L.Aq.val.get(), L.Aq.nnz, s);
       }
-      L.tpr_q = prepare(L.Aq, L.coarsest ? OpRole::Plain : OpRole::Smooth, xbytes);
+      L.tpr_q = prepare(L.Aq, L.coarsest ? OpRole::Plain : OpRole::Formed, xbytes);
     } catch (const Error& e) {
       if (e.code != AIRG_ERR_NOMEM) throw;
       L.drop_formed();

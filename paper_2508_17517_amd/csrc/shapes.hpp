@@ -14,7 +14,7 @@ constexpr int kShapeXcd = 1 << 8;
 constexpr int kShapeLds = 1 << 9;
 constexpr int kShapeEntries = 1 << 10;
 
-enum class OpRole { Plain, CPoint, Restrict, Smooth, Top, Coarsest };
+enum class OpRole { Plain, CPoint, Restrict, Steps, Formed, Top, Coarsest };
 
 // What the rule looks at: the operator's size, the bytes of a stored value and
 // of a vector element, and with compressed columns the widest 64-row window.
@@ -84,11 +84,17 @@ inline int default_shape(const OpShape& A, OpRole role) {
       // two lanes are even or better (level 2: 15.2, 15.8)
       if (entries && avg > 2.4 && avg <= 3.5) return 1 | kShapeEntries | kShapeXcd;
       break;
-    case OpRole::Smooth:
-      // FV 2048^2 levels 0 and 1 (1.7 and 4.1 entries a row): 17.6 -> 15.1 and
-      // 16.6 -> 15.7 us; a diagonal (1 entry) and rows of 9 are better with
-      // lanes, and so are rows of 5 where an entry is 6 bytes or less (DG 1024^2
-      // level 1: 16.9 and 16.7 in FP64, 14.9 and 14.2 in FP32, 16.6 and 12.4 in BF16)
+    case OpRole::Steps:
+      // A_ff where the smoother takes its steps: as the restrictors, rows of 3
+      // entries only (FD 3606^2 level 2: 22.0 -> 20.5 us; 1.8 entries 22.1, 24.6;
+      // 3.9 entries on FV 4096^2 level 2 with two lanes 30.6, 36.3)
+      if (entries && avg > 2.4 && avg <= 3.5) return 1 | kShapeEntries | kShapeXcd;
+      break;
+    case OpRole::Formed:
+      // q(A_ff), whose rows gather further.  FV 2048^2 levels 0 and 1 (1.7 and 4.1
+      // entries a row): 17.6 -> 15.1 and 16.6 -> 15.7 us, FV 4096^2 78.4 -> 63.7 and
+      // 71.2 -> 62.1; a diagonal (1 entry) and rows of 9 are better with lanes, and so
+      // are rows of 4 where an entry is 6 bytes (FV 2048^2 level 1 in FP32: 13.8, 13.7)
       if (entries && avg > 1.2 && avg <= (A.vbytes == 8 ? 5.5 : 3.5)) return 1 | kShapeEntries | kShapeXcd;
       break;
     case OpRole::Top:

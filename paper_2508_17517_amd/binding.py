@@ -208,4 +208,12 @@ def load_host_dense():
     lib.airg_host_numerical_rank.restype = ip
     lib.airg_host_default_shape.argtypes = [ip, c_i64, c_i64, ip, ip, ip, c_i64]
     lib.airg_host_default_shape.restype = ip
+    lib.airg_host_walk_entries.argtypes = [c_i32, c_i32, ip, ip, ip, P(ctypes.c_uint32)]
+    lib.airg_host_walk_entries.restype = ip
+    lib.airg_host_find_col.argtypes = [ctypes.c_void_p, c_i32, c_i32, c_i32]
+    lib.airg_host_find_col.restype = ip
+    lib.airg_host_first_from.argtypes = [ctypes.c_void_p, c_i32, c_i32, c_i64]
+    lib.airg_host_first_from.restype = c_i64
+    lib.airg_host_pairs_before.argtypes = [c_i32]
+    lib.airg_host_pairs_before.restype = c_i64
     return lib

@@ -96,14 +96,14 @@ __global__ __launch_bounds__(256) void strength_kernel(CSRView A, double theta, 
   const int lane = threadIdx.x & (G - 1);
   const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= A.rows) return;
-  const int s = A.rowptr[i], e = A.rowptr[i + 1];
+  const epos s = A.rowptr[i], e = A.rowptr[i + 1];
   double m = 0.0;
-  for (int p = s + lane; p < e; p += G)
+  for (epos p = s + lane; p < e; p += G)
     if (A.col[p] != i) m = fmax(m, fabs(A.val[p]));
 #pragma unroll
   for (int o = G / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, G));
   const double thr = theta * m;
-  for (int p = s + lane; p < e; p += G) {
+  for (epos p = s + lane; p < e; p += G) {
     const double v = A.val[p];
     mask[p] = (A.col[p] != i && v != 0.0 && fabs(v) >= thr) ? 1 : 0;
   }
@@ -353,12 +353,12 @@ __global__ __launch_bounds__(256) void extract_kernel(CSRView A, const int8_t* _
   const int lane = threadIdx.x & (G - 1);
   const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= A.rows || state[i] != rs) return;
-  const int s = A.rowptr[i], e = A.rowptr[i + 1];
+  const epos s = A.rowptr[i], e = A.rowptr[i + 1];
   const int64_t row = rowidx[i];
   const int o = FILL ? rowptr_out[row] : 0;
   int n = 0;
-  for (int p0 = s; p0 < e; p0 += G) {
-    const int p = p0 + lane;
+  for (epos p0 = s; p0 < e; p0 += G) {
+    const epos p = p0 + lane;
     const int j = p < e ? A.col[p] : -1;
     const bool keep = j >= 0 && state[j] == cs;
     const unsigned long long b = group_ballot<G>(keep);

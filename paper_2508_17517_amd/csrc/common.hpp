@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "airg.h"
+#include "entries.hpp"
 #include "error.hpp"
 
 namespace airg {

@@ -1,9 +1,10 @@
-// Host-only C entry points over the dense routines and the launch-shape rule,
-// for CPU tests (not part of the public ABI).
+// Host-only C entry points over the dense routines, the launch-shape rule and
+// the arithmetic on entry positions, for CPU tests (not part of the public ABI).
 #include <cstring>
 #include <vector>
 
 #include "dense.hpp"
+#include "entries.hpp"
 #include "error.hpp"
 #include "shapes.hpp"
 
@@ -68,5 +69,32 @@ int airg_host_default_shape(int role, int64_t rows, int64_t nnz, int vbytes, int
                             int64_t max_span) {
   return default_shape({rows, nnz, vbytes, xbytes, windows != 0, max_span}, (OpRole)role);
 }
+
+// Walks entries s .. e - 1 as the kernels do: in chunks of len (len > 0), or in
+// strides of -len from lane `lane`.  Writes up to cap (first, end) pairs and
+// returns their number, cap + 1 where the walk does not end.
+int airg_host_walk_entries(int32_t s, int32_t e, int len, int lane, int cap, uint32_t* out) {
+  int n = 0;
+  const epos end = e;
+  if (len > 0) {
+    for (epos c0 = s; c0 < end; c0 += len) {
+      if (n == cap) return cap + 1;
+      out[2 * n] = c0;
+      out[2 * n++ + 1] = chunk_end(c0, end, len);
+    }
+  } else {
+    for (epos p = (epos)s + lane; p < end; p += -len) {
+      if (n == cap) return cap + 1;
+      out[2 * n] = p;
+      out[2 * n++ + 1] = p + 1;
+    }
+  }
+  return n;
+}
+int airg_host_find_col(const int32_t* col, int32_t lo, int32_t hi, int32_t j) { return find_col(col, lo, hi, j); }
+int64_t airg_host_first_from(const int32_t* col, int32_t lo, int32_t hi, int64_t w0) {
+  return first_from(col, lo, hi, w0);
+}
+int64_t airg_host_pairs_before(int32_t e) { return pairs_before(e); }
 
 }  // extern "C"

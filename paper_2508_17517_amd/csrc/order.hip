@@ -824,10 +824,10 @@ __global__ __launch_bounds__(256) void bfs_sweep_kernel(CSRView A, int32_t* leve
   // the group acts as one on what its first lane saw
   const int32_t li = __shfl(load(i), 0, G);
   if (li != d && li != -1) return;
-  const int s = A.rowptr[i], e = A.rowptr[i + 1];
+  const epos s = A.rowptr[i], e = A.rowptr[i + 1];
   bool any = false;
-  for (int p0 = s; p0 < e; p0 += G) {
-    const int p = p0 + lane;
+  for (epos p0 = s; p0 < e; p0 += G) {
+    const epos p = p0 + lane;
     const int j = p < e ? A.col[p] : -1;
     const int32_t lj = j >= 0 ? load(j) : -2;
     if (li == d) {
@@ -979,7 +979,7 @@ __global__ __launch_bounds__(256) void landmark_step_kernel(CSRView A, CSRView A
       a0 = A.rowptr[u];
       na = A.rowptr[u + 1] - a0;
       t0 = At.rowptr[u];
-      deg = na + At.rowptr[u + 1] - t0;
+      deg = na + (At.rowptr[u + 1] - t0);
     }
     int dmax = deg;
 #pragma unroll
@@ -1182,7 +1182,7 @@ __global__ __launch_bounds__(256) void coords_down_kernel(CSRView Z, const doubl
   const int64_t c = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (c >= Z.rows) return;
   const unsigned long long x = (unsigned long long)(xyc[c].x * 256.0), y = (unsigned long long)(xyc[c].y * 256.0);
-  for (int p = Z.rowptr[c] + lane; p < Z.rowptr[c + 1]; p += G) {
+  for (epos p = (epos)Z.rowptr[c] + lane, e = Z.rowptr[c + 1]; p < e; p += G) {
     const unsigned long long w = (unsigned long long)(fmin(fabs(Z.val[p]), 4.0) * 65536.0);
     if (w == 0) continue;
     CoordSum* t = sum + Z.col[p];
@@ -1212,7 +1212,7 @@ __global__ __launch_bounds__(256) void coords_up_kernel(const int8_t* __restrict
   }
   const int64_t f = fidx[i];
   double w = 0.0, x = 0.0, y = 0.0;
-  for (int p = Afc.rowptr[f] + lane; p < Afc.rowptr[f + 1]; p += G) {
+  for (epos p = (epos)Afc.rowptr[f] + lane, e = Afc.rowptr[f + 1]; p < e; p += G) {
     const double a = fabs(Afc.val[p]);
     const double2 c = xyc[Afc.col[p]];
     w += a;
@@ -1272,7 +1272,7 @@ __global__ __launch_bounds__(256) void coords_relax_kernel(CSRView A, CSRView At
   const int lane = threadIdx.x & (G - 1);
   const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= A.rows) return;
-  const int s = A.rowptr[i], na = A.rowptr[i + 1] - s, t = At.rowptr[i], deg = na + At.rowptr[i + 1] - t;
+  const int s = A.rowptr[i], na = A.rowptr[i + 1] - s, t = At.rowptr[i], deg = na + (At.rowptr[i + 1] - t);
   double x = 0.0, y = 0.0;
   for (int k = lane; k < deg; k += G) {
     const double2 c = xy[k < na ? A.col[s + k] : At.col[t + k - na]];

@@ -321,12 +321,12 @@ __global__ __launch_bounds__(256) void hash_product_kernel(
     if (NUMERIC) hv[k] = 0.0;
   }
   wave_order();
-  const int s = A.rowptr[i], e = A.rowptr[i + 1];
+  const epos s = A.rowptr[i], e = A.rowptr[i + 1];
   int n = 0;  // columns in the table, the same in every lane of the group
   bool full = false;
-  for (int p0 = s; p0 < e && !full; p0 += G) {
+  for (epos p0 = s; p0 < e && !full; p0 += G) {
     // the next G entries of the row: their rows of B, one per lane
-    const int np = min(G, e - p0);
+    const int np = (int)min((epos)G, e - p0);
     int b0 = 0, b1 = 0;
     double a = 0.0;
     if (lane < np) {
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void hash_product_kernel(
       b1 = bptr[k + 1];
       if (NUMERIC) a = A.val[p0 + lane];
     }
-    int q0 = __shfl(b0, 0, G), q1 = __shfl(b1, 0, G);
+    epos q0 = __shfl(b0, 0, G), q1 = __shfl(b1, 0, G);
     int c = -1;
     double v = 0.0;
     if (q0 + lane < q1) {
@@ -345,7 +345,8 @@ __global__ __launch_bounds__(256) void hash_product_kernel(
     for (int t = 0; t < np; ++t) {
       const double at = NUMERIC ? __shfl(a, t, G) : 0.0;
       // the first entries of the next row
-      int r0 = 0, r1 = 0, cn = -1;
+      epos r0 = 0, r1 = 0;
+      int cn = -1;
       double vn = 0.0;
       if (t + 1 < np) {
         r0 = __shfl(b0, t + 1, G);
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(256) void hash_product_kernel(
           if (NUMERIC) vn = bval[r0 + lane];
         }
       }
-      for (int q = q0; q < q1; q += G) {
+      for (epos q = q0; q < q1; q += G) {
         if (n + G > T) {
           full = true;
           break;
@@ -502,15 +503,9 @@ __global__ __launch_bounds__(64) void window_product_kernel(CSRView A, CSRView B
     wave_order();
     for (int p = s; p < e; ++p) {
       const int k = A.col[p];
-      int lo = B.rowptr[k], hi = B.rowptr[k + 1];
-      const int end = hi;
-      while (lo < hi) {  // the first entry at or past w0
-        const int mid = (lo + hi) >> 1;
-        if (B.col[mid] < w0) lo = mid + 1;
-        else hi = mid;
-      }
+      const epos end = B.rowptr[k + 1], lo = first_from(B.col, B.rowptr[k], end, w0);
       const double a = A.val[p];
-      for (int q = lo + lane; q < end; q += 64) {
+      for (epos q = lo + lane; q < end; q += 64) {
         const int c = B.col[q];
         if (c >= w1) break;
         const int t = (int)(c - w0);
@@ -631,17 +626,6 @@ void one_point_product(const CSR& A, const int32_t* pmap, int64_t nc, CSR& AP, h
 // ------------------------------------------------------------------ fixed sparsity
 // T_out[p] = sum over q in row i (ascending) of T_in[q] * Aff[col(q), col(p)],
 // i.e. (T_in Aff) restricted to the pattern of Aff.
-__device__ __forceinline__ int find_col(const int32_t* col, int lo, int hi, int j) {
-  while (lo < hi) {
-    int mid = (lo + hi) >> 1;
-    int c = col[mid];
-    if (c == j) return mid;
-    if (c < j) lo = mid + 1;
-    else hi = mid;
-  }
-  return -1;
-}
-
 // One thread per output entry p (its row i from the entry's row index): the
 // entry sums over the row's entries q in ascending order.
 __global__ void masked_power_entry_kernel(CSRView Aff, const int32_t* __restrict__ row_of,
@@ -746,7 +730,7 @@ __global__ __launch_bounds__(256) void masked_poly_kernel(CSRView A, PolyCoeffs 
         b0 = A.rowptr[j];
         b1 = A.rowptr[j + 1];
       }
-      int q0 = __shfl(b0, 0, G), q1 = __shfl(b1, 0, G);
+      epos q0 = __shfl(b0, 0, G), q1 = __shfl(b1, 0, G);
       int cc = -1;
       double x = 0.0;
       if (q0 + lane < q1) {
@@ -754,7 +738,8 @@ __global__ __launch_bounds__(256) void masked_poly_kernel(CSRView A, PolyCoeffs 
         x = A.val[q0 + lane];
       }
       for (int t = 0; t < np; ++t) {
-        int r0 = 0, r1 = 0, cn = -1;
+        epos r0 = 0, r1 = 0;
+        int cn = -1;
         double xn = 0.0;
         if (t + 1 < np) {
           r0 = __shfl(b0, t + 1, G);
@@ -765,7 +750,7 @@ __global__ __launch_bounds__(256) void masked_poly_kernel(CSRView A, PolyCoeffs 
           }
         }
         const double w = tin[p0 + t];
-        for (int q = q0; q < q1; q += G) {
+        for (epos q = q0; q < q1; q += G) {
           if (q > q0) {
             cc = -1;
             if (q + lane < q1) {
@@ -1039,14 +1024,14 @@ __global__ __launch_bounds__(256) void rdrop_kernel(CSRView Z, double tol, doubl
   const int lane = threadIdx.x & (G - 1);
   const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= Z.rows) return;
-  const int s = Z.rowptr[i], e = Z.rowptr[i + 1];
+  const epos s = Z.rowptr[i], e = Z.rowptr[i + 1];
   double m = 0.0;
-  for (int p = s + lane; p < e; p += G) m = fmax(m, fabs(Z.val[p]));
+  for (epos p = s + lane; p < e; p += G) m = fmax(m, fabs(Z.val[p]));
   const double thr = tol * group_max<G>(m);
   int n = 0;
   const int o = FILL ? rowptr[i] : 0;
-  for (int p0 = s; p0 < e; p0 += G) {
-    const int p = p0 + lane;
+  for (epos p0 = s; p0 < e; p0 += G) {
+    const epos p = p0 + lane;
     const double v = p < e ? Z.val[p] : 0.0;
     const bool keep = p < e && fabs(v) >= thr;
     const unsigned long long b = group_ballot<G>(keep);
@@ -1098,16 +1083,16 @@ __global__ __launch_bounds__(256) void adrop_kernel(CSRView A, double tol, int l
   const int lane = threadIdx.x & (G - 1);
   const int64_t i = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
   if (i >= A.rows) return;
-  const int s = A.rowptr[i], e = A.rowptr[i + 1];
+  const epos s = A.rowptr[i], e = A.rowptr[i + 1];
   double m = 0.0;
-  for (int p = s + lane; p < e; p += G)
+  for (epos p = s + lane; p < e; p += G)
     if (A.col[p] != i) m = fmax(m, fabs(A.val[p]));
   const double thr = tol * group_max<G>(m);
   // the diagonal first: the dropped values are added to it in column order
   double d = 0.0;
   int dlane = -1;
-  for (int p0 = s; p0 < e; p0 += G) {
-    const int p = p0 + lane;
+  for (epos p0 = s; p0 < e; p0 += G) {
+    const epos p = p0 + lane;
     const bool diag = p < e && A.col[p] == i;
     const unsigned long long b = group_ballot<G>(diag);
     if (b) {
@@ -1119,8 +1104,8 @@ __global__ __launch_bounds__(256) void adrop_kernel(CSRView A, double tol, int l
   int n = 0;
   const int o = FILL ? rowptr[i] : 0;
   int dat = -1;
-  for (int p0 = s; p0 < e; p0 += G) {
-    const int p = p0 + lane;
+  for (epos p0 = s; p0 < e; p0 += G) {
+    const epos p = p0 + lane;
     const int j = p < e ? A.col[p] : -1;
     const double v = p < e ? A.val[p] : 0.0;
     const bool drop = p < e && j != i && fabs(v) < thr;
@@ -1464,7 +1449,7 @@ __global__ __launch_bounds__(256) void col_span_kernel(CSRView A, int64_t nblk, 
   const int64_t r0 = blk << kColBlockShift;
   const int64_t r1 = min(r0 + ((int64_t)1 << kColBlockShift), A.rows);
   int mn = 0x7fffffff, mx = -1;
-  for (int p = A.rowptr[r0] + lane; p < A.rowptr[r1]; p += 64) {
+  for (epos p = (epos)A.rowptr[r0] + lane, e = A.rowptr[r1]; p < e; p += 64) {
     const int c = A.col[p];
     mn = min(mn, c);
     mx = max(mx, c);
@@ -1495,7 +1480,7 @@ __global__ __launch_bounds__(256) void col16_kernel(CSRView A, int64_t nblk, con
   const int64_t r0 = blk << kColBlockShift;
   const int64_t r1 = min(r0 + ((int64_t)1 << kColBlockShift), A.rows);
   const int b = cbase[blk];
-  for (int p = A.rowptr[r0] + (threadIdx.x & 63); p < A.rowptr[r1]; p += 64)
+  for (epos p = (epos)A.rowptr[r0] + (threadIdx.x & 63), e = A.rowptr[r1]; p < e; p += 64)
     col16[p] = b >= 0 ? (uint16_t)(A.col[p] - b) : (uint16_t)0;
 }
 

@@ -46,7 +46,7 @@ struct CSRT {
     return 0;
   }
   // the column of entry p in a row of base b (callers pass b >= 0 only with C16)
-  __device__ __forceinline__ int column(int p, int b) const {
+  __device__ __forceinline__ int column(epos p, int b) const {
     if constexpr (C16) return b + (int)col16[p];
     return col[p];
   }
@@ -66,14 +66,14 @@ constexpr int unroll_for() { return 4; }
 
 // sum over entries p = s, s + 1, ... < e of val[p] * x[col[p]], in that order
 template <int U, class MV, bool C16, class X, class XI>
-__device__ __forceinline__ X row_dot_cols(const CSRT<MV, C16>& A, int s, int e, int b,
+__device__ __forceinline__ X row_dot_cols(const CSRT<MV, C16>& A, epos s, epos e, int b,
                                           const XI* __restrict__ x, X sum) {
-  for (int p0 = s; p0 < e; p0 += U) {
+  for (epos p0 = s; p0 < e; p0 += U) {
     int col[U];
     X v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int p = p0 + u;
+      const epos p = p0 + u;
       col[u] = p < e ? A.column(p, b) : -1;
       v[u] = p < e ? (X)ldv(A.val[p]) : X(0);
     }
@@ -187,7 +187,7 @@ __device__ __forceinline__ X add_pairs(const XI* __restrict__ gx, const int (&c0
 template <int TPR, int U, bool OFF, class MV, bool C16, class X, class XI>
 __device__ __forceinline__ X row_dot_pairs_cols(const CSRT<MV, C16>& A, int s, int e, int b,
                                                 int lane, const XI* __restrict__ gx, X sum) {
-  const int qe = (e + 1) >> 1;
+  const int qe = (int)pairs_before(e);
   for (int q0 = (s >> 1) + lane; q0 < qe; q0 += TPR * U) {
     int c0[U], c1[U];
     X v0[U], v1[U];
@@ -261,16 +261,16 @@ struct ColVec {  // only the element's own alignment is promised
   typedef T type __attribute__((ext_vector_type(C), aligned(sizeof(T))));
 };
 template <int C, class MV, bool C16, class X, class XI>
-__device__ __forceinline__ void row_dot_cols_block(const CSRT<MV, C16>& A, int s, int e, int step, int b,
+__device__ __forceinline__ void row_dot_cols_block(const CSRT<MV, C16>& A, epos s, epos e, int step, int b,
                                                    const XI* __restrict__ x, int kshift, X (&sum)[C]) {
   using V = typename ColVec<XI, C>::type;
   constexpr int U = 4;
-  for (int p0 = s; p0 < e; p0 += U * step) {
+  for (epos p0 = s; p0 < e; p0 += U * step) {
     int col[U];
     X v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int p = p0 + u * step;
+      const epos p = p0 + u * step;
       col[u] = p < e ? A.column(p, b) : -1;
       v[u] = p < e ? (X)ldv(A.val[p]) : X(0);
     }
@@ -304,7 +304,8 @@ __global__ __launch_bounds__(256) void spmm_kernel(CSRT<MV, C16> A, const XI* __
   X sum[C];
 #pragma unroll
   for (int q = 0; q < C; ++q) sum[q] = X(0);
-  const int rs = A.rowptr[row] + lane, re = A.rowptr[row + 1], b = A.base(row);
+  const epos rs = (epos)A.rowptr[row] + lane, re = A.rowptr[row + 1];
+  const int b = A.base(row);
   bool wide = true;  // uniform over the wavefront: its rows lie in one 64-row block
   if constexpr (C16) {
     if (b < 0) {
@@ -347,22 +348,22 @@ __global__ __launch_bounds__(256) void spmv_rowblock_kernel(CSRT<MV, C16> A,
   const int64_t row = (int64_t)r0 + t;
   const bool mine = row < r1;
   typename Epi::Pre pre{};
-  int rs = 0, re = 0;
+  epos rs = 0, re = 0;
   if (mine) {
     pre = epi.pre(A.out_row(row));
     rs = A.rowptr[row];
     re = A.rowptr[row + 1];
   }
-  const int p0 = A.rowptr[r0], p1 = (!MASK || A.computed(r0)) ? A.rowptr[r1] : p0;
+  const epos p0 = A.rowptr[r0], p1 = (!MASK || A.computed(r0)) ? A.rowptr[r1] : p0;
   const int base = A.base(r0);  // one 64-row group per block
   X sum = 0;
-  for (int c0 = p0; c0 < p1; c0 += kRowBlockNnz) {  // one pass unless a single long row
-    const int c1 = min(c0 + kRowBlockNnz, p1);
+  for (epos c0 = p0; c0 < p1; c0 += kRowBlockNnz) {  // one pass unless a single long row
+    const epos c1 = chunk_end(c0, p1, kRowBlockNnz);
     int col[8];
     X v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int p = c0 + t + 256 * u;
+      const epos p = c0 + t + 256 * u;
       bool in = p < c1;
       if constexpr (C16) col[u] = in ? (base >= 0 ? A.column(p, base) : A.col[p]) : 0;
       else col[u] = in ? A.col[p] : 0;
@@ -370,13 +371,13 @@ __global__ __launch_bounds__(256) void spmv_rowblock_kernel(CSRT<MV, C16> A,
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int p = c0 + t + 256 * u;
+      const epos p = c0 + t + 256 * u;
       if (p < c1) prod[p - c0] = v[u] * (X)x[col[u]];
     }
     __syncthreads();
     if (mine) {
-      const int e = min(re, c1);
-      for (int p = max(rs, c0); p < e; ++p) sum = sum + prod[p - c0];
+      const epos e = min(re, c1);
+      for (epos p = max(rs, c0); p < e; ++p) sum = sum + prod[p - c0];
     }
     __syncthreads();
   }
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(256) void spmv_entries_kernel(CSRT<MV, C16> A, cons
   const bool live = row < A.rows;
   const int64_t rend = r0 + 256 < A.rows ? r0 + 256 : A.rows;
   typename Epi::Pre pre{};
-  int rs = 0, re = 0;
+  epos rs = 0, re = 0;
   if (live) {
     pre = epi.pre(A.out_row(row));
     rs = A.rowptr[row];
@@ -415,7 +416,8 @@ __global__ __launch_bounds__(256) void spmv_entries_kernel(CSRT<MV, C16> A, cons
   }
   // first entry of each 64-row group of the block (gstart[4]: the block's end),
   // the group's column base and whether it is computed
-  int gstart[5], gbase[4];
+  epos gstart[5];
+  int gbase[4];
   bool gon[4];
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
@@ -426,13 +428,13 @@ __global__ __launch_bounds__(256) void spmv_entries_kernel(CSRT<MV, C16> A, cons
   }
   gstart[4] = A.rowptr[rend];
   X sum = 0;
-  for (int c0 = gstart[0]; c0 < gstart[4]; c0 += kEntryChunk) {
-    const int c1 = c0 + kEntryChunk < gstart[4] ? c0 + kEntryChunk : gstart[4];
+  for (epos c0 = gstart[0]; c0 < gstart[4]; c0 += kEntryChunk) {
+    const epos c1 = chunk_end(c0, gstart[4], kEntryChunk);
     int col[4];
     X v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int p = c0 + t + 256 * u;
+      const epos p = c0 + t + 256 * u;
       const int g = (p >= gstart[1]) + (p >= gstart[2]) + (p >= gstart[3]);
       col[u] = -1;
       v[u] = X(0);
@@ -450,8 +452,8 @@ __global__ __launch_bounds__(256) void spmv_entries_kernel(CSRT<MV, C16> A, cons
       if (col[u] >= 0) prod[t + 256 * u] = v[u] * xv[u];
     __syncthreads();
     if (live) {
-      const int e = re < c1 ? re : c1;
-      for (int p = rs > c0 ? rs : c0; p < e; ++p) sum = sum + prod[p - c0];
+      const epos e = re < c1 ? re : c1;
+      for (epos p = rs > c0 ? rs : c0; p < e; ++p) sum = sum + prod[p - c0];
     }
     __syncthreads();
   }
@@ -511,7 +513,7 @@ __global__ __launch_bounds__(64 * TPR) void spmv_lds_kernel(CSRT<MV, true> A,
   if (staged) {
     // the lane's first U pairs are loaded before the x window, so the two
     // memory round trips overlap; the LDS gathers wait for the barrier
-    const int qe = (e + 1) >> 1;
+    const int qe = (int)pairs_before(e);
     int q0 = (s >> 1) + lane;
     int c0[U], c1[U];
     X v0[U], v1[U];
@@ -1005,20 +1007,20 @@ __global__ __launch_bounds__(256) void spmv_seq_kernel(const int32_t* __restrict
   const int t = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * per, r1 = min(r0 + per, rows);
   const bool mine = t < r1 - r0;
-  int rs = 0, re = 0;
+  epos rs = 0, re = 0;
   if (mine) {
     rs = rowptr[r0 + t];
     re = rowptr[r0 + t + 1];
   }
-  const int p0 = rowptr[r0], p1 = rowptr[r1];
+  const epos p0 = rowptr[r0], p1 = rowptr[r1];
   double sum = 0.0;
-  for (int c0 = p0; c0 < p1; c0 += kSeqChunk) {
-    const int c1 = min(c0 + kSeqChunk, p1);
+  for (epos c0 = p0; c0 < p1; c0 += kSeqChunk) {
+    const epos c1 = chunk_end(c0, p1, kSeqChunk);
     int c[8];
     double v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int p = c0 + t + 256 * u;
+      const epos p = c0 + t + 256 * u;
       c[u] = p < c1 ? col[p] : -1;
       v[u] = p < c1 ? val[p] : 0.0;
     }
@@ -1027,8 +1029,8 @@ __global__ __launch_bounds__(256) void spmv_seq_kernel(const int32_t* __restrict
       if (c[u] >= 0) prod[t + 256 * u] = v[u] * x[c[u]];
     __syncthreads();
     if (mine) {
-      const int e = min(re, c1);
-      for (int p = max(rs, c0); p < e; ++p) sum = sum + prod[p - c0];
+      const epos e = min(re, c1);
+      for (epos p = max(rs, c0); p < e; ++p) sum = sum + prod[p - c0];
     }
     __syncthreads();
   }

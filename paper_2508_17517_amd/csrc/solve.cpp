@@ -1302,10 +1302,11 @@ int autotune(Hierarchy& H, Workspace& W, int reps, std::vector<airg_tune_entry>&
         const int shape = base | (xcd << 8);
         const double us = g.f64 ? time_product<double>(g.A, shape, x64, W.w.get(), reps, W, s)
                                 : time_product<float>(g.A, shape, x32, W.e32.get(), reps, W, s);
-        if (shape == *g.tpr) e.default_us = us;
+        const bool untuned = shape == (*g.tpr & ~kShapeColumnsXcd);
+        if (untuned) e.default_us = us;
         if (us < e.best_us) {
           e.best_us = us;
-          best = shape;
+          best = untuned ? *g.tpr : shape;
         }
       }
     e.lanes = best & 0xff;

@@ -621,7 +621,7 @@ static void launch_spmv_t(const OpView& Av, int shape, int K, const XI* x, Epi e
     }
   } else {
     if (K > 64 || (K & (K - 1)) != 0) fail(AIRG_ERR_INTERNAL, "column count must be a power of two <= 64");
-    launch_spmm<MV, C16, X>(A, Av.nnz, K, x, epi, xcd, s);
+    launch_spmm<MV, C16, X>(A, Av.nnz, K, x, epi, xcd | (shape & kShapeColumnsXcd ? 1 : 0), s);
   }
   AIRG_CHECK_LAUNCH();
 }
@@ -654,7 +654,8 @@ static void launch_spmv(const OpView& A, int tpr, int K, const float* x, Epi epi
 
 int pick_tpr(int64_t rows, int64_t nnz) { return default_lanes(rows, nnz, 12.0 * (double)nnz, true); }
 int pick_shape(const CSR& A, OpRole role, int vbytes, int xbytes) {
-  return default_shape({A.rows, A.nnz, vbytes, xbytes, A.col16.get() != nullptr, A.max_span}, role);
+  return default_shape({A.rows, A.nnz, vbytes, xbytes, A.col16.get() != nullptr, A.max_span}, role) |
+         kShapeColumnsXcd;
 }
 
 // ------------------------------------------------------------------ epilogues

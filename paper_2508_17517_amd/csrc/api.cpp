@@ -244,7 +244,8 @@ int columns_together(int64_t n, int cnt) {
 
 // Up to 64 columns are solved together as K interleaved columns, K the next
 // power of two (padding columns are zero), fewer when n K would pass 2^31 or
-// the padding would cost more than another solve.
+// the padding would cost more than another solve.  Groups that only such a split
+// made write their solutions together, after the last of them succeeded.
 int solve_columns(airg_ctx* c, Hierarchy& H, Workspace& W, std::map<int, std::unique_ptr<Workspace>>& Wk,
                   int nrhs, const double* b, int64_t ldb, double* x, int64_t ldx, int guess,
                   airg_solve_info* info) {
@@ -254,11 +255,16 @@ int solve_columns(airg_ctx* c, Hierarchy& H, Workspace& W, std::map<int, std::un
   if (!H.seg.empty())
     fail(AIRG_ERR_INVALID, "a batch handle solves through airg_solve_batch (one entry per problem)");
   int status = AIRG_OK;
+  struct Group {
+    const Workspace* ws;
+    int k0, cnt;
+  };
+  std::vector<Group> kept;  // solved and not yet stored; a split's groups have workspaces of their own
   for (int k0 = 0; k0 < nrhs;) {
     // K interleaved columns, with n K elements addressable by one launch
     int kmax = 64;
     while (kmax > 1 && H.n0 * (int64_t)kmax > (int64_t)INT32_MAX) kmax >>= 1;
-    const int cnt = columns_together(H.n0, std::min(kmax, nrhs - k0));
+    const int all = std::min(kmax, nrhs - k0), cnt = columns_together(H.n0, all);
     int K = 1;
     while (K < cnt) K <<= 1;
     Workspace* ws = &W;
@@ -274,7 +280,7 @@ int solve_columns(airg_ctx* c, Hierarchy& H, Workspace& W, std::map<int, std::un
     int st;
     try {
       st = fgmres_solve(H, *ws, b + (int64_t)k0 * ldb, ldb, x + (int64_t)k0 * ldx, ldx, cnt,
-                        guess != 0, info ? info + k0 : nullptr);
+                        guess != 0, info ? info + k0 : nullptr, cnt == all);
     } catch (const Error&) {
       // a persistent coarse solve whose barrier gave up leaves garbage that
       // can also break the outer loop down: report the cause
@@ -283,6 +289,13 @@ int solve_columns(airg_ctx* c, Hierarchy& H, Workspace& W, std::map<int, std::un
       throw;
     }
     if (st != AIRG_OK) status = st;
+    if (cnt < all) {
+      kept.push_back({ws, k0, cnt});
+    } else if (!kept.empty()) {
+      for (const Group& g : kept) store_solution(H, *g.ws, x + (int64_t)g.k0 * ldx, ldx, g.cnt);
+      kept.clear();
+      AIRG_HIP(hipStreamSynchronize(H.s));
+    }
     k0 += cnt;
   }
   return status;

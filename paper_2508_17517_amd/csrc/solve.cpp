@@ -855,8 +855,14 @@ void vcycle(const Hierarchy& H, Workspace& W, const double* in, double* e64, flo
   vcycle_launches(H, W, in, e64, e32, in32_ready, H.s);
 }
 
+void store_solution(const Hierarchy& H, const Workspace& W, double* x, int64_t ldx, int kvalid) {
+  const int32_t* pos = H.levels[0].pos.get();
+  if (W.K > 1) launch_gather_cols(x, ldx, W.xperm.get(), pos, H.n0, W.K, kvalid, H.s);
+  else launch_gather(x, W.xperm.get(), pos, H.n0, H.s);
+}
+
 int fgmres_solve(const Hierarchy& H, Workspace& W, const double* b, int64_t ldb, double* x,
-                 int64_t ldx, int kvalid, bool guess, airg_solve_info* info) {
+                 int64_t ldx, int kvalid, bool guess, airg_solve_info* info, bool store) {
   hipStream_t s = H.s;
   const int K = W.K;
   const int64_t n = H.n0 * K;  // stacked length
@@ -883,8 +889,7 @@ int fgmres_solve(const Hierarchy& H, Workspace& W, const double* b, int64_t ldb,
     std::vector<airg_solve_info> res;
     bool ok = false;
     solve_processes(H, W, P, res, ok);
-    if (K > 1) launch_gather_cols(x, ldx, W.xperm.get(), pos, H.n0, K, kvalid, s);
-    else launch_gather(x, W.xperm.get(), pos, H.n0, s);
+    if (store) store_solution(H, W, x, ldx, kvalid);
     AIRG_HIP(hipEventRecord(W.ev1, s));
     AIRG_HIP(hipEventSynchronize(W.ev1));
     float ms = 0.f;
@@ -1102,7 +1107,7 @@ int fgmres_solve(const Hierarchy& H, Workspace& W, const double* b, int64_t ldb,
       else launch_basis_combine(W.xperm.get(), Zb, ld, W.ybuf.get(), k, n, s);
     }
   }
-  launch_gather(x, W.xperm.get(), pos, H.n0, s);
+  if (store) store_solution(H, W, x, ldx, kvalid);
   if (!converged) status = AIRG_NOT_CONVERGED;
   AIRG_HIP(hipEventRecord(W.ev1, s));
   AIRG_HIP(hipEventSynchronize(W.ev1));

@@ -84,9 +84,11 @@ void vcycle(const Hierarchy& H, Workspace& W, const double* in, double* e64,
 // one process per problem, with kernels over each problem's ranges of the
 // nested numbering; otherwise one process runs over the block-diagonal
 // system until every problem reaches |r_p| <= rtol |b_p|.  info receives
-// one entry per column or problem.
+// one entry per column or problem.  Without `store` the solution stays in the
+// workspace until store_solution writes it.
 int fgmres_solve(const Hierarchy& H, Workspace& W, const double* b, int64_t ldb, double* x,
-                 int64_t ldx, int kvalid, bool guess, airg_solve_info* info);
+                 int64_t ldx, int kvalid, bool guess, airg_solve_info* info, bool store = true);
+void store_solution(const Hierarchy& H, const Workspace& W, double* x, int64_t ldx, int kvalid);
 
 // Replays one V-cycle's launches of a kernel class `reps` times between HIP
 // events (airg_time_kernels).

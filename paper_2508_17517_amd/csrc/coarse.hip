@@ -469,6 +469,7 @@ bool dense_newton(const CSR& A, const std::vector<cplx>& roots, CSR& Q, hipStrea
   }
   DBuf<double> d(h.size(), s);
   d.from_host(h.data(), h.size());
+  AIRG_HIP(hipStreamSynchronize(s));  // h goes out of scope, by an allocation that fails too
   const int64_t nnz = (int64_t)n * n;
   Q.rows = Q.cols = n;
   Q.nnz = nnz;

@@ -183,9 +183,14 @@ typedef struct {
   int32_t pmisr_rounds[AIRG_MAX_LEVELS];
   double trunc_rel[AIRG_MAX_LEVELS];       /* truncation test result (NaN if not tested) */
   double grid_complexity;                  /* sum n_l / n_0 */
-  double cycle_complexity;                 /* V-cycle FLOPs / FLOPs of one top-grid SpMV */
-  double storage_complexity;               /* nnz kept for the solve / nnz(A_0) */
-  double vcycle_bytes;                     /* algorithmic HBM bytes of one V-cycle */
+  double cycle_complexity;                 /* V-cycle FLOPs / FLOPs of one top-grid SpMV, and */
+  double storage_complexity;               /* nnz kept for the solve / nnz(A_0), of the algorithm
+                                              as the paper counts it: every polynomial applied
+                                              step by step, also where the handle multiplies
+                                              with the polynomial formed as one matrix, which
+                                              it then keeps besides (airg_formed_nnz) */
+  double vcycle_bytes;                     /* algorithmic HBM bytes of one V-cycle as the
+                                              handle runs it, formed polynomials included */
   double setup_ms;                         /* device+host time of airg_setup */
   double setup_component_ms[8];            /* cf split, prolongator, gmres poly,
                                               restrictor spgemm, coarse spgemm,
@@ -283,6 +288,12 @@ int airg_trim(airg_handle h);
 
 /* Hierarchy statistics. */
 int airg_get_stats(airg_handle h, airg_stats* s);
+
+/* Entries of the matrix that a level's polynomial is formed as (the smoother's
+ * q(A_ff), on the coarsest level the Newton polynomial), 0 where it is applied
+ * step by step.  A V-cycle then does 2 *nnz flops there in place of the d
+ * products with A_ff (the Newton products). */
+int airg_formed_nnz(airg_handle h, int level, int64_t* nnz);
 
 /* Level sizes and level arrays (the arrays need keep_setup_data = 1, except
  * for the coarsest level's matrix and roots and every level's coefficients). */

@@ -127,7 +127,14 @@ class Solver:
     def stats(self):
         s = binding.Stats()
         binding.check(self.lib.airg_get_stats(self.h, ctypes.byref(s)), self.lib)
-        return s.as_dict()
+        d = s.as_dict()
+        # entries of each level's polynomial where it is formed as one matrix, else 0
+        v = ctypes.c_int64()
+        d["nnz_formed"] = []
+        for l in range(d["levels"]):
+            binding.check(self.lib.airg_formed_nnz(self.h, l, ctypes.byref(v)), self.lib)
+            d["nnz_formed"].append(v.value)
+        return d
 
     def time_kernels(self, cls="poly", reps=20):
         """Average launch time and algorithmic bytes of one kernel class of the

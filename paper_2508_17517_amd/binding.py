@@ -121,6 +121,7 @@ SYMBOLS = {
     "airg_adjoint_solve": (c_i32, [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, c_i64,
                                    ctypes.c_void_p, c_i64, ctypes.c_int, P(SolveInfo)]),
     "airg_get_stats": (c_i32, [ctypes.c_void_p, P(Stats)]),
+    "airg_formed_nnz": (c_i32, [ctypes.c_void_p, ctypes.c_int, P(c_i64)]),
     "airg_trim": (c_i32, [ctypes.c_void_p]),
     "airg_level_info_get": (c_i32, [ctypes.c_void_p, ctypes.c_int, P(LevelInfo)]),
     "airg_export_level": (c_i32, [ctypes.c_void_p, ctypes.c_int, P(LevelArrays)]),

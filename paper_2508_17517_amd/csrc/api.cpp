@@ -524,6 +524,15 @@ int airg_get_stats(airg_handle h, airg_stats* s) {
   });
 }
 
+int airg_formed_nnz(airg_handle h, int level, int64_t* nnz) {
+  return guard([&]() {
+    airg_ctx* c = handle_of(h);
+    if (!nnz || level < 0 || level >= (int)c->H.levels.size()) fail(AIRG_ERR_INVALID, "bad level");
+    *nnz = c->H.levels[level].Aq.nnz;
+    return (int)AIRG_OK;
+  });
+}
+
 int airg_level_info_get(airg_handle h, int level, airg_level_info* out) {
   return guard([&]() {
     airg_ctx* c = handle_of(h);

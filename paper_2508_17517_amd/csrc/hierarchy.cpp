@@ -1006,7 +1006,7 @@ void hierarchy_stats(const Hierarchy& H, airg_stats* st) {
       st->coarse_roots = (int)L.roots.size();
     } else {
       const int d = (int)L.alpha.size() - 1;
-      // complexities in the paper's terms: Z, A_fc and A_ff (d + 1 times), or
+      // complexities in the paper's terms, whatever is formed: Z, A_fc and A_ff (d + 1 times), or
       // Z, A_fc, A_ff and Ahat^{-1} once each with the assembled smoother
       const bool asm_smoother = L.Ahat.rows > 0;
       const double smooth = asm_smoother ? (double)L.Aff.nnz + (double)L.Ahat.nnz

@@ -891,26 +891,33 @@ __global__ void add_diag_kernel(int64_t rows, const int32_t* rowptr, const int32
 // takes) plus bytes at the rate that products reach inside a solve, where the
 // rest of the cycle has been through the caches: 3.8 TB/s for A's short rows, 3.3
 // for Q, whose rows gather further (an entry with an FP32 value counts 8 bytes for
-// that, not 6); and Q has to win by a tenth.  (Back to back
-// on warm caches both reach 4.6 to 5, and by that level 2 of FV 2048^2, 22 entries
-// a row, would win.)  One V-cycle's smoother with Q against the steps, from
+// that, not 6), and 4.5 from 64 entries a row on; and Q has to win by a tenth.
+// (Back to back on warm caches all reach 4.6 to 5, and by that level 2 of FV 2048^2,
+// 22 entries a row, would win.)  One V-cycle's smoother with Q against the steps, from
 // solves of both, FP64: FV 2048^2 level 0 -59 us, level 1 -40, level 2 -5 of some 45;
 // in FP32 -36, -18 and 0; FV 4096^2 -199, -73 and, level 2, +33; the batch of 48 -312, -147 and +30; FD
 // 3606^2 level 1 (d = 6) -131; DG 1024^2 level 0 -18.  Small levels are all
 // launches: Q may be ten times denser there and still wins (FV 512^2, all levels:
-// -48 us of 278 a cycle).
+// -48 us of 278 a cycle).  Priced at 3.3 the long rows of small systems kept their
+// steps: FV 512^2 levels 4 and 5 (198 and 303 entries a row) 2.08 ms a solve, 1.96
+// formed; DG 193 x 180 level 3 (232) 2.33 and 2.23; 6 problems of 256^2 level 4
+// (176) 2.63 and 2.58, FP32 2.50 and 2.44.
 bool exact_polynomial(const CSR& A, const std::vector<double>& alpha, double vbytes, double xbytes,
                       CSR& Q, hipStream_t s) {
   Q = CSR();
   const int d = (int)alpha.size() - 1;
   const int64_t n = A.rows;
   if (d < 2 || n <= 0 || A.nnz < n) return false;
-  constexpr double kLaunchUs = 2.6, kStepBytesPerUs = 3.8e6, kBytesPerUs = 3.3e6, kWin = 0.9;
+  constexpr double kLaunchUs = 2.6, kStepBytesPerUs = 3.8e6, kBytesPerUs = 3.3e6, kLongBytesPerUs = 4.5e6,
+                   kWin = 0.9;
   const double free_us =
       d * (kLaunchUs + ((vbytes + 2.0) * (double)A.nnz + (4.0 + 3.0 * xbytes) * (double)n) / kStepBytesPerUs);
-  const double max_nnz =
-      std::min(2147483647.0, ((kWin * free_us - kLaunchUs) * kBytesPerUs - (4.0 + 3.0 * xbytes) * (double)n) /
-                                 (6.0 + 0.5 * xbytes));
+  auto fits = [&](double bytes_per_us) {  // the entries that Q may have at that rate
+    return std::min(2147483647.0, ((kWin * free_us - kLaunchUs) * bytes_per_us - (4.0 + 3.0 * xbytes) * (double)n) /
+                                      (6.0 + 0.5 * xbytes));
+  };
+  const double long_rows = 64.0 * (double)n, max_short = fits(kBytesPerUs), max_long = fits(kLongBytesPerUs);
+  const double max_nnz = max_long >= long_rows ? max_long : max_short;
   // the growth of a power's entries over the last one's: 2.8 and more from
   // 8 entries a row on, where a product would only find that out
   auto hopeless = [&](double nnz, double growth, int left) {
@@ -937,6 +944,7 @@ bool exact_polynomial(const CSR& A, const std::vector<double>& alpha, double vby
     add_diag(T, alpha[k]);
     P = std::move(T);
   }
+  if ((double)P.nnz > max_short && (double)P.nnz < long_rows) return false;
   if (fetch(missing.get(), s)) return false;
   Q = std::move(P);
   return true;

@@ -118,11 +118,21 @@ inline int default_shape(const OpShape& A, OpRole role) {
       // 38.9; FV 8192^2, 408 MB, 87, 110, 122), and unstaged below 32,768 rows (25,111
       // rows 8.2 and 8.6); in FP32 and BF16 from 8192 rows on (13,463 rows 5.5 us,
       // unstaged 6.2).  The XCD mapping, which leaves a step's result where the next
-      // step reads it, pays while the vectors are short (7,926 rows: a solve of 2.12
-      // ms without and 2.06 with; batch of 48, 139,245 rows: 41.8 and 43.8).
+      // step reads it, pays while the vectors are short: staged below 40,000 rows
+      // (solves in ms without and with it: 13,382 rows 5.12 and 5.09, 28,842 in BF16
+      // 9.39 and 9.14, 36,168 6.65 and 6.54; 16,771 3.75 and 3.83; a batch's 42,409
+      // 5.45 and 5.60, 139,245 41.8 and 43.8), unstaged below 8192 (7,926 rows 2.12
+      // and 2.06).
       if (A.windows && avg >= 48.0 && A.max_span * A.xbytes <= 64 * 1024 && 64.0 * avg >= 2.0 * (double)A.max_span &&
           A.rows >= (A.xbytes == 8 ? 32768 : 8192))
-        return (A.xbytes == 8 && bytes <= 160e6 ? 8 : 16) | kShapeLds;
+        return (A.xbytes == 8 && bytes <= 160e6 ? 8 : 16) | kShapeLds | (A.rows < 40000 ? kShapeXcd : 0);
+      // Unstaged, 32 lanes pay from 80 entries a row, and from 16,384 rows on, where
+      // 16 lanes are enough wavefronts, from 256 (whole solves in ms with 16 and 32
+      // lanes: 6 problems of 256^2, 66 entries, 2.54 and 2.68; FV 1300^2, 15,514 rows
+      // of 172 entries, 6.60 and 6.46; FD 2000^2, 19,704 of 249, 16.62 and 17.06; FD
+      // 3606^2, 26,974 of 345, 26.49 and 26.37).
+      if (A.rows >= 8192 && bytes <= kCachedBytes && avg > 50.0 && avg <= (A.rows >= 16384 ? 256.0 : 80.0))
+        return 16;
       xcd = A.rows < 8192;
       break;
     case OpRole::Plain: break;

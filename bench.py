@@ -70,7 +70,7 @@ def stream_bandwidth(kind, nbytes, blocks=8192, reps=20):
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "fv2048_poly_hbm_traffic.md")
 # sources that decide the poly-SpMV launches and their operators
 TRAFFIC_SOURCES = ["spmv.hip", "hierarchy.cpp", "solve.cpp", "order.hip", "spgemm.hip",
-                   "common.hpp"]
+                   "common.hpp", "entries.hpp", "shapes.hpp"]
 
 
 def kernel_source_digest():
